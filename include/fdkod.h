@@ -187,14 +187,17 @@ fdkod_status fdkod_backproject(fdkod_plan_t plan, const void* filt, float* vol,
 
 /* ------------------------------------------------------------------ tuning
  * Kernel shapes are chosen per plan: the backprojection's slices per thread
- * and LDS footprint / angles per stage, and the decimation's column chunks.
- * fdkod_plan_create picks a default that holds the plan's geometry (or the
- * entry of the file named by the environment variable FDKOD_TUNE_CACHE);
- * fdkod_tune measures the alternatives.                                    */
+ * and the decimation's column chunks.  fdkod_plan_create picks a default that
+ * holds the plan's geometry (or the entry of the file named by the
+ * environment variable FDKOD_TUNE_CACHE); fdkod_tune measures the
+ * alternatives.  The backprojection's tile, footprint and angle groups follow
+ * from z_run, the geometry and the volume's size; tile_w, tile_h and
+ * angles_per_stage are part of a variant's key and have to hold the plan's
+ * block footprint, but select nothing beyond it.                           */
 typedef struct {
-    int32_t z_run;            /* slices per backprojection thread: 16 or 32 */
-    int32_t tile_w, tile_h;   /* LDS footprint of a 16 x 16 x z_run block: 32/64 x 48/64 */
-    int32_t angles_per_stage; /* angles staged in LDS per barrier: 1, 2 or 4 */
+    int32_t z_run;            /* slices per backprojection thread, at most: 16, 32 or 64 */
+    int32_t tile_w, tile_h;   /* footprint of a 16 x 16 x z_run block: 32/64 x 48/64/96 */
+    int32_t angles_per_stage; /* 1, 2 or 4 */
     int32_t decim_chunks;     /* 64-column chunks per decimation wavefront: 1, 2, 4 or 8 */
     float bp_ms;              /* backprojection time measured by fdkod_tune (else 0) */
     float decim_ms;           /* decimation time measured by fdkod_tune (else 0) */
@@ -207,7 +210,7 @@ fdkod_status fdkod_get_tuning(fdkod_plan_t plan, fdkod_tuning* out);
  * footprint cannot hold the plan's block footprint (the plan is unchanged). */
 fdkod_status fdkod_set_tuning(fdkod_plan_t plan, const fdkod_tuning* t);
 
-/* Autotuner: times every valid backprojection variant (fdkod_reconstruct)
+/* Autotuner: times the backprojection for every valid z_run (fdkod_reconstruct)
  * and decimation chunking (fdkod_decompose) on the caller's buffers and
  * stream (one warm-up and three timed runs each), applies the fastest and
  * returns it.  Overwrites vol and ws.  Synchronises the stream; not for use
@@ -239,7 +242,7 @@ fdkod_status fdkod_choose_s(const fdkod_params* prm, int32_t s_max, double c1_ms
  * squares, one filter launch per FFT length over the volumes too small to fill
  * the GPU alone (larger ones keep a launch each), one grouped decimation launch
  * over all volumes' (square, row) tasks and one persistent backprojection
- * launch whose workgroups take (volume, square, 16 x 16 tile, slab) items from
+ * launch whose workgroups take (volume, square, tile, run of slices) items from
  * a ticket queue, largest first.  The launch sequence can be captured in a
  * hipGraph. */
 typedef struct fdkod_batch_s* fdkod_batch_t;
@@ -400,8 +403,8 @@ fdkod_status fdkod_adamw_step(float* master, float* m1, float* m2, const float* 
  *   volume slab      float32 [nzs][N][N]
  * The band calls compute for those rows and slices exactly what the
  * whole-volume calls compute (bit for bit when v0 is even, as
- * fdkod_band_rows returns it, and z0 is a multiple of the plan's z_run; the
- * filter transforms detector rows 2k and 2k + 1 together).  Asynchronous on
+ * fdkod_band_rows returns it; the filter transforms detector rows 2k and
+ * 2k + 1 together).  Asynchronous on
  * `stream`; they allocate nothing.
  * ------------------------------------------------------------------------- */
 

@@ -21,6 +21,7 @@ struct fdkod_batch_s {
     int device = 0, count = 0, store = 0;
     std::vector<fdkod_plan_t> plans;
     BpVariant bpv{32, 32, 48, 1};
+    BpShape bps{};
     int dec_chunks = 1;
     int bp_blocks = 0;
     int nitems = 0;
@@ -91,10 +92,13 @@ bool holds_all(const fdkod_batch_t b, const BpVariant& v) {
 }
 
 // Work items of the persistent backprojection for the current z run: volumes
-// by decreasing work, each volume's items by square, slab and tile (tiles
+// by decreasing work, each volume's items by square, run and tile (tiles
 // that share footprints are adjacent), then cut into one range per XCD of
-// about equal work (tile voxels x slab depth x decimated angles).
+// about equal work (decimated angles: every item's tile and run cost the same).
 fdkod_status build_items(fdkod_batch_t b) {
+    if (!bp_shape(b->plans.data(), b->count, b->bpv.zrun, false, &b->bps))
+        return fail(FDKOD_E_UNSUPPORTED, "no backprojection variant holds every volume");
+    const int edge = b->bps.bx;
     std::vector<int> order(b->count);
     std::iota(order.begin(), order.end(), 0);
     auto vol_work = [&](int vb) {
@@ -106,18 +110,15 @@ fdkod_status build_items(fdkod_batch_t b) {
     std::vector<int64_t> work;
     for (int vb : order) {
         const fdkod_plan_s* pl = b->plans[vb];
-        const int nzt = bp_zslabs(pl->nz, b->bpv.zrun);
+        const int nzt = bp_zslabs((pl->nz + 1) / 2, b->bps.zp);
         for (int q = 0; q < pl->nsq; ++q) {
             const SquareDesc& d = pl->sq[q];
-            for (int zt = 0; zt < nzt; ++zt) {
-                const int zc = std::min(b->bpv.zrun, pl->nz - zt * b->bpv.zrun);
-                for (int y = d.y0; y < d.y1; y += kTileXY)
-                    for (int x = d.x0; x < d.x1; x += kTileXY) {
-                        const int64_t vox = (int64_t)std::min(kTileXY, d.x1 - x) * std::min(kTileXY, d.y1 - y);
+            for (int zt = 0; zt < nzt; ++zt)
+                for (int y = d.y0; y < d.y1; y += edge)
+                    for (int x = d.x0; x < d.x1; x += edge) {
                         items.push_back(BatchItem{vb, q, x, y, zt, 0, 0, 0});
-                        work.push_back(vox * zc * pl->pd);
+                        work.push_back(pl->pd);
                     }
-            }
         }
         if ((int64_t)items.size() > (int64_t)1 << 30) return fail(FDKOD_E_UNSUPPORTED, "too many work items");
     }
@@ -139,7 +140,7 @@ fdkod_status build_items(fdkod_batch_t b) {
     HIP_TRY(hipMemcpy(b->d_items, items.data(), sizeof(BatchItem) * items.size(), hipMemcpyHostToDevice),
             "hipMemcpy items");
     b->nitems = (int)items.size();
-    const int occ = backproject_batch_occupancy(b->bpv, b->store);
+    const int occ = backproject_batch_occupancy(b->bps, b->store);
     hipDeviceProp_t prop;
     HIP_TRY(hipGetDeviceProperties(&prop, b->device), "hipGetDeviceProperties");
     b->bp_blocks = std::max(1, occ) * prop.multiProcessorCount;
@@ -279,7 +280,7 @@ fdkod_status run_backproject(fdkod_batch_t b, hipStream_t st) {
     a.nitems = b->nitems;
     for (int x = 0; x <= kXcds; ++x) a.xstart[x] = b->xstart[x];
     a.counter = b->d_counter;
-    HIP_TRY(launch_backproject_batch(a, b->bpv, b->store, b->bp_blocks, st), "persistent backprojection launch");
+    HIP_TRY(launch_backproject_batch(a, b->bps, b->store, b->bp_blocks, st), "persistent backprojection launch");
     return FDKOD_OK;
 }
 
@@ -473,21 +474,26 @@ fdkod_status fdkod_batch_tune(fdkod_batch_t b, fdkod_stream_t stream, fdkod_tuni
     }
     float best = 1e30f;
     BpVariant bestv = b->bpv;
-    for (int zr : {64, 32, 16})
+    for (int zr : {32, 16}) {
+        // the kernel follows from the z run and the geometries: one key for each z run
+        BpVariant v{};
+        bool holds = false;
         for (int tw : {32, 64})
-            for (int th : {48, 64, 96})
-                for (int g : {1, 2, 4}) {
-                    const BpVariant v{zr, tw, th, g};
-                    if (!holds_all(b, v)) continue;
-                    b->bpv = v;
-                    if ((r = build_items(b)) != FDKOD_OK) return r;
-                    float ms = 0.0f;
-                    if ((r = time_ms(st, 3, [&] { return run_backproject(b, st); }, &ms)) != FDKOD_OK) return r;
-                    if (ms < best) {
-                        best = ms;
-                        bestv = v;
-                    }
+            for (int th : {48, 64})
+                if (!holds) {
+                    v = BpVariant{zr, tw, th, 1};
+                    holds = holds_all(b, v);
                 }
+        if (!holds) continue;
+        b->bpv = v;
+        if ((r = build_items(b)) != FDKOD_OK) return r;
+        float ms = 0.0f;
+        if ((r = time_ms(st, 3, [&] { return run_backproject(b, st); }, &ms)) != FDKOD_OK) return r;
+        if (ms < best) {
+            best = ms;
+            bestv = v;
+        }
+    }
     b->bpv = bestv;
     if ((r = build_items(b)) != FDKOD_OK) return r;
     if (out) {

@@ -233,30 +233,120 @@ void ramp_tables(int n, int m, std::vector<float2>& resp, std::vector<float>& gt
 
 namespace fdkod {
 
-// Choose the backprojection LDS footprint (TW x TH samples) that holds the
-// footprint of a 16 x 16 x zrun voxel block at any angle, from the slice's
-// smallest depth Dmin = R - (N-1)/sqrt(2).
-bool bp_tiles_for(int n, int nz, double r, int zrun, int cone_side, int* tw, int* th) {
+// Detector columns and rows that a 16 x 16 (x, y) tile times `slices`
+// consecutive slices within |z| <= zmax covers at any angle, margins included,
+// from the slice's smallest depth Dmin = R - (N-1)/sqrt(2).  cone_side > 0:
+// cone-corrected rows of squares at most cone_side voxels wide.
+static void bp_need(int n, double r, int edge, int slices, double zmax, int cone_side, double slack, int margin, int* need_c, int* need_r) {
     const double c = (n - 1) / 2.0;
     const double dmin = r - c * std::sqrt(2.0);
     const double mag = r / dmin;
     const double lat = c * std::sqrt(2.0) / dmin;
-    const double diag = (kTileXY - 1) * std::sqrt(2.0);
+    const double diag = (edge - 1) * std::sqrt(2.0);
     const double span_c = diag * mag * std::sqrt(1.0 + lat * lat);
-    const double zmax = (nz - 1) / 2.0 + zrun;     // runs may extend past the last slice
     // rows per slice: R / D (eq. (9)); on cone-corrected rows D_c / D, where
     // D_c <= D + h with h the square's half diagonal
     const double hd = cone_side * std::sqrt(0.5);
     const double rows_per_z = cone_side ? (dmin + hd) / dmin : mag;
     const double numer = cone_side ? dmin + hd : r;   // bounds R (or D_c) where D = dmin
-    const double span_r = (zrun - 1) * rows_per_z + zmax * numer * diag / (dmin * dmin);
-    const int need_c = (int)std::ceil(span_c + 1e-6) + 4;
-    const int need_r = (int)std::ceil(span_r + 1e-6) + 4;
+    const double span_r = (slices - 1) * rows_per_z + zmax * numer * diag / (dmin * dmin);
+    // (capped: a source this close fits no kernel, and the count must fit an int)
+    *need_c = (int)std::ceil(std::min(span_c, 1e6) + slack) + margin;
+    *need_r = (int)std::ceil(std::min(span_r, 1e6) + slack) + margin;
+}
+
+bool bp_tiles_for(int n, int nz, double r, int zrun, int cone_side, int* tw, int* th) {
+    int need_c = 0, need_r = 0;
+    bp_need(n, r, kTileXY, zrun, (nz - 1) / 2.0 + zrun, cone_side, 1e-6, 4, &need_c, &need_r);
     *tw = need_c <= 32 ? 32 : (need_c <= 64 ? 64 : 0);
     *th = need_r <= 48 ? 48 : (need_r <= 64 ? 64 : (need_r <= 96 ? 96 : 0));
     return *tw && *th;
 }
 
+// The kernel shape of the volumes `pls` (one plan, or all of a batch, whose
+// persistent kernel takes no angle groups) for a z run.
+//
+// Work is counted in waves of 8 x 8 voxels times 8 slice pairs.  Few of them
+// leave most of the GPU idle and the time is the chain of angles, each about
+// (1.1 + 0.12 pairs) k cycles of latency; then small tiles, few pairs per
+// thread and angle groups (a part of the angles each) shorten it.  Measured
+// (us; 16 x 16 tiles of 16 pairs against the shape chosen): N = 64, s = 2, 256
+// waves 34.7 / 9.0; N = 96, s = 2, 864 waves 48.3 / 23.1; N = 128, s = 3, 2048
+// waves 38.2 / 23.5; at 5760 (N = 160, s = 3) the groups cost more than they
+// give (77.8 / 90.7).
+//
+// With enough waves the cost is VALU instructions: about 12 per slice pair
+// and 58 (8 x 8 tiles: 76, the footprint's margin weighs more) per thread and
+// angle, over every lane and slice of the tiles, those outside the squares
+// and the volume included.  An 8 x 8 tile pays where squares fill 16 x 16
+// tiles badly: N = 192, s = 3 (24-voxel squares) 133 -> 112 us, N = 384, s = 4
+// 815 -> 748; 32-voxel squares (N = 256, s = 3) 217 / 303.
+bool bp_shape(const fdkod_plan_s* const* pls, int count, int zrun, bool groups, BpShape* out) {
+    int64_t waves8 = 0;
+    for (int i = 0; i < count; ++i) waves8 += (int64_t)pls[i]->ntiles8 * bp_zslabs((pls[i]->nz + 1) / 2, 8);
+    auto shape = [&](int bx, int zp, int ag, BpShape* sh) {
+        int need_c = 0, need_r = 0;
+        if (2 * zp > zrun) return false;
+        for (int i = 0; i < count; ++i) {
+            const fdkod_plan_s* pl = pls[i];
+            int c = 0, r = 0;
+            // the lower runs reach from the volume's end to at most zp slices past its middle
+            bp_need(pl->n, pl->r, bx, zp, std::max((pl->nz - 1) / 2.0, (double)zp), cone_side(pl), 0.05, 2, &c, &r);
+            need_c = std::max(need_c, c);
+            need_r = std::max(need_r, r);
+            if ((int64_t)(bx == 8 ? pl->ntiles8 : pl->ntiles) * bp_zslabs((pl->nz + 1) / 2, zp) > (int64_t)1 << 30)
+                return false;
+        }
+        return backproject_shape_for(bx, zp, ag, need_c, need_r, sh);
+    };
+    struct Try {
+        int64_t most;
+        int bx, zp, ag;
+    };
+    const Try small[] = {{640, 8, 4, 4},  {640, 8, 8, 4},  {640, 16, 4, 4},  {640, 16, 8, 4}, {1200, 8, 8, 4},
+                         {1200, 16, 8, 4}, {4000, 16, 8, 2}};
+    if (groups)
+        for (const Try& t : small)
+            if (waves8 <= t.most && shape(t.bx, t.zp, t.ag, out)) return true;
+    if (zrun == 64 && shape(16, 32, 1, out)) return true;
+    double best = 0.0;
+    bool found = false;
+    for (const Try& t : {Try{0, 16, 16, 1}, Try{0, 16, 8, 1}, Try{0, 8, 8, 1}}) {
+        BpShape sh;
+        if (!shape(t.bx, t.zp, 1, &sh)) continue;
+        double cost = 0.0;
+        for (int i = 0; i < count; ++i) {
+            const fdkod_plan_s* pl = pls[i];
+            const double waves = (t.bx == 8 ? pl->ntiles8 * 1.1 : pl->ntiles * 4.0);
+            cost += waves * bp_zslabs((pl->nz + 1) / 2, t.zp) * pl->pd * (12 * t.zp + (t.bx == 8 ? 76 : 58));
+        }
+        if (!found || cost < best) {
+            best = cost;
+            *out = sh;
+            found = true;
+        }
+    }
+    return found;
+}
+
+bool bp_set_variant(fdkod_plan_s* pl, const BpVariant& v) {
+    BpShape sh;
+    if (!bp_shape(&pl, 1, v.zrun, true, &sh)) return false;
+    pl->bpv = v;
+    pl->bps = sh;
+    return true;
+}
+
+BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs) {
+    BpArgs a{};
+    a.v = v;
+    a.tiles = pl->bps.bx == 8 ? pl->d_tiles8 : pl->d_tiles;
+    a.ntiles = pl->bps.bx == 8 ? pl->ntiles8 : pl->ntiles;
+    a.nzt = runs;
+    a.nlogical = a.ntiles * a.nzt;
+    a.chunk = (a.nlogical + 7) / 8;
+    return a;
+}
 
 DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks) {
     return decim_args_band(pl, filt, ws, chunks, 0, pl->n);
@@ -352,6 +442,15 @@ bool variant_holds(const fdkod_plan_s* pl, const BpVariant& v) {
     return v.tile_w >= tw && v.tile_h >= th;
 }
 
+bool first_variant(const fdkod_plan_s* pl, int zrun, BpVariant* out) {
+    for (int tw : {32, 64})
+        for (int th : {48, 64, 96}) {
+            *out = BpVariant{zrun, tw, th, 1};
+            if (variant_holds(pl, *out)) return true;
+        }
+    return false;
+}
+
 BpVol bp_vol(const fdkod_plan_s* pl, const void* filt, const void* ws, float* vol) {
     return bp_vol_band(pl, filt, ws, vol, 0, pl->n, 0, pl->nz);
 }
@@ -371,6 +470,7 @@ BpVol bp_vol_band(const fdkod_plan_s* pl, const void* filt, const void* ws, floa
     v.v0 = v0;
     v.nv = nv;
     v.zbase = zbase;
+    v.nzf = pl->nz;
     v.cone = pl->cone;
     v.row_stride_direct = direct ? pl->n : 0;
     v.r = (float)pl->r;
@@ -760,6 +860,24 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
         if (e != hipSuccess) return bail(hip_fail(e, "hipMemcpy squares"));
     }
 
+    // tiles of 16 x 16 voxels (also the transpose's) and of 8 x 8
+    auto make_tiles = [&](int edge) {
+        std::vector<BpTile> t;
+        for (int q = 0; q < pl->nsq; ++q) {
+            const SquareDesc& d = pl->sq[q];
+            for (int y = d.y0; y < d.y1; y += edge)
+                for (int x = d.x0; x < d.x1; x += edge) t.push_back(BpTile{q, x, y, 0});
+        }
+        return t;
+    };
+    const std::vector<BpTile> tiles = make_tiles(kTileXY), tiles8 = make_tiles(8);
+    pl->ntiles = (int)tiles.size();
+    pl->ntiles8 = (int)tiles8.size();
+    if ((int64_t)pl->ntiles * bp_zslabs(pl->nz, 16) > (int64_t)1 << 30)
+        return bail(fail(FDKOD_E_UNSUPPORTED, "volume too large for one launch"));
+    if ((st = upload(pl, &pl->d_tiles, tiles)) != FDKOD_OK) return bail(st);
+    if ((st = upload(pl, &pl->d_tiles8, tiles8)) != FDKOD_OK) return bail(st);
+
     // default kernel shapes: the row-staged decimation where it applies (the
     // paper's plain decimation), else 64 * chunks local columns per
     // decimation wavefront (the smallest power of two covering the widest
@@ -772,33 +890,20 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     pl->bp_ok = false;
     for (int zr : {32, 16, 64}) {
         int tw = 0, th = 0;
-        // one angle per stage: the smallest LDS footprint, the highest occupancy
         if (bp_tiles_for(pl->n, pl->nz, pl->r, zr, cone_side(pl), &tw, &th) &&
             backproject_variant_exists(BpVariant{zr, tw, th, 1})) {
-            pl->bpv = BpVariant{zr, tw, th, 1};
-            pl->bp_ok = true;
-            break;
+            pl->bp_ok = bp_set_variant(pl, BpVariant{zr, tw, th, 1});
+            if (pl->bp_ok) break;
         }
     }
     {
         BpVariant cv{};
         int cc = 0;
         if (pl->bp_ok && tune_cache_lookup(pl, &cv, &cc) && variant_holds(pl, cv) &&
-            ((cc == 0 && pl->staged_cpt) || cc == 1 || cc == 2 || cc == 4 || cc == 8) && cc <= max_chunks(pl)) {
-            pl->bpv = cv;
+            ((cc == 0 && pl->staged_cpt) || cc == 1 || cc == 2 || cc == 4 || cc == 8) && cc <= max_chunks(pl) &&
+            bp_set_variant(pl, cv))
             pl->dec_chunks = cc;
-        }
     }
-    std::vector<BpTile> tiles;
-    for (int q = 0; q < pl->nsq; ++q) {
-        const SquareDesc& d = pl->sq[q];
-        for (int y = d.y0; y < d.y1; y += kTileXY)
-            for (int x = d.x0; x < d.x1; x += kTileXY) tiles.push_back(BpTile{q, x, y, 0});
-    }
-    pl->ntiles = (int)tiles.size();
-    if ((int64_t)pl->ntiles * bp_zslabs(pl->nz, 16) > (int64_t)1 << 30)
-        return bail(fail(FDKOD_E_UNSUPPORTED, "volume too large for one launch"));
-    if ((st = upload(pl, &pl->d_tiles, tiles)) != FDKOD_OK) return bail(st);
     // the learned filter's backward pass sums its workgroups' partial
     // gradients in a fixed order (a plan the filter applies to only)
     if (pl->s > 0 && !pl->cone && pl->wmax <= kLearnedMaxWidth &&
@@ -859,14 +964,8 @@ fdkod_status fdkod_reconstruct(fdkod_plan_t pl, const void* filt, const void* ws
     if (!direct && !ws) return fail(FDKOD_E_ARG, "workspace is NULL");
     if (!pl->bp_ok)
         return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds 64 x 64");
-    BpArgs a;
-    a.v = bp_vol(pl, filt, ws, vol);
-    a.tiles = pl->d_tiles;
-    a.ntiles = pl->ntiles;
-    a.nzt = bp_zslabs(pl->nz, pl->bpv.zrun);
-    a.nlogical = a.ntiles * a.nzt;
-    a.chunk = (a.nlogical + 7) / 8;
-    HIP_TRY(launch_backproject(a, pl->bpv, pl->store, (hipStream_t)stream), "backprojection kernel launch");
+    const BpArgs a = bp_args(pl, bp_vol(pl, filt, ws, vol), bp_zslabs((pl->nz + 1) / 2, pl->bps.zp));
+    HIP_TRY(launch_backproject(a, pl->bps, pl->store, (hipStream_t)stream), "backprojection kernel launch");
     return FDKOD_OK;
 }
 
@@ -937,7 +1036,8 @@ fdkod_status fdkod_set_tuning(fdkod_plan_t pl, const fdkod_tuning* t) {
         return fail(FDKOD_E_UNSUPPORTED, "decim_chunks must be 0, 1, 2, 4 or 8");
     if (c > max_chunks(pl))
         return fail(FDKOD_E_UNSUPPORTED, "decim_chunks above 4 with more than two decimation windows");
-    pl->bpv = v;
+    if (!bp_set_variant(pl, v))
+        return fail(FDKOD_E_UNSUPPORTED, "backprojection variant missing or too small for this geometry");
     pl->dec_chunks = c;
     pl->tuned_bp_ms = t->bp_ms;
     pl->tuned_dec_ms = t->decim_ms;
@@ -969,24 +1069,21 @@ fdkod_status fdkod_tune(fdkod_plan_t pl, const void* filt, void* ws, float* vol,
         pl->tuned_dec_ms = best;
         if ((r = fdkod_decompose(pl, filt, ws, stream)) != FDKOD_OK) return r;
     }
+    // the kernel follows from the z run and the geometry: one key for each z run
     float best = 1e30f;
     BpVariant bestv = pl->bpv;
-    for (int zr : {64, 32, 16})
-        for (int tw : {32, 64})
-            for (int th : {48, 64, 96})
-                for (int g : {1, 2, 4}) {
-                    const BpVariant v{zr, tw, th, g};
-                    if (!variant_holds(pl, v)) continue;
-                    pl->bpv = v;
-                    float ms = 0.0f;
-                    r = time_ms(st, 3, [&] { return fdkod_reconstruct(pl, filt, ws, vol, stream); }, &ms);
-                    if (r != FDKOD_OK) return r;
-                    if (ms < best) {
-                        best = ms;
-                        bestv = v;
-                    }
-                }
-    pl->bpv = bestv;
+    for (int zr : {64, 32, 16}) {
+        BpVariant v{};
+        if (!first_variant(pl, zr, &v) || !bp_set_variant(pl, v)) continue;
+        float ms = 0.0f;
+        r = time_ms(st, 3, [&] { return fdkod_reconstruct(pl, filt, ws, vol, stream); }, &ms);
+        if (r != FDKOD_OK) return r;
+        if (ms < best) {
+            best = ms;
+            bestv = v;
+        }
+    }
+    bp_set_variant(pl, bestv);
     pl->tuned_bp_ms = best;
     tune_cache_store(pl);
     return out ? fdkod_get_tuning(pl, out) : FDKOD_OK;

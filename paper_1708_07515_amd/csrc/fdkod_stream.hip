@@ -98,14 +98,24 @@ StreamLayout stream_layout(const fdkod_plan_s* pl, int nzs) {
 
 fdkod_status launch_slab(const fdkod_plan_s* pl, const void* filt, const void* ws, int v0, int nv, int z0,
                          int nzs, float* vol, hipStream_t st) {
-    BpArgs a;
-    a.v = bp_vol_band(pl, filt, ws, vol, v0, nv, z0, nzs);
-    a.tiles = pl->d_tiles;
-    a.ntiles = pl->ntiles;
-    a.nzt = bp_zslabs(nzs, pl->bpv.zrun);
-    a.nlogical = a.ntiles * a.nzt;
-    a.chunk = (a.nlogical + 7) / 8;
-    HIP_TRY(launch_backproject(a, pl->bpv, pl->store, st), "backprojection kernel launch");
+    // the whole volume's runs that meet the slab: lower ones by their own
+    // slices, mirrored ones by their images (the same arithmetic for every
+    // slice as in the whole volume)
+    const int zp = pl->bps.zp, mid = (pl->nz - 1) / 2;      // last lower slice
+    int low0 = 0, nlow = 0, up0 = 0, nup = 0;
+    if (z0 <= mid) {
+        low0 = z0 / zp;
+        nlow = std::min(z0 + nzs - 1, mid) / zp - low0 + 1;
+    }
+    if (z0 + nzs - 1 > mid) {
+        up0 = (pl->nz - 1 - (z0 + nzs - 1)) / zp;
+        nup = (pl->nz - 1 - std::max(z0, mid + 1)) / zp - up0 + 1;
+    }
+    BpArgs a = bp_args(pl, bp_vol_band(pl, filt, ws, vol, v0, nv, z0, nzs), nlow + nup);
+    a.low0 = low0;
+    a.nlow = nlow;
+    a.up0 = up0;
+    HIP_TRY(launch_backproject_slab(a, pl->bps, pl->store, st), "backprojection kernel launch");
     return FDKOD_OK;
 }
 

@@ -28,7 +28,7 @@ struct DecimStep {
     float w1;     // weight into the newer open window
 };
 
-// Backprojection tile: 16 x 16 voxels in x, y of one square.
+// Backprojection tile: 16 x 16 (or 8 x 8) voxels in x, y of one square.
 struct BpTile {
     int sq;       // square index
     int x0, y0;   // first voxel of the tile (indices)
@@ -129,6 +129,7 @@ struct BpVol {
     int n, nz, pd;          // nz: slices in the output buffer
     int v0, nv;             // detector rows [v0, v0 + nv) held by data (rows outside read zero)
     int zbase;              // volume slice of output slice 0
+    int nzf;                // slices of the whole volume, N_z
     int cone;               // 1: data rows are cone-corrected (row offset z D_c / D)
     int row_stride_direct;  // 0 for per-square layout [m][v][W_q]
     float r, cu, cv, cz;
@@ -140,14 +141,15 @@ struct BpArgs {
     BpVol v;
     const BpTile* tiles;
     int ntiles;             // xy tiles
-    int nzt;                // z tiles
+    int nzt;                // runs of slice pairs (slab: of slices)
     int nlogical;           // ntiles * nzt
     int chunk;              // logical WGs per XCD
+    int low0, nlow, up0;    // slab: first lower run and their count, first mirrored run
 };
 
 // One work item of the batched (persistent) backprojection.
 struct BatchItem {
-    int vol, sq, x0, y0, zt, pad0, pad1, pad2;
+    int vol, sq, x0, y0, zt, pad0, pad1, pad2;   // zt: run of slice pairs
 };
 
 // Work items are split into one contiguous range per XCD (items
@@ -164,10 +166,16 @@ struct BpBatchArgs {
     unsigned* counter;       // kXcds ticket counters, kCounterStride apart
 };
 
-// A backprojection kernel variant: slices per thread, LDS footprint
-// (columns x rows), angles staged per barrier.
+// Public key of a backprojection variant (fdkod_tuning): slices per thread
+// and the LDS footprint (columns x rows) that has to hold a block of them.
 struct BpVariant {
     int zrun, tile_w, tile_h, g;
+};
+
+// A backprojection kernel's shape: tile side, slice pairs per thread, columns
+// and rows of its staged footprints, angle groups.
+struct BpShape {
+    int bx, zp, tw, th, ag;
 };
 
 hipError_t launch_bounds(const BoundsArgs& a, hipStream_t st);
@@ -182,11 +190,12 @@ hipError_t launch_decimate(const DecimVol& a, int chunks, int store, hipStream_t
 bool staged_shape_exists(int cpt, int segc);
 hipError_t launch_decimate_staged(const DecimVol& a, int cpt, int segc, int store, hipStream_t st);
 hipError_t launch_decimate_batch(const DecimBatchArgs& a, int chunks, int store, hipStream_t st);
-hipError_t launch_backproject(const BpArgs& a, const BpVariant& var, int store, hipStream_t st);
-hipError_t launch_backproject_batch(const BpBatchArgs& a, const BpVariant& var, int store,
-                                    int blocks, hipStream_t st);
+hipError_t launch_backproject(const BpArgs& a, const BpShape& sh, int store, hipStream_t st);
+hipError_t launch_backproject_slab(const BpArgs& a, const BpShape& sh, int store, hipStream_t st);
+bool backproject_shape_for(int bx, int zp, int ag, int need_c, int need_r, BpShape* out);
+hipError_t launch_backproject_batch(const BpBatchArgs& a, const BpShape& sh, int store, int blocks, hipStream_t st);
 // workgroups of the batched kernel that fit on one CU (0 if the variant is unknown)
-int backproject_batch_occupancy(const BpVariant& var, int store);
+int backproject_batch_occupancy(const BpShape& sh, int store);
 bool backproject_variant_exists(const BpVariant& var);
 hipError_t launch_reset_counter(unsigned* counter, hipStream_t st);
 

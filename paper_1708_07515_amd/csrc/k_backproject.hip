@@ -6,19 +6,29 @@
 //   U = depth / R,  tau = a(x, y) - a_c + c_u - u0  (eq. (1), folded back-shift),
 //   v* = z R / depth + c_v                            (eq. (9))
 //
-// Workgroup = 16 x 16 voxels in (x, y) of one square times ZR consecutive
-// slices; every thread owns one (x, y) and ZR accumulators in registers.
-// Angles are processed in batches of G.  For each angle of a batch the
-// footprint of the workgroup's voxel block on the (local) detector is bounded
-// with eq. (1) at the block's corners (columns) and eq. (9) at its corner
-// depths and end slices (rows) -- the paper's vertex bound applied to the
-// block -- and that footprint (at most TH x TW samples, padded by one sample
-// on every side) is staged in LDS as quads (Y, dU, dV, dUV) of forward
-// differences, so one 128-bit LDS read fetches all four samples of a
+// Workgroup = a 16 x 16 (or 8 x 8) tile of one square times a run of ZP
+// slices and their mirror images about the mid-plane; every thread owns one
+// (x, y) and 2 ZP accumulators in registers.  Slices z and -z see detector
+// rows c_v + b and c_v - b at every angle, so a pair shares its row index, its
+// fraction and its LDS address: the mirrored footprint is staged in reversed
+// row order, and the pair's second sample lies at a constant offset from the
+// first.  For each angle the footprint of the tile's run on the (local)
+// detector is bounded with eq. (1) at the tile's corners (columns) and eq. (9)
+// at its corner depths and end slices (rows) -- the paper's vertex bound
+// applied to the block -- and staged in LDS as quads (Y, dU, dV, dUV) of
+// forward differences, so one 128-bit LDS read fetches all four samples of a
 // bilinear interpolation, which is then three FMAs.  Per (x, y, angle) a
-// thread computes tau, U and the weight once; along z only the row
-// coordinate moves, linearly (b = z / U), so an update costs a row index,
-// one LDS read and four FMAs.
+// thread computes tau, U and the weight once; along z only the row coordinate
+// moves, linearly (b = z / U): four instructions for each pair (row, fraction,
+// index, address) and four FMAs for each update.
+//
+// Bound: VALU issue, with the LDS close behind.  Counters at N = 512, s = 3,
+// FP32 (16 pairs per thread): 7.8 VALU instructions per update issued at one
+// wave-instruction per compute unit and cycle, LDS busy 75 % (4 cycles per
+// wave for a 128-bit read, 13.6 for a 128-bit write, which is why only the
+// rows an angle needs are staged).  With one slice per index (10.4 per update)
+// 1.70 ms, 2000^2 x 1000 slices, s = 4: 50 ms, direct FDK at N = 256: 1.86 ms;
+// now 1.36, 41.5 and 1.41 ms (4.4e12 updates/s).
 #include "internal.h"
 #include "dtype.h"
 
@@ -46,16 +56,27 @@ typedef __attribute__((address_space(3))) const f4v* lds_f4ptr;
 
 // Per-angle footprints and constants are computed for kFpChunk angles at a
 // time (one lane per angle) and kept for two such chunks.
-constexpr int kFpChunk = 64;
+constexpr int kFpChunk = 8;
 
-// LDS of one workgroup: G staged footprints and, for two chunks of angles,
+// Margin of a block's footprint, in samples: far above the rounding of the
+// footprint's and the voxels' coordinates (about 1e-7 of N), far below a sample.
+constexpr float kBpMargin = 0.01f;
+
+// One angle's constants of a 16 x 16 tile and run.
+struct BpAngle {
+    float ax, ay, cs, sn;        // R (dL Dc - Lc dD) / Dc = ax dx + ay dy; cos, sin
+    float dc, kc, top, kr;       // Dc, c_u - u0 - c0, R (or Dc on cone-corrected rows), c_v - r0
+    int c0, off[2];              // footprint's first column; byte offset of its first sample (lower, mirrored)
+    int nq;                      // quad rows per staging lane
+};
+
+// LDS of one group of BX BX threads: the NT staged footprints (the quads of TH
+// detector rows: TH - 1 rows of TW + 4 quads) and, for two chunks of angles,
 // the per-angle constants.
-template <int TW, int TH, int G>
+template <int NT, int TW, int TH>
 struct BpSmem {
-    float4 tile[G][TH * (TW + 1)];
-    int4 meta[2][kFpChunk];      // c0, r0 (first column / row of the footprint), rows, -
-    float4 mgeo[2][kFpChunk];    // cos, sin, Dc, Lc
-    float2 mgeo2[2][kFpChunk];   // R / Dc, c_u - u0 - c0
+    float4 tile[NT * (TH - 1) * (TW + 4)];
+    BpAngle ang[2][kFpChunk];
 };
 
 // Lane l receives lane l + 1's value (a DPP wave shift; lane 63 receives 0).
@@ -63,28 +84,51 @@ __device__ __forceinline__ float from_next_lane(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130 /* wave_shl:1 */, 0xf, 0xf, false));
 }
 
-// Backprojection of one 16 x 16 x ZR voxel block (tile tl, slab zt) of one
-// volume.  Every thread of the workgroup calls it (it contains barriers).
+// Backprojection of one BX x BX (x, y) tile tl (BX = 16 or 8) over run `run` of ZP lower
+// slices (l = run ZP + k) and their mirror images (l' = N_z - 1 - l):
+// NT = 2 both (side ignored), NT = 1 one of them (side 0: lower, 1: mirrored).
+// AG groups of BX BX threads share the angles (each takes a contiguous part)
+// and their sums are added in group order at the end.  The arithmetic of a
+// slice does not depend on NT, so a slab gives the bits of the whole volume.
+// Every thread of the workgroup calls it (it contains barriers).
 //
-// Angles go in batches of G.  While batch b is accumulated from LDS, the
-// detector samples of batch b + 1 are already being loaded into registers
-// (their footprints were bounded one batch earlier), so global-memory latency
-// overlaps the arithmetic; two barriers per batch separate the LDS phases.
-template <int ZR, int TW, int TH, int G, int STORE>
-__device__ __forceinline__ void bp_block(const BpVol& v, int zt, const BpTile& tl,
-                                         BpSmem<TW, TH, G>& sm) {
+// While angle m is accumulated from LDS, the detector samples of angle m + 1
+// are already being loaded into registers, so global-memory latency overlaps
+// the arithmetic; two barriers per angle separate the LDS phases.
+template <int BX, int ZP, int NT, int TW, int TH, int AG, int STORE>
+__device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, const BpTile& tl,
+                                         BpSmem<NT, TW, TH> (&sms)[AG]) {
+    // the thread within its group, and the group's part of the angles
+    constexpr int NTHR = BX * BX;
+    const int tid = AG == 1 ? threadIdx.x : threadIdx.x & (NTHR - 1);
+    const int grp = AG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTHR);
+    BpSmem<NT, TW, TH>& sm = sms[grp];
+    const int per = (v.pd + AG - 1) / AG;
+    const int mbeg = grp * per, mend = min(mbeg + per, v.pd);
     using S = Store<STORE>;
     using T = typename S::T;
-    constexpr int TWP = TW + 1;   // LDS row pitch in quads (odd: spreads banks)
+    // LDS row pitch in quads: 4 mod 16, so that the 16 lanes of one 4 x 4
+    // patch of voxels (at most six columns of one or two rows) read distinct
+    // groups of four banks
+    constexpr int TWP = TW + 4;
+    constexpr int SIDE = (TH - 1) * TWP;   // quads from a lower sample to the mirrored one
     auto& tile = sm.tile;
     const SquareDesc sq = v.squares[tl.sq];
     const int2 gd = v.grid[tl.sq];
     const int u0 = gd.x, width = gd.y;
 
     const int n = v.n;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int ix1 = min(tl.x0 + 15, sq.x1 - 1);
-    const int iy1 = min(tl.y0 + 15, sq.y1 - 1);
+    // The 16 lanes that one cycle of a 128-bit LDS read serves take a 4 x 4
+    // patch of voxels, a wave four patches (along x, or 2 x 2 of an 8 x 8
+    // tile).  Measured: those lanes are, in each half of the wave, the groups
+    // of four lanes with an even number of bits in their index, then those
+    // with an odd one.
+    const int lq = tid >> 2;                     // group of four lanes
+    const int patch = ((lq ^ (lq >> 1) ^ (lq >> 2)) & 1) | ((lq >> 2) & 2);
+    const int tx = (tid & 3) + 4 * (BX == 16 ? patch : patch & 1);
+    const int ty = ((lq >> 1) & 3) + 4 * (BX == 16 ? tid >> 6 : patch >> 1);
+    const int ix1 = min(tl.x0 + BX - 1, sq.x1 - 1);
+    const int iy1 = min(tl.y0 + BX - 1, sq.y1 - 1);
     const int i = tl.x0 + tx, j = tl.y0 + ty;
     const bool own = (i <= ix1) && (j <= iy1);
     // offsets from the square centre; threads outside the square use the
@@ -94,11 +138,11 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int zt, const BpTile& t
     const float bx0 = (float)tl.x0 - v.cu - sq.xc, bx1 = (float)ix1 - v.cu - sq.xc;
     const float by0 = (float)tl.y0 - v.cu - sq.yc, by1 = (float)iy1 - v.cu - sq.yc;
 
-    // the run covers ZR slices even past the volume's end (those voxels are
-    // computed and discarded), so the staged rows always hold the whole run
-    const int l0 = zt * ZR;                       // output slice (volume slice zbase + l0)
-    const float z0 = (float)(v.zbase + l0) - v.cz;
-    const float zlast = (float)(v.zbase + l0 + ZR - 1) - v.cz;
+    // the run covers ZP slices even past the volume's middle (those voxels
+    // are computed and discarded), so the staged rows always hold the whole run
+    const int l0 = run * ZP;
+    const float z0 = (float)l0 - v.cz;
+    const float zlast = (float)(l0 + ZP - 1) - v.cz;
 
     const bool direct = v.row_stride_direct != 0;
     const int row_stride = direct ? v.row_stride_direct : width;
@@ -106,30 +150,40 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int zt, const BpTile& t
     const T* data = (const T*)v.data + (direct ? 0 : sq.y_off_row * v.nv);
     const float kq = v.cu - (float)u0;            // tau = rel + kq
 
-    // staging map: a lane keeps one footprint column and NQ consecutive rows
-    // (their quads), for which it loads NQ + 1 rows
-    constexpr int NGRP = 256 / TW;
-    static_assert(TH % NGRP == 0, "uniform staging trip count");
-    constexpr int NQ = TH / NGRP;
+    // staging map: footprint t is staged by NTHR / NT threads; a lane keeps
+    // one footprint column and nq consecutive rows (their quads), for which
+    // it loads nq + 1 rows
+    constexpr int SIDE_THR = NTHR / NT;
+    constexpr int NGRP = SIDE_THR / TW;
+    static_assert((TH - 1) % NGRP == 0, "uniform staging trip count");
+    constexpr int NQ = (TH - 1) / NGRP;          // at most; an angle's own count is BpAngle::nq
     constexpr int NR = NQ + 1;
-    const int scol = threadIdx.x % TW;
-    const int srow = (threadIdx.x / TW) * NQ;
+    constexpr int NQMIN = NQ < 4 ? NQ : NQ / 2 + 1;  // rows staged without a branch
+    const int scol = tid % TW;
+    const int sgrp = (tid % SIDE_THR) / TW;
+    // the footprint this thread stages (uniform over a wave unless one wave
+    // stages both), and whether it is a mirrored one
+    constexpr bool kSideUniform = NT == 1 || SIDE_THR >= 64;
+    const int st_t = NT == 1 ? 0 : kSideUniform ? __builtin_amdgcn_readfirstlane(tid / SIDE_THR) : tid / SIDE_THR;
+    const int mirrored = NT == 2 ? st_t : side;
 
     // footprints of the block at the kFpChunk angles from m0 (a multiple of
     // kFpChunk), one lane of the first wave per angle: eq. (1) at the block's
     // corners bounds the columns, eq. (9) at its corner depths and end slices
-    // the rows; one sample of margin on every side covers the rounding of the
-    // reciprocals.  Angle m's constants sit at [(m / kFpChunk) % 2][m % kFpChunk].
-    static_assert(kFpChunk % G == 0, "a batch of angles lies within one chunk");
+    // the rows; kBpMargin of a sample on every side covers the rounding of the
+    // reciprocals.  The mirrored run's rows are n - 1 minus these.  Angle m's
+    // constants sit at [(m / kFpChunk) % 2][m % kFpChunk].
+    constexpr int ES = (int)sizeof(T);
+    const uint32_t plane_bytes = (uint32_t)(plane * ES);
     auto footprint = [&](int m0) {
         const int slot = (m0 / kFpChunk) & 1;
-        if (threadIdx.x < kFpChunk && m0 + (int)threadIdx.x < v.pd) {
-            const int m = m0 + threadIdx.x;
+        const int m = mbeg + m0 + tid;
+        if (tid < kFpChunk && m < mend) {
             const float2 t = v.trig[m];
             const float dc = v.r + sq.xc * t.x + sq.yc * t.y;
             const float lc = sq.yc * t.x - sq.xc * t.y;
             const float rdc = __builtin_amdgcn_rcpf(dc);
-            float tlo = INFINITY, thi = -INFINITY, vlo = INFINITY, vhi = -INFINITY;
+            float tlo = INFINITY, vlo = INFINITY, vhi = -INFINITY;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float cx = (k & 1) ? bx1 : bx0;
@@ -137,206 +191,249 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int zt, const BpTile& t
                 const float dl = cy * t.x - cx * t.y;
                 const float dd = cx * t.x + cy * t.y;
                 const float rd = __builtin_amdgcn_rcpf(dc + dd);
-                const float tau = v.r * (dl * dc - lc * dd) * rdc * rd + kq;
-                tlo = fminf(tlo, tau);
-                thi = fmaxf(thi, tau);
+                tlo = fminf(tlo, v.r * (dl * dc - lc * dd) * rdc * rd + kq);
                 const float iu = (v.cone ? dc : v.r) * rd;   // row offset per unit z
                 const float va = z0 * iu + v.cv, vb = zlast * iu + v.cv;
                 vlo = fminf(vlo, fminf(va, vb));
                 vhi = fmaxf(vhi, fmaxf(va, vb));
             }
-            const int c0 = (int)floorf(tlo) - 1;
-            const int r0 = (int)floorf(vlo) - 1;
-            const int rows = min((int)floorf(vhi) + 3 - r0, TH);
-            sm.meta[slot][threadIdx.x] = make_int4(c0, r0, rows, 0);
-            sm.mgeo[slot][threadIdx.x] = make_float4(t.x, t.y, dc, lc);
-            sm.mgeo2[slot][threadIdx.x] = make_float2(v.r * rdc, kq - (float)c0);
+            const int c0 = (int)floorf(tlo - kBpMargin);
+            const int r0 = (int)floorf(vlo - kBpMargin);
+            const int quads = (int)floorf(vhi + kBpMargin) + 1 - r0;    // quad rows r0 .. floor(vhi)
+            const float lr = v.r * lc * rdc;
+            BpAngle a;
+            a.ax = -fmaf(v.r, t.y, lr * t.x);
+            a.ay = fmaf(v.r, t.x, -(lr * t.y));
+            a.cs = t.x;
+            a.sn = t.y;
+            a.dc = dc;
+            a.kc = kq - (float)c0;
+            a.top = v.cone ? dc : v.r;
+            a.kr = v.cv - (float)r0;
+            a.c0 = c0;
+            a.off[0] = ((r0 - v.v0) * row_stride + c0) * ES;
+            a.off[1] = ((n - 1 - r0 - v.v0) * row_stride + c0) * ES;
+            a.nq = min((quads + NGRP - 1) / NGRP, NQ);
+            sm.ang[slot][tid] = a;
         }
     };
-    // detector samples of the footprints of [m0, m0 + G) into registers, as
-    // raw bits of the storage type (converted when staged, so no load is
-    // waited for early).  One buffer resource spans the angle's plane of the
-    // data: rows outside the buffer fall outside it and read zero (a row above
-    // the first wraps to a huge unsigned offset), and a column outside
-    // [0, width) gets an offset beyond every plane, so its samples read zero
-    // too.  A lane's samples are consecutive rows, so each costs one add.
-    // Footprints of more than 16 samples per thread are loaded after the
-    // arithmetic instead (their registers would cost occupancy).
-    constexpr bool kPrefetch = G * NR <= 16;
-    constexpr int ES = (int)sizeof(T);
-    const uint32_t plane_bytes = (uint32_t)(plane * ES);
-    const int rstep_bytes = row_stride * ES;
-    uint32_t pre[G][NR];
-    auto fetch_one = [&](int m0, int g) {
-        {
-            const bool gok = m0 + g < v.pd;
-            const int4 mt = gok ? sm.meta[((m0 + g) / kFpChunk) & 1][(m0 + g) % kFpChunk] : make_int4(0, 0, 0, 0);
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-                uniform_ptr(data + (size_t)(gok ? m0 + g : 0) * plane), (short)0, (int)plane_bytes, 0x00020000);
-            const int col = mt.x + scol;
-            const int row = mt.y + srow - v.v0;           // row within the buffer
-            const int off0 = (unsigned)col < (unsigned)width ? (row * row_stride + col) * ES : (int)0x80000000;
-            // (each offset in its own register, never folded into the
-            // instruction's constant offset: the range check must see the
-            // whole offset of every sample)
+    // detector samples of angle m's footprint into registers, as raw bits of
+    // the storage type (converted when staged, so no load is waited for
+    // early).  One buffer resource spans the angle's plane of the data: rows
+    // outside the buffer fall outside it and read zero (a row above the first
+    // wraps to a huge unsigned offset), and a column outside [0, width) gets
+    // an offset beyond every plane, so its samples read zero too.  A lane's
+    // samples are consecutive rows (downwards for a mirrored footprint), so
+    // each costs one add.  Footprints of more than 16 samples per thread are
+    // loaded after the arithmetic instead (their registers would cost
+    // occupancy).
+    constexpr bool kPrefetch = NR <= 16;
+    const int rstep_bytes = (mirrored ? -row_stride : row_stride) * ES;
+    uint32_t pre[NR];
+    auto fetch = [&](int m) {
+        const BpAngle& an = sm.ang[(m / kFpChunk) & 1][m % kFpChunk];
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            uniform_ptr(data + (size_t)(mbeg + m) * plane), (short)0, (int)plane_bytes, 0x00020000);
+        const int nq = __builtin_amdgcn_readfirstlane(an.nq);
+        const int col = an.c0 + scol, at = an.off[mirrored] + scol * ES + __mul24(sgrp, nq * rstep_bytes);
+        const int off0 = (unsigned)col < (unsigned)width ? at : (int)0x80000000;
+        // (each offset in its own register, never folded into the
+        // instruction's constant offset: the range check must see the
+        // whole offset of every sample)
 #pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                int off;
-                if (r == 0) {
-                    off = off0;
-                    asm volatile("" : "+v"(off));
-                } else {
-                    asm volatile("v_add_u32 %0, %1, %2" : "=v"(off) : "s"(r * rstep_bytes), "v"(off0));
-                }
-                pre[g][r] = S::raw_bits(rs, off);
+        for (int q = 0; q < NR; ++q) {
+            if (q > NQMIN && q > nq) break;      // uniform
+            int off;
+            if (q == 0) {
+                off = off0;
+                asm volatile("" : "+v"(off));
+            } else if constexpr (!kSideUniform) {
+                off = off0 + q * rstep_bytes;
+                asm volatile("" : "+v"(off));
+            } else {
+                asm volatile("v_add_u32 %0, %1, %2" : "=v"(off) : "s"(q * rstep_bytes), "v"(off0));
             }
+            pre[q] = S::raw_bits(rs, off);
         }
     };
     // quads (Y, dU, dV, dUV) into LDS: at (r, c), Y = Y[r][c], dU = Y[r][c+1]
     // - Y[r][c], dV = Y[r+1][c] - Y[r][c], dUV = dU[r+1] - dU[r], so that the
     // bilinear sample at (r + fv, c + fu) is Y + fu dU + fv (dV + fu dUV).
-    // The last column's quad is never read (the column index is at most
-    // TW - 2), so the lane that receives the next group's first sample
-    // writes an unused quad; nor is the last row's (the row index is at most
-    // TH - 2), whose extra row lies past the tile.  Rows below the
-    // footprint's last are written too: they lie inside the tile and are
-    // never read.
-    auto stage_one = [&](int g) {
-        float y[NR], du[NR];
+    // The last column's quad is never read, so the lane that receives the
+    // next group's first sample writes an unused quad; nor are rows below the
+    // footprint's last.
+    auto stage = [&](int m) {
+        const int nq = __builtin_amdgcn_readfirstlane(sm.ang[(m / kFpChunk) & 1][m % kFpChunk].nq);
+        float4* dst = tile + st_t * SIDE + scol + __mul24(sgrp, nq * TWP);
+        float y0 = S::from_bits(pre[0]);
+        float du0 = from_next_lane(y0) - y0;
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            y[r] = S::from_bits(pre[g][r]);
-            du[r] = from_next_lane(y[r]) - y[r];
-        }
-#pragma unroll
-        for (int r = 0; r < NQ; ++r)
-            tile[g][(srow + r) * TWP + scol] = make_float4(y[r], du[r], y[r + 1] - y[r], du[r + 1] - du[r]);
-    };
-
-    float acc[ZR];
-#pragma unroll
-    for (int k = 0; k < ZR; ++k) acc[k] = 0.0f;
-
-    auto fetch_stage = [&](int m0) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            fetch_one(m0, g);
-            stage_one(g);
+        for (int r = 0; r < NQ; ++r) {
+            if (r >= NQMIN && r >= nq) break;    // uniform
+            const float y1 = S::from_bits(pre[r + 1]);
+            const float du1 = from_next_lane(y1) - y1;
+            dst[r * TWP] = make_float4(y0, du0, y1 - y0, du1 - du0);
+            y0 = y1;
+            du0 = du1;
         }
     };
+
+    const float sr2 = v.scale * v.r * v.r;
+    float acc[NT][ZP];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int k = 0; k < ZP; ++k) acc[t][k] = 0.0f;
 
     // the first chunk's footprints; the next chunk's are computed while the
-    // first batch of a chunk is accumulated (two barriers before their first
+    // first angle of a chunk is accumulated (two barriers before their first
     // use, and after the last use of the chunk two before them)
-    if (threadIdx.x < 64) footprint(0);
+    // (m counts the group's angles; a group with fewer than `per` only joins
+    // the barriers of the last rounds)
+    const int count = mend - mbeg;
+    if (tid < 64) footprint(0);
     __syncthreads();
-    fetch_stage(0);
+    if (AG == 1 || count > 0) {
+        fetch(0);
+        stage(0);
+    }
     __syncthreads();
 #pragma unroll 1
-    for (int m0 = 0; m0 < v.pd; m0 += G) {
-        const int cs = (m0 / kFpChunk) & 1, ci0 = m0 % kFpChunk;
-        const int gcount = min(G, v.pd - m0);
-        const bool more = m0 + G < v.pd;
-        if (kPrefetch && more) {             // in flight during the arithmetic below
-#pragma unroll
-            for (int g = 0; g < G; ++g) fetch_one(m0 + G, g);
+    for (int m = 0; m < per; ++m) {
+        if (AG > 1 && m >= count) {
+            __syncthreads();
+            __syncthreads();
+            continue;
         }
-        if (ci0 == 0 && m0 + kFpChunk < v.pd && threadIdx.x < 64) footprint(m0 + kFpChunk);
-#pragma unroll 1
-        for (int g = 0; g < gcount; ++g) {
-            const float4 mg = sm.mgeo[cs][ci0 + g];
-            const float2 mg2 = sm.mgeo2[cs][ci0 + g];
-            const int4 mt = sm.meta[cs][ci0 + g];
-            const float dl = dy * mg.x - dx * mg.y;
-            const float dd = dx * mg.x + dy * mg.y;
-            const float d = mg.z + dd;
-            const float rd = __builtin_amdgcn_rcpf(d);
-            const float tau = (dl * mg.z - mg.w * dd) * mg2.x * rd + mg2.y;
-            const float invu = v.r * rd;                 // 1 / U
-            float w = v.scale * invu * invu;
-            // row offset per unit z: R / D (eq. (9)), or D_c / D on cone-corrected rows
-            float vstep = (v.cone ? mg.z : v.r) * rd;
-            const float tf = floorf(tau);
-            const float fu = tau - tf;
-            const int ci = min(max((int)tf, 0), TW - 2);
-            FDKOD_CHECK_EVENT(g_checks_bp, kCheckBpCols, own && ((int)tf < 0 || (int)tf > TW - 2));
-            float v0 = fmaf(z0, vstep, v.cv - (float)mt.y);
-            // the row index is monotone in z: check the run's ends once; a
-            // run outside the staged rows (never expected) contributes zero
-            const float vend = fmaf((float)(ZR - 1), vstep, v0);
-            if (!(v0 >= 0.0f && vend < (float)(mt.z - 1))) {
-                FDKOD_CHECK_EVENT(g_checks_bp, kCheckBpRows, own);
-                w = 0.0f;
-                v0 = 0.5f;
-                vstep = 0.0f;
-            }
-            // 32-bit LDS byte address of the thread's column in this footprint
-            uint32_t tga = (uint32_t)(uintptr_t)(lds_cptr)(tile[g] + ci);
-            asm volatile("" : "+v"(tga));   // keep it one register: address = mad24(row, pitch, tga)
+        const bool more = m + 1 < count;
+        if (kPrefetch && more) fetch(m + 1);             // in flight during the arithmetic below
+        if (m % kFpChunk == 0 && m + kFpChunk < count && tid < 64) footprint(m + kFpChunk);
+        const BpAngle& an = sm.ang[(m / kFpChunk) & 1][m % kFpChunk];
+        const float d = an.dc + fmaf(dx, an.cs, dy * an.sn);
+        const float rd = __builtin_amdgcn_rcpf(d);
+        float tau = fmaf(fmaf(dx, an.ax, dy * an.ay), rd, an.kc);
+        const float w = sr2 * rd * rd;               // (pi / P') U^-2, U = D / R
+        // row offset per unit z: R / D (eq. (9)), or D_c / D on cone-corrected rows
+        const float vstep = an.top * rd;
+        float v0 = fmaf(z0, vstep, an.kr);
+        FDKOD_CHECK_EVENT(g_checks_bp, kCheckBpCols, own && !(tau >= 0.0f && tau < (float)(TW - 1)));
+        FDKOD_CHECK_EVENT(g_checks_bp, kCheckBpRows,
+                          own && !(v0 >= 0.0f && fmaf((float)(ZP - 1), vstep, v0) < (float)(TH - 1)));
+        // the footprint holds every column and row of the run (the planner's
+        // bounds); the clamps keep the reads inside the tile all the same
+        tau = __builtin_amdgcn_fmed3f(tau, 0.0f, (float)(TW - 1) - 0.01f);
+        v0 = __builtin_amdgcn_fmed3f(v0, 0.0f, fmaf(-(float)(ZP - 1), vstep, (float)(TH - 1) - 0.01f));
+        const float fu = __builtin_amdgcn_fractf(tau);
+        // 32-bit LDS byte address of the thread's column in the footprints
+        uint32_t tga = (uint32_t)(uintptr_t)(lds_cptr)(tile + (int)tau);
+        asm volatile("" : "+v"(tga));   // keep it one register: address = mad24(row, pitch, tga)
 #pragma unroll
-            for (int k = 0; k < ZR; ++k) {
-                const float vv = fmaf((float)k, vstep, v0);
-                const float fv = __builtin_amdgcn_fractf(vv);
-                const uint32_t ri = (uint32_t)(int)vv;
-                const lds_f4ptr p = (lds_f4ptr)(uintptr_t)(tga + __umul24(ri, (uint32_t)(TWP * sizeof(float4))));
-                const f4v Q = p[0];
+        for (int k = 0; k < ZP; ++k) {
+            const float vv = k == 0 ? v0 : fmaf((float)k, vstep, v0);
+            const float fv = __builtin_amdgcn_fractf(vv);
+            const uint32_t ri = (uint32_t)(int)vv;
+            const lds_f4ptr p = (lds_f4ptr)(uintptr_t)(tga + __umul24(ri, (uint32_t)(TWP * sizeof(float4))));
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const f4v Q = p[t * SIDE];
                 const float top = fmaf(fu, Q.y, Q.x);          // row ri at tau
                 const float dv = fmaf(fu, Q.w, Q.z);           // row ri + 1 minus row ri at tau
-                acc[k] = fmaf(w, fmaf(fv, dv, top), acc[k]);
-                // four slices per group: their accumulators are complete before
-                // the next group's reads are issued (without this fence the
-                // compiler may issue all ZR reads first and trade occupancy
-                // for the registers that holds them)
+                acc[t][k] = fmaf(w, fmaf(fv, dv, top), acc[t][k]);
+            }
+            // four updates per group: their accumulators are complete before
+            // the next group's reads are issued (without this fence the
+            // compiler may issue all reads first and trade occupancy for the
+            // registers that holds them)
+            if constexpr (NT == 2) {
+                if ((k & 1) == 1)
+                    asm volatile("" : "+v"(acc[0][k - 1]), "+v"(acc[1][k - 1]), "+v"(acc[0][k]), "+v"(acc[1][k])
+                                 :: "memory");
+            } else {
                 if ((k & 3) == 3)
-                    asm volatile("" : "+v"(acc[k - 3]), "+v"(acc[k - 2]), "+v"(acc[k - 1]), "+v"(acc[k])
+                    asm volatile("" : "+v"(acc[0][k - 3]), "+v"(acc[0][k - 2]), "+v"(acc[0][k - 1]), "+v"(acc[0][k])
                                  :: "memory");
             }
         }
         __syncthreads();
         if (more) {
-            if (kPrefetch) {
-#pragma unroll
-                for (int g = 0; g < G; ++g) stage_one(g);
-            } else {
-                fetch_stage(m0 + G);
-            }
+            if (!kPrefetch) fetch(m + 1);
+            stage(m + 1);
         }
         __syncthreads();
     }
-    if (own) {
-        const size_t slice = (size_t)n * n;
-        float* out = v.vol + (size_t)l0 * slice + (size_t)j * n + i;
-        const int kmax = min(ZR, v.nz - l0);
+    if constexpr (AG > 1) {
+        // the groups' sums, added in group order (the tiles are no longer
+        // needed; thread t's value e lies at word NTHR e + t)
+        static_assert(sizeof(sm.tile) >= sizeof(float) * NTHR * NT * ZP, "sums fit the tile");
+        float* mine = (float*)sm.tile;
+        if (grp > 0) {
 #pragma unroll
-        for (int k = 0; k < ZR; ++k) {
-            if (k < kmax) *out = acc[k];
-            out += slice;
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int k = 0; k < ZP; ++k) mine[NTHR * (t * ZP + k) + tid] = acc[t][k];
+        }
+        __syncthreads();
+        if (grp > 0) return;
+        for (int g = 1; g < AG; ++g) {
+            const float* other = (const float*)sms[g].tile;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int k = 0; k < ZP; ++k) acc[t][k] += other[NTHR * (t * ZP + k) + tid];
+        }
+    }
+    if (own) {
+        // lower slices up to the middle, mirrored ones above it; of the
+        // output's slices [zbase, zbase + nz)
+        const size_t slice = (size_t)n * n;
+        float* out = v.vol + (size_t)j * n + i;
+#pragma unroll
+        for (int k = 0; k < ZP; ++k) {
+            const int l = l0 + k, lm = v.nzf - 1 - l;
+            const int ol = l - v.zbase, om = lm - v.zbase;
+            if ((NT == 2 || side == 0) && l <= lm && ol >= 0 && ol < v.nz) out[(size_t)ol * slice] = acc[0][k];
+            if ((NT == 2 || side == 1) && l < lm && om >= 0 && om < v.nz) out[(size_t)om * slice] = acc[NT - 1][k];
         }
     }
 }
 
-template <int ZR, int TW, int TH, int G, int STORE>
-__global__ __launch_bounds__(256) void k_backproject(BpArgs a) {
-    __shared__ BpSmem<TW, TH, G> sm;
+// Whole volume: workgroup = tile x run of slice pairs.
+template <int BX, int ZP, int TW, int TH, int AG, int STORE>
+__global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject(BpArgs a) {
+    __shared__ BpSmem<2, TW, TH> sm[AG];
     // XCD-aware order: each XCD runs a contiguous range of logical blocks
     const int b = blockIdx.x;
     const int lblk = (b & 7) * a.chunk + (b >> 3);
     if (lblk >= a.nlogical) return;               // before any barrier
     const int zt = lblk / a.ntiles;
     const BpTile tl = a.tiles[lblk - zt * a.ntiles];
-    bp_block<ZR, TW, TH, G, STORE>(a.v, zt, tl, sm);
+    bp_block<BX, ZP, 2, TW, TH, AG, STORE>(a.v, zt, 0, tl, sm);
+}
+
+// A slab of slices: workgroup = tile x run, the lower runs that meet the slab
+// first, then the mirrored ones.
+template <int BX, int ZP, int TW, int TH, int AG, int STORE>
+__global__ __launch_bounds__(BX * BX * AG) void k_backproject_slab(BpArgs a) {
+    __shared__ BpSmem<1, TW, TH> sm[AG];
+    const int b = blockIdx.x;
+    const int lblk = (b & 7) * a.chunk + (b >> 3);
+    if (lblk >= a.nlogical) return;               // before any barrier
+    const int zt = lblk / a.ntiles;
+    const BpTile tl = a.tiles[lblk - zt * a.ntiles];
+    const int side = zt >= a.nlow;
+    bp_block<BX, ZP, 1, TW, TH, AG, STORE>(a.v, side ? a.up0 + zt - a.nlow : a.low0 + zt, side, tl, sm);
 }
 
 // Persistent backprojection over the work items of many volumes.  Workgroup
 // b runs on XCD b mod 8 (round-robin dispatch) and first takes tickets from
 // that XCD's range of items, so the tiles that share footprints (same volume,
-// square and slab) meet in one L2; when its range is exhausted it takes
+// square and run) meet in one L2; when its range is exhausted it takes
 // tickets from the other XCDs' ranges in turn.  Every workgroup leaves after
 // all eight ranges are exhausted.  The counters must be zero at launch
 // (launch_reset_counter).
-template <int ZR, int TW, int TH, int G, int STORE>
-__global__ __launch_bounds__(256) void k_backproject_batch(BpBatchArgs a) {
-    __shared__ BpSmem<TW, TH, G> sm;
+template <int BX, int ZP, int TW, int TH, int STORE>
+__global__ __launch_bounds__(BX * BX, 4) void k_backproject_batch(BpBatchArgs a) {
+    __shared__ BpSmem<2, TW, TH> sm[1];
     __shared__ int ticket;
     const int home = blockIdx.x & (kXcds - 1);
     for (int k = 0; k < kXcds; ++k) {
@@ -353,7 +450,7 @@ __global__ __launch_bounds__(256) void k_backproject_batch(BpBatchArgs a) {
             // scalar registers, as the single-volume kernel's arguments are
             const BatchItem bi = uniform_load(a.items + beg + it);
             const BpVol v = uniform_load(a.vols + bi.vol);
-            bp_block<ZR, TW, TH, G, STORE>(v, bi.zt, BpTile{bi.sq, bi.x0, bi.y0, 0}, sm);
+            bp_block<BX, ZP, 2, TW, TH, 1, STORE>(v, bi.zt, 0, BpTile{bi.sq, bi.x0, bi.y0, 0}, sm);
         }
     }
 }
@@ -367,8 +464,19 @@ hipError_t launch_reset_counter(unsigned* counter, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Variant table: (zrun, TW, TH, G).  G is limited so that the LDS of one
-// workgroup stays within 64 KB.
+// Kernel shapes: (tile side, slice pairs per thread, footprint columns,
+// footprint rows, angle groups).  The whole-volume and slab kernels exist for
+// each, the batch kernel for those of one group.
+#define FDKOD_BP_SHAPES_ONE(X) \
+    X(16, 16, 32, 25, 1) X(16, 16, 32, 33, 1) X(16, 16, 32, 49, 1) X(16, 16, 64, 33, 1) X(16, 16, 64, 49, 1) \
+    X(16, 8, 32, 17, 1) X(16, 8, 32, 25, 1) X(16, 8, 32, 41, 1) X(16, 8, 64, 41, 1) X(16, 8, 64, 57, 1) \
+    X(8, 8, 16, 17, 1)
+#define FDKOD_BP_SHAPES(X) FDKOD_BP_SHAPES_ONE(X) \
+    X(16, 32, 32, 49, 1) X(16, 32, 32, 65, 1) \
+    X(16, 8, 32, 17, 2) X(16, 8, 32, 17, 4) X(16, 8, 32, 25, 2) X(16, 8, 32, 25, 4) X(16, 4, 32, 17, 4) \
+    X(8, 8, 16, 17, 4) X(8, 4, 16, 13, 4)
+
+// Public tuning keys (z run, tile columns, tile rows, angles per stage).
 #define FDKOD_BP_VARIANTS(X)  \
     X(64, 32, 96, 1) \
     X(32, 32, 48, 1) X(32, 32, 48, 2) X(32, 32, 48, 4) \
@@ -388,53 +496,70 @@ bool backproject_variant_exists(const BpVariant& var) {
     return false;
 }
 
-hipError_t launch_backproject(const BpArgs& a, const BpVariant& var, int store, hipStream_t st) {
+bool backproject_shape_for(int bx, int zp, int ag, int need_c, int need_r, BpShape* out) {
+    BpShape best{};
+#define FDKOD_X(B, Z, W, H, A)                                                                       \
+    if (B == bx && Z == zp && A == ag && W >= need_c && H >= need_r && (!best.zp || W * H < best.tw * best.th)) \
+        best = BpShape{B, Z, W, H, A};
+    FDKOD_BP_SHAPES(FDKOD_X)
+#undef FDKOD_X
+    *out = best;
+    return best.zp != 0;
+}
+
+static bool same_shape(const BpShape& sh, int bx, int zp, int tw, int th, int ag) {
+    return sh.bx == bx && sh.zp == zp && sh.tw == tw && sh.th == th && sh.ag == ag;
+}
+
+// K<..., STORE> for the run-time storage type
+#define FDKOD_BP_LAUNCH(K, GRID, BLOCK, ...)                                                      \
+    switch (store) {                                                                              \
+        case 0: hipLaunchKernelGGL((K<__VA_ARGS__, 0>), GRID, dim3(BLOCK), 0, st, a); break;      \
+        case 1: hipLaunchKernelGGL((K<__VA_ARGS__, 1>), GRID, dim3(BLOCK), 0, st, a); break;      \
+        default: hipLaunchKernelGGL((K<__VA_ARGS__, 2>), GRID, dim3(BLOCK), 0, st, a); break;     \
+    }                                                                                             \
+    return hipGetLastError();
+
+hipError_t launch_backproject(const BpArgs& a, const BpShape& sh, int store, hipStream_t st) {
     const dim3 grid(8 * a.chunk);
-#define FDKOD_X(Z, W, H, GG)                                                                   \
-    if (var.zrun == Z && var.tile_w == W && var.tile_h == H && var.g == GG) {                  \
-        switch (store) {                                                                       \
-            case 0: hipLaunchKernelGGL((k_backproject<Z, W, H, GG, 0>), grid, dim3(256), 0, st, a); break; \
-            case 1: hipLaunchKernelGGL((k_backproject<Z, W, H, GG, 1>), grid, dim3(256), 0, st, a); break; \
-            default: hipLaunchKernelGGL((k_backproject<Z, W, H, GG, 2>), grid, dim3(256), 0, st, a); break; \
-        }                                                                                      \
-        return hipGetLastError();                                                              \
-    }
-    FDKOD_BP_VARIANTS(FDKOD_X)
+#define FDKOD_X(B, Z, W, H, A) \
+    if (same_shape(sh, B, Z, W, H, A)) { FDKOD_BP_LAUNCH(k_backproject, grid, B * B * A, B, Z, W, H, A) }
+    FDKOD_BP_SHAPES(FDKOD_X)
 #undef FDKOD_X
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_backproject_batch(const BpBatchArgs& a, const BpVariant& var, int store,
-                                    int blocks, hipStream_t st) {
-#define FDKOD_X(Z, W, H, GG)                                                                   \
-    if (var.zrun == Z && var.tile_w == W && var.tile_h == H && var.g == GG) {                  \
-        switch (store) {                                                                       \
-            case 0: hipLaunchKernelGGL((k_backproject_batch<Z, W, H, GG, 0>), dim3(blocks), dim3(256), 0, st, a); break; \
-            case 1: hipLaunchKernelGGL((k_backproject_batch<Z, W, H, GG, 1>), dim3(blocks), dim3(256), 0, st, a); break; \
-            default: hipLaunchKernelGGL((k_backproject_batch<Z, W, H, GG, 2>), dim3(blocks), dim3(256), 0, st, a); break; \
-        }                                                                                      \
-        return hipGetLastError();                                                              \
-    }
-    FDKOD_BP_VARIANTS(FDKOD_X)
+hipError_t launch_backproject_slab(const BpArgs& a, const BpShape& sh, int store, hipStream_t st) {
+    const dim3 grid(8 * a.chunk);
+#define FDKOD_X(B, Z, W, H, A) \
+    if (same_shape(sh, B, Z, W, H, A)) { FDKOD_BP_LAUNCH(k_backproject_slab, grid, B * B * A, B, Z, W, H, A) }
+    FDKOD_BP_SHAPES(FDKOD_X)
 #undef FDKOD_X
     return hipErrorInvalidValue;
 }
 
-int backproject_batch_occupancy(const BpVariant& var, int store) {
+hipError_t launch_backproject_batch(const BpBatchArgs& a, const BpShape& sh, int store, int blocks, hipStream_t st) {
+#define FDKOD_X(B, Z, W, H, A) \
+    if (same_shape(sh, B, Z, W, H, A)) { FDKOD_BP_LAUNCH(k_backproject_batch, dim3(blocks), B * B, B, Z, W, H) }
+    FDKOD_BP_SHAPES_ONE(FDKOD_X)
+#undef FDKOD_X
+    return hipErrorInvalidValue;
+}
+
+int backproject_batch_occupancy(const BpShape& sh, int store) {
     int nb = 0;
-#define FDKOD_X(Z, W, H, GG)                                                                   \
-    if (var.zrun == Z && var.tile_w == W && var.tile_h == H && var.g == GG) {                  \
-        hipError_t e = hipErrorInvalidValue;                                                   \
-        switch (store) {                                                                       \
-            case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_backproject_batch<Z, W, H, GG, 0>, 256, 0); break; \
-            case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_backproject_batch<Z, W, H, GG, 1>, 256, 0); break; \
-            default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_backproject_batch<Z, W, H, GG, 2>, 256, 0); break; \
-        }                                                                                      \
-        return e == hipSuccess ? nb : 0;                                                       \
+    hipError_t e = hipErrorInvalidValue;
+#define FDKOD_X(B, Z, W, H, A)                                                                     \
+    if (same_shape(sh, B, Z, W, H, A)) {                                                           \
+        switch (store) {                                                                           \
+            case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_backproject_batch<B, Z, W, H, 0>, B * B, 0); break; \
+            case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_backproject_batch<B, Z, W, H, 1>, B * B, 0); break; \
+            default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_backproject_batch<B, Z, W, H, 2>, B * B, 0); break; \
+        }                                                                                          \
     }
-    FDKOD_BP_VARIANTS(FDKOD_X)
+    FDKOD_BP_SHAPES_ONE(FDKOD_X)
 #undef FDKOD_X
-    return 0;
+    return e == hipSuccess ? nb : 0;
 }
 
 }  // namespace fdkod

@@ -25,10 +25,11 @@ struct fdkod_plan_s {
     // staged_cpt = 0 when it does not apply to the plan)
     int dec_chunks = 1;
     int staged_cpt = 0, staged_segc = 0;
-    // backprojection kernel shape
+    // backprojection: the public key and the kernel shape chosen for it
     fdkod::BpVariant bpv{32, 32, 48, 1};
+    fdkod::BpShape bps{};
     bool bp_ok = false;     // some variant's LDS footprint holds a block's footprint
-    int ntiles = 0;
+    int ntiles = 0, ntiles8 = 0;   // tiles of 16 x 16 and of 8 x 8 voxels
     int64_t ws_row_elems = 0;  // workspace elements per detector row: P' * sum_q W_q
     int64_t ws_elems = 0;      // ws_row_elems * N
     float tuned_bp_ms = 0.0f, tuned_dec_ms = 0.0f;
@@ -56,6 +57,7 @@ struct fdkod_plan_s {
     float* d_gtail = nullptr;
     float2* d_tw = nullptr;
     fdkod::BpTile* d_tiles = nullptr;
+    fdkod::BpTile* d_tiles8 = nullptr;
     std::vector<void*> allocs;
 };
 
@@ -76,9 +78,18 @@ inline int max_chunks(const fdkod_plan_s* pl) { return pl->nw > 2 ? kDecimMaxChu
 inline int cone_side(const fdkod_plan_s* pl) { return pl->cone ? (pl->n + (1 << pl->s) - 1) >> pl->s : 0; }
 // a backprojection variant exists and its LDS footprint holds the plan's
 bool variant_holds(const fdkod_plan_s* pl, const BpVariant& v);
+// the first key of a z run that holds the plan's geometry
+bool first_variant(const fdkod_plan_s* pl, int zrun, BpVariant* out);
+// the kernel shape of one plan (or a batch's: groups = false) for a z run;
+// false when none holds the geometry
+bool bp_shape(const fdkod_plan_s* const* pls, int count, int zrun, bool groups, BpShape* out);
+// set a plan's key and the shape that follows from it (false: unchanged)
+bool bp_set_variant(fdkod_plan_s* pl, const BpVariant& v);
+// launch arguments of a plan's shape over `runs` runs of its tiles
+BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs);
 // tasks per square of the decimation for a chunk count
 inline int dec_tasks_per_sq(int wmax, int chunks) { return (wmax + 64 * chunks - 1) / (64 * chunks); }
-// z slabs of the backprojection for a variant
+// runs of zrun slices in nz
 inline int bp_zslabs(int nz, int zrun) { return (nz + zrun - 1) / zrun; }
 
 // argument blocks for one plan (data pointers supplied by the caller); the
