@@ -403,8 +403,8 @@ fdkod_status fdkod_adamw_step(float* master, float* m1, float* m2, const float* 
  *   volume slab      float32 [nzs][N][N]
  * The band calls compute for those rows and slices exactly what the
  * whole-volume calls compute (bit for bit when v0 is even, as
- * fdkod_band_rows returns it; the filter transforms detector rows 2k and
- * 2k + 1 together).  Asynchronous on
+ * fdkod_band_rows returns it, and z0 is a multiple of the plan's z_run; the
+ * filter transforms detector rows 2k and 2k + 1 together).  Asynchronous on
  * `stream`; they allocate nothing.
  * ------------------------------------------------------------------------- */
 

@@ -290,8 +290,8 @@ bool bp_shape(const fdkod_plan_s* const* pls, int count, int zrun, bool groups, 
         for (int i = 0; i < count; ++i) {
             const fdkod_plan_s* pl = pls[i];
             int c = 0, r = 0;
-            // the lower runs reach from the volume's end to at most zp slices past its middle
-            bp_need(pl->n, pl->r, bx, zp, std::max((pl->nz - 1) / 2.0, (double)zp), cone_side(pl), 0.05, 2, &c, &r);
+            // the lower runs reach from the volume's end to at most two runs past its middle
+            bp_need(pl->n, pl->r, bx, zp, std::max((pl->nz - 1) / 2.0, 2.0 * zp), cone_side(pl), 0.05, 2, &c, &r);
             need_c = std::max(need_c, c);
             need_r = std::max(need_r, r);
             if ((int64_t)(bx == 8 ? pl->ntiles8 : pl->ntiles) * bp_zslabs((pl->nz + 1) / 2, zp) > (int64_t)1 << 30)

@@ -98,23 +98,28 @@ StreamLayout stream_layout(const fdkod_plan_s* pl, int nzs) {
 
 fdkod_status launch_slab(const fdkod_plan_s* pl, const void* filt, const void* ws, int v0, int nv, int z0,
                          int nzs, float* vol, hipStream_t st) {
-    // the whole volume's runs that meet the slab: lower ones by their own
-    // slices, mirrored ones by their images (the same arithmetic for every
-    // slice as in the whole volume)
+    // lower slices of the slab, and the lower slices whose images lie in it,
+    // two runs to a workgroup.  A slab that starts at a multiple of the z run
+    // takes the whole volume's runs (its bits); any other starts its own, so
+    // that no slice outside it is computed for their sake.
     const int zp = pl->bps.zp, mid = (pl->nz - 1) / 2;      // last lower slice
-    int low0 = 0, nlow = 0, up0 = 0, nup = 0;
+    const int unit = z0 % pl->bpv.zrun == 0 ? zp : 1;
+    int low0 = 0, low1 = 0, up0 = 0, up1 = 0;
     if (z0 <= mid) {
-        low0 = z0 / zp;
-        nlow = std::min(z0 + nzs - 1, mid) / zp - low0 + 1;
+        low0 = z0 / unit * unit;
+        low1 = std::min(z0 + nzs - 1, mid) + 1;
     }
     if (z0 + nzs - 1 > mid) {
-        up0 = (pl->nz - 1 - (z0 + nzs - 1)) / zp;
-        nup = (pl->nz - 1 - std::max(z0, mid + 1)) / zp - up0 + 1;
+        up0 = (pl->nz - z0 - nzs) / unit * unit;
+        up1 = pl->nz - std::max(z0, mid + 1);
     }
+    const int nlow = bp_zslabs(low1 - low0, 2 * zp), nup = bp_zslabs(up1 - up0, 2 * zp);
     BpArgs a = bp_args(pl, bp_vol_band(pl, filt, ws, vol, v0, nv, z0, nzs), nlow + nup);
     a.low0 = low0;
+    a.low1 = low1;
     a.nlow = nlow;
     a.up0 = up0;
+    a.up1 = up1;
     HIP_TRY(launch_backproject_slab(a, pl->bps, pl->store, st), "backprojection kernel launch");
     return FDKOD_OK;
 }

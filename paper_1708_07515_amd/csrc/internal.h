@@ -144,7 +144,8 @@ struct BpArgs {
     int nzt;                // runs of slice pairs (slab: of slices)
     int nlogical;           // ntiles * nzt
     int chunk;              // logical WGs per XCD
-    int low0, nlow, up0;    // slab: first lower run and their count, first mirrored run
+    int low0, low1, nlow;   // slab: its lower slices [low0, low1) and their workgroups,
+    int up0, up1;           // the lower slices [up0, up1) whose images lie in it
 };
 
 // One work item of the batched (persistent) backprojection.

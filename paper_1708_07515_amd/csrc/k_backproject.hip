@@ -65,17 +65,18 @@ constexpr float kBpMargin = 0.01f;
 // One angle's constants of a 16 x 16 tile and run.
 struct BpAngle {
     float ax, ay, cs, sn;        // R (dL Dc - Lc dD) / Dc = ax dx + ay dy; cos, sin
-    float dc, kc, top, kr;       // Dc, c_u - u0 - c0, R (or Dc on cone-corrected rows), c_v - r0
-    int c0, off[2];              // footprint's first column; byte offset of its first sample (lower, mirrored)
+    float dc, kc, top, kr[2];    // Dc, c_u - u0 - c0, R (or Dc on cone-corrected rows), c_v - r0 of each footprint
+    int c0, off[2];              // the footprints' first column; byte offset of the first sample of each
     int nq;                      // quad rows per staging lane
+    int pad[3];
 };
 
-// LDS of one group of BX BX threads: the NT staged footprints (the quads of TH
+// LDS of one group of BX BX threads: two staged footprints (the quads of TH
 // detector rows: TH - 1 rows of TW + 4 quads) and, for two chunks of angles,
 // the per-angle constants.
-template <int NT, int TW, int TH>
+template <int TW, int TH>
 struct BpSmem {
-    float4 tile[NT * (TH - 1) * (TW + 4)];
+    float4 tile[2 * (TH - 1) * (TW + 4)];
     BpAngle ang[2][kFpChunk];
 };
 
@@ -84,25 +85,31 @@ __device__ __forceinline__ float from_next_lane(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130 /* wave_shl:1 */, 0xf, 0xf, false));
 }
 
-// Backprojection of one BX x BX (x, y) tile tl (BX = 16 or 8) over run `run` of ZP lower
-// slices (l = run ZP + k) and their mirror images (l' = N_z - 1 - l):
-// NT = 2 both (side ignored), NT = 1 one of them (side 0: lower, 1: mirrored).
+// Backprojection of one BX x BX (x, y) tile tl (BX = 16 or 8).  PAIR: the ZP
+// lower slices from l0 and their mirror images (l' = N_z - 1 - l).  Otherwise
+// (slabs): the lower (side 0) or mirrored (1) slices of the 2 ZP from l0, in
+// two runs of ZP with row indices of their own (the second only if `two`);
+// the arithmetic of a slice is the same, so a slab whose runs start where the whole volume's do gives its
+// bits.
+//
 // AG groups of BX BX threads share the angles (each takes a contiguous part)
-// and their sums are added in group order at the end.  The arithmetic of a
-// slice does not depend on NT, so a slab gives the bits of the whole volume.
-// Every thread of the workgroup calls it (it contains barriers).
+// and their sums are added in group order at the end.  Every thread of the
+// workgroup calls it (it contains barriers).
 //
 // While angle m is accumulated from LDS, the detector samples of angle m + 1
 // are already being loaded into registers, so global-memory latency overlaps
 // the arithmetic; two barriers per angle separate the LDS phases.
-template <int BX, int ZP, int NT, int TW, int TH, int AG, int STORE>
-__device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, const BpTile& tl,
-                                         BpSmem<NT, TW, TH> (&sms)[AG]) {
+template <int BX, int ZP, bool PAIR, int TW, int TH, int AG, int STORE>
+__device__ __forceinline__ void bp_block(const BpVol& v, int l0, int side, bool two, const BpTile& tl,
+                                         BpSmem<TW, TH> (&sms)[AG]) {
+    // fused only where written: every instantiation rounds alike, and
+    // D = Dc + dD rounds once
+#pragma clang fp contract(off)
     // the thread within its group, and the group's part of the angles
     constexpr int NTHR = BX * BX;
     const int tid = AG == 1 ? threadIdx.x : threadIdx.x & (NTHR - 1);
     const int grp = AG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NTHR);
-    BpSmem<NT, TW, TH>& sm = sms[grp];
+    BpSmem<TW, TH>& sm = sms[grp];
     const int per = (v.pd + AG - 1) / AG;
     const int mbeg = grp * per, mend = min(mbeg + per, v.pd);
     using S = Store<STORE>;
@@ -140,9 +147,8 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
 
     // the run covers ZP slices even past the volume's middle (those voxels
     // are computed and discarded), so the staged rows always hold the whole run
-    const int l0 = run * ZP;
-    const float z0 = (float)l0 - v.cz;
-    const float zlast = (float)(l0 + ZP - 1) - v.cz;
+    // first slice of each footprint's run
+    const float z0[2] = {(float)l0 - v.cz, (float)(PAIR ? l0 : l0 + ZP) - v.cz};
 
     const bool direct = v.row_stride_direct != 0;
     const int row_stride = direct ? v.row_stride_direct : width;
@@ -150,10 +156,10 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
     const T* data = (const T*)v.data + (direct ? 0 : sq.y_off_row * v.nv);
     const float kq = v.cu - (float)u0;            // tau = rel + kq
 
-    // staging map: footprint t is staged by NTHR / NT threads; a lane keeps
+    // staging map: footprint t is staged by half of the threads; a lane keeps
     // one footprint column and nq consecutive rows (their quads), for which
     // it loads nq + 1 rows
-    constexpr int SIDE_THR = NTHR / NT;
+    constexpr int SIDE_THR = NTHR / 2;
     constexpr int NGRP = SIDE_THR / TW;
     static_assert((TH - 1) % NGRP == 0, "uniform staging trip count");
     constexpr int NQ = (TH - 1) / NGRP;          // at most; an angle's own count is BpAngle::nq
@@ -163,9 +169,9 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
     const int sgrp = (tid % SIDE_THR) / TW;
     // the footprint this thread stages (uniform over a wave unless one wave
     // stages both), and whether it is a mirrored one
-    constexpr bool kSideUniform = NT == 1 || SIDE_THR >= 64;
-    const int st_t = NT == 1 ? 0 : kSideUniform ? __builtin_amdgcn_readfirstlane(tid / SIDE_THR) : tid / SIDE_THR;
-    const int mirrored = NT == 2 ? st_t : side;
+    constexpr bool kSideUniform = SIDE_THR >= 64;
+    const int st_t = kSideUniform ? __builtin_amdgcn_readfirstlane(tid / SIDE_THR) : tid / SIDE_THR;
+    const int mirrored = PAIR ? st_t : side;
 
     // footprints of the block at the kFpChunk angles from m0 (a multiple of
     // kFpChunk), one lane of the first wave per angle: eq. (1) at the block's
@@ -180,26 +186,35 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
         const int m = mbeg + m0 + tid;
         if (tid < kFpChunk && m < mend) {
             const float2 t = v.trig[m];
-            const float dc = v.r + sq.xc * t.x + sq.yc * t.y;
-            const float lc = sq.yc * t.x - sq.xc * t.y;
+            const float dc = fmaf(sq.yc, t.y, fmaf(sq.xc, t.x, v.r));
+            const float lc = fmaf(sq.yc, t.x, -(sq.xc * t.y));
             const float rdc = __builtin_amdgcn_rcpf(dc);
-            float tlo = INFINITY, vlo = INFINITY, vhi = -INFINITY;
+            float tlo = INFINITY, iulo = INFINITY, iuhi = -INFINITY;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float cx = (k & 1) ? bx1 : bx0;
                 const float cy = (k & 2) ? by1 : by0;
-                const float dl = cy * t.x - cx * t.y;
-                const float dd = cx * t.x + cy * t.y;
+                const float dl = fmaf(cy, t.x, -(cx * t.y));
+                const float dd = fmaf(cx, t.x, cy * t.y);
                 const float rd = __builtin_amdgcn_rcpf(dc + dd);
-                tlo = fminf(tlo, v.r * (dl * dc - lc * dd) * rdc * rd + kq);
+                tlo = fminf(tlo, fmaf(v.r * fmaf(dl, dc, -(lc * dd)) * rdc, rd, kq));
                 const float iu = (v.cone ? dc : v.r) * rd;   // row offset per unit z
-                const float va = z0 * iu + v.cv, vb = zlast * iu + v.cv;
-                vlo = fminf(vlo, fminf(va, vb));
-                vhi = fmaxf(vhi, fmaxf(va, vb));
+                iulo = fminf(iulo, iu);
+                iuhi = fmaxf(iuhi, iu);
             }
             const int c0 = (int)floorf(tlo - kBpMargin);
-            const int r0 = (int)floorf(vlo - kBpMargin);
-            const int quads = (int)floorf(vhi + kBpMargin) + 1 - r0;    // quad rows r0 .. floor(vhi)
+            int r0[2], quads = 0;
+#pragma unroll
+            for (int f = 0; f < (PAIR ? 1 : 2); ++f) {
+                const float zl = z0[f] + (float)(ZP - 1);
+                const float vlo = fminf(fminf(fmaf(z0[f], iulo, v.cv), fmaf(z0[f], iuhi, v.cv)),
+                                        fminf(fmaf(zl, iulo, v.cv), fmaf(zl, iuhi, v.cv)));
+                const float vhi = fmaxf(fmaxf(fmaf(z0[f], iulo, v.cv), fmaf(z0[f], iuhi, v.cv)),
+                                        fmaxf(fmaf(zl, iulo, v.cv), fmaf(zl, iuhi, v.cv)));
+                r0[f] = (int)floorf(vlo - kBpMargin);
+                quads = max(quads, (int)floorf(vhi + kBpMargin) + 1 - r0[f]);    // quad rows r0 .. floor(vhi)
+            }
+            if (PAIR) r0[1] = r0[0];
             const float lr = v.r * lc * rdc;
             BpAngle a;
             a.ax = -fmaf(v.r, t.y, lr * t.x);
@@ -209,10 +224,13 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
             a.dc = dc;
             a.kc = kq - (float)c0;
             a.top = v.cone ? dc : v.r;
-            a.kr = v.cv - (float)r0;
             a.c0 = c0;
-            a.off[0] = ((r0 - v.v0) * row_stride + c0) * ES;
-            a.off[1] = ((n - 1 - r0 - v.v0) * row_stride + c0) * ES;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const bool mir = PAIR ? f == 1 : side != 0;
+                a.kr[f] = v.cv - (float)r0[f];
+                a.off[f] = (((mir ? n - 1 - r0[f] : r0[f]) - v.v0) * row_stride + c0) * ES;
+            }
             a.nq = min((quads + NGRP - 1) / NGRP, NQ);
             sm.ang[slot][tid] = a;
         }
@@ -235,7 +253,7 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             uniform_ptr(data + (size_t)(mbeg + m) * plane), (short)0, (int)plane_bytes, 0x00020000);
         const int nq = __builtin_amdgcn_readfirstlane(an.nq);
-        const int col = an.c0 + scol, at = an.off[mirrored] + scol * ES + __mul24(sgrp, nq * rstep_bytes);
+        const int col = an.c0 + scol, at = an.off[st_t] + scol * ES + __mul24(sgrp, nq * rstep_bytes);
         const int off0 = (unsigned)col < (unsigned)width ? at : (int)0x80000000;
         // (each offset in its own register, never folded into the
         // instruction's constant offset: the range check must see the
@@ -279,9 +297,9 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
     };
 
     const float sr2 = v.scale * v.r * v.r;
-    float acc[NT][ZP];
+    float acc[2][ZP];
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int k = 0; k < ZP; ++k) acc[t][k] = 0.0f;
 
@@ -315,43 +333,62 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
         const float w = sr2 * rd * rd;               // (pi / P') U^-2, U = D / R
         // row offset per unit z: R / D (eq. (9)), or D_c / D on cone-corrected rows
         const float vstep = an.top * rd;
-        float v0 = fmaf(z0, vstep, an.kr);
         FDKOD_CHECK_EVENT(g_checks_bp, kCheckBpCols, own && !(tau >= 0.0f && tau < (float)(TW - 1)));
-        FDKOD_CHECK_EVENT(g_checks_bp, kCheckBpRows,
-                          own && !(v0 >= 0.0f && fmaf((float)(ZP - 1), vstep, v0) < (float)(TH - 1)));
         // the footprint holds every column and row of the run (the planner's
         // bounds); the clamps keep the reads inside the tile all the same
         tau = __builtin_amdgcn_fmed3f(tau, 0.0f, (float)(TW - 1) - 0.01f);
-        v0 = __builtin_amdgcn_fmed3f(v0, 0.0f, fmaf(-(float)(ZP - 1), vstep, (float)(TH - 1) - 0.01f));
+        const float vmost = fmaf(-(float)(ZP - 1), vstep, (float)(TH - 1) - 0.01f);
+        float v0[2];
+#pragma unroll
+        for (int f = 0; f < (PAIR ? 1 : 2); ++f) {
+            v0[f] = fmaf(z0[f], vstep, an.kr[f]);
+            FDKOD_CHECK_EVENT(g_checks_bp, kCheckBpRows, own && !(v0[f] >= 0.0f && v0[f] < vmost + 0.01f));
+            v0[f] = __builtin_amdgcn_fmed3f(v0[f], 0.0f, vmost);
+        }
         const float fu = __builtin_amdgcn_fractf(tau);
         // 32-bit LDS byte address of the thread's column in the footprints
         uint32_t tga = (uint32_t)(uintptr_t)(lds_cptr)(tile + (int)tau);
         asm volatile("" : "+v"(tga));   // keep it one register: address = mad24(row, pitch, tga)
+        // one update: the sample of footprint t at row ri + fv
+        auto update = [&](int t, int k, lds_f4ptr p, float fv) {
+            const f4v Q = p[t * SIDE];
+            const float top = fmaf(fu, Q.y, Q.x);          // row ri at tau
+            const float dv = fmaf(fu, Q.w, Q.z);           // row ri + 1 minus row ri at tau
+            acc[t][k] = fmaf(w, fmaf(fv, dv, top), acc[t][k]);
+        };
+        auto row_of = [&](int t, int k, float* fv) -> lds_f4ptr {
+            const float vv = k == 0 ? v0[t] : fmaf((float)k, vstep, v0[t]);
+            *fv = __builtin_amdgcn_fractf(vv);
+            return (lds_f4ptr)(uintptr_t)(tga + __umul24((uint32_t)(int)vv, (uint32_t)(TWP * sizeof(float4))));
+        };
+        // four updates per group: their accumulators are complete before the
+        // next group's reads are issued (without these fences the compiler may
+        // issue all reads first and trade occupancy for the registers that
+        // holds them)
+        if constexpr (PAIR) {
 #pragma unroll
-        for (int k = 0; k < ZP; ++k) {
-            const float vv = k == 0 ? v0 : fmaf((float)k, vstep, v0);
-            const float fv = __builtin_amdgcn_fractf(vv);
-            const uint32_t ri = (uint32_t)(int)vv;
-            const lds_f4ptr p = (lds_f4ptr)(uintptr_t)(tga + __umul24(ri, (uint32_t)(TWP * sizeof(float4))));
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const f4v Q = p[t * SIDE];
-                const float top = fmaf(fu, Q.y, Q.x);          // row ri at tau
-                const float dv = fmaf(fu, Q.w, Q.z);           // row ri + 1 minus row ri at tau
-                acc[t][k] = fmaf(w, fmaf(fv, dv, top), acc[t][k]);
-            }
-            // four updates per group: their accumulators are complete before
-            // the next group's reads are issued (without this fence the
-            // compiler may issue all reads first and trade occupancy for the
-            // registers that holds them)
-            if constexpr (NT == 2) {
+            for (int k = 0; k < ZP; ++k) {
+                float fv;
+                const lds_f4ptr p = row_of(0, k, &fv);
+                update(0, k, p, fv);
+                update(1, k, p, fv);
                 if ((k & 1) == 1)
                     asm volatile("" : "+v"(acc[0][k - 1]), "+v"(acc[1][k - 1]), "+v"(acc[0][k]), "+v"(acc[1][k])
                                  :: "memory");
-            } else {
-                if ((k & 3) == 3)
-                    asm volatile("" : "+v"(acc[0][k - 3]), "+v"(acc[0][k - 2]), "+v"(acc[0][k - 1]), "+v"(acc[0][k])
-                                 :: "memory");
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                if (t == 1 && !two) break;           // uniform
+#pragma unroll
+                for (int k = 0; k < ZP; ++k) {
+                    float fv;
+                    const lds_f4ptr p = row_of(t, k, &fv);
+                    update(t, k, p, fv);
+                    if ((k & 3) == 3)
+                        asm volatile("" : "+v"(acc[t][k - 3]), "+v"(acc[t][k - 2]), "+v"(acc[t][k - 1]), "+v"(acc[t][k])
+                                     :: "memory");
+                }
             }
         }
         __syncthreads();
@@ -364,11 +401,11 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
     if constexpr (AG > 1) {
         // the groups' sums, added in group order (the tiles are no longer
         // needed; thread t's value e lies at word NTHR e + t)
-        static_assert(sizeof(sm.tile) >= sizeof(float) * NTHR * NT * ZP, "sums fit the tile");
+        static_assert(sizeof(sm.tile) >= sizeof(float) * NTHR * 2 * ZP, "sums fit the tile");
         float* mine = (float*)sm.tile;
         if (grp > 0) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int k = 0; k < ZP; ++k) mine[NTHR * (t * ZP + k) + tid] = acc[t][k];
         }
@@ -377,7 +414,7 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
         for (int g = 1; g < AG; ++g) {
             const float* other = (const float*)sms[g].tile;
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int k = 0; k < ZP; ++k) acc[t][k] += other[NTHR * (t * ZP + k) + tid];
         }
@@ -389,10 +426,13 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
         float* out = v.vol + (size_t)j * n + i;
 #pragma unroll
         for (int k = 0; k < ZP; ++k) {
-            const int l = l0 + k, lm = v.nzf - 1 - l;
-            const int ol = l - v.zbase, om = lm - v.zbase;
-            if ((NT == 2 || side == 0) && l <= lm && ol >= 0 && ol < v.nz) out[(size_t)ol * slice] = acc[0][k];
-            if ((NT == 2 || side == 1) && l < lm && om >= 0 && om < v.nz) out[(size_t)om * slice] = acc[NT - 1][k];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const bool mir = PAIR ? t == 1 : side != 0;
+                const int l = l0 + k + (PAIR ? 0 : t * ZP), lm = v.nzf - 1 - l;
+                const int o = (mir ? lm : l) - v.zbase;
+                if ((mir ? l < lm : l <= lm) && o >= 0 && o < v.nz) out[(size_t)o * slice] = acc[t][k];
+            }
         }
     }
 }
@@ -400,28 +440,29 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int run, int side, cons
 // Whole volume: workgroup = tile x run of slice pairs.
 template <int BX, int ZP, int TW, int TH, int AG, int STORE>
 __global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject(BpArgs a) {
-    __shared__ BpSmem<2, TW, TH> sm[AG];
+    __shared__ BpSmem<TW, TH> sm[AG];
     // XCD-aware order: each XCD runs a contiguous range of logical blocks
     const int b = blockIdx.x;
     const int lblk = (b & 7) * a.chunk + (b >> 3);
     if (lblk >= a.nlogical) return;               // before any barrier
     const int zt = lblk / a.ntiles;
     const BpTile tl = a.tiles[lblk - zt * a.ntiles];
-    bp_block<BX, ZP, 2, TW, TH, AG, STORE>(a.v, zt, 0, tl, sm);
+    bp_block<BX, ZP, true, TW, TH, AG, STORE>(a.v, zt * ZP, 0, true, tl, sm);
 }
 
-// A slab of slices: workgroup = tile x run, the lower runs that meet the slab
-// first, then the mirrored ones.
+// A slab of slices: workgroup = tile x two runs of one side, those of the
+// lower runs that meet the slab first, then the mirrored ones'.
 template <int BX, int ZP, int TW, int TH, int AG, int STORE>
-__global__ __launch_bounds__(BX * BX * AG) void k_backproject_slab(BpArgs a) {
-    __shared__ BpSmem<1, TW, TH> sm[AG];
+__global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject_slab(BpArgs a) {
+    __shared__ BpSmem<TW, TH> sm[AG];
     const int b = blockIdx.x;
     const int lblk = (b & 7) * a.chunk + (b >> 3);
     if (lblk >= a.nlogical) return;               // before any barrier
     const int zt = lblk / a.ntiles;
     const BpTile tl = a.tiles[lblk - zt * a.ntiles];
     const int side = zt >= a.nlow;
-    bp_block<BX, ZP, 1, TW, TH, AG, STORE>(a.v, side ? a.up0 + zt - a.nlow : a.low0 + zt, side, tl, sm);
+    const int l0 = side ? a.up0 + 2 * ZP * (zt - a.nlow) : a.low0 + 2 * ZP * zt;
+    bp_block<BX, ZP, false, TW, TH, AG, STORE>(a.v, l0, side, l0 + ZP < (side ? a.up1 : a.low1), tl, sm);
 }
 
 // Persistent backprojection over the work items of many volumes.  Workgroup
@@ -433,7 +474,7 @@ __global__ __launch_bounds__(BX * BX * AG) void k_backproject_slab(BpArgs a) {
 // (launch_reset_counter).
 template <int BX, int ZP, int TW, int TH, int STORE>
 __global__ __launch_bounds__(BX * BX, 4) void k_backproject_batch(BpBatchArgs a) {
-    __shared__ BpSmem<2, TW, TH> sm[1];
+    __shared__ BpSmem<TW, TH> sm[1];
     __shared__ int ticket;
     const int home = blockIdx.x & (kXcds - 1);
     for (int k = 0; k < kXcds; ++k) {
@@ -450,7 +491,7 @@ __global__ __launch_bounds__(BX * BX, 4) void k_backproject_batch(BpBatchArgs a)
             // scalar registers, as the single-volume kernel's arguments are
             const BatchItem bi = uniform_load(a.items + beg + it);
             const BpVol v = uniform_load(a.vols + bi.vol);
-            bp_block<BX, ZP, 2, TW, TH, 1, STORE>(v, bi.zt, 0, BpTile{bi.sq, bi.x0, bi.y0, 0}, sm);
+            bp_block<BX, ZP, true, TW, TH, 1, STORE>(v, bi.zt * ZP, 0, true, BpTile{bi.sq, bi.x0, bi.y0, 0}, sm);
         }
     }
 }
