@@ -140,7 +140,7 @@ fdkod_status fdkod_learned_backward(fdkod_plan_t pl, const void* filt, const flo
     fdkod_status st = learned_check(pl);
     if (st != FDKOD_OK) return st;
     const LearnedArgs a = learned_args(pl, filt, nullptr, dws, weights, grad, pl->n);
-    HIP_TRY(launch_learned_bwd(a, pl->store, (hipStream_t)stream), "learned gradient kernel launch");
+    HIP_TRY(launch_learned_bwd(a, pl->d, pl->store, (hipStream_t)stream), "learned gradient kernel launch");
     return FDKOD_OK;
 }
 
@@ -152,7 +152,7 @@ fdkod_status fdkod_learned_backward_band(fdkod_plan_t pl, const void* filt_band,
     if (st != FDKOD_OK) return st;
     if ((st = check_band(pl, v0, nrows)) != FDKOD_OK) return st;
     const LearnedArgs a = learned_args(pl, filt_band, nullptr, dws_band, weights, grad, nrows);
-    HIP_TRY(launch_learned_bwd(a, pl->store, (hipStream_t)stream), "learned gradient kernel launch");
+    HIP_TRY(launch_learned_bwd(a, pl->d, pl->store, (hipStream_t)stream), "learned gradient kernel launch");
     return FDKOD_OK;
 }
 

@@ -517,41 +517,59 @@ __global__ __launch_bounds__(kThreads) void k_learned_fwd_ring(LearnedArgs a) {
 // holds columns 4g .. 4g + 3 of channel lr.  That is the B-operand layout of a
 // product over columns, so every reduction over positions is an MFMA:
 //   dW2^T_a[b][ch] += G^T[b][col] x A_a[col][ch],   G[col][b] = dR[col - b + 2]
-//   dA_a[col][ch]   = G[col][b] x W2_a^T[b][ch]      (b = 0..4, padded to 8)
+//   dA_a[col][ch]   = G[col][b] x W2_a^T[b][ch]      (b = 0..4)
 //   dW1^T[tap][ch] += X^T[tap][col] x dH[col][ch]
-// The first two take FP32 operands (16x16x4 products: A, the BF16-rounded
-// activation, and dR, in FP32), the third BF16 ones (dH rounded, as S).
-// db1 is a per-lane sum of dH, reduced over the lane groups at the end.
-constexpr int kDrPad = 16;                          // dR row: column c at index c + 16
-constexpr int kDrLen = kDrPad + 16 * ((kLearnedMaxWidth + 15) / 16) + 18;
+// All are BF16 products with FP32 accumulation.  A, W2, S and the rounded dH
+// are BF16 already; dR is FP32 and enters as the sum of three BF16 parts
+// (8 significant bits each: 24, so the parts add up to dR exactly), which
+// the row's staging splits once.  dA's three parts times five offsets fill
+// one K = 16 product, dW2 takes two K = 32 ones (two parts, the third), and
+// dW1 two angles in each K = 32 one: 26 matrix instructions per tile of 16
+// columns, against 45 (30 of them FP32 ones of twice the time) before.
+// Columns outside [0, W) have dR operands of zero.  db1 is a per-lane sum of
+// dH, reduced over the lane groups at the end.
+//
+// RING: the forward's row reuse (its conditions): four new rows per angle,
+// fetched while the current angle is computed and staged into the ring slots
+// outside its window, dR in two buffers, one barrier per angle.  Otherwise
+// the next angle's nine rows are fetched during the current one and staged
+// after it.  Without the prefetch every angle waited for its rows: 32-slice
+// slab at 2000^2, s = 4: 28.0 ms.
+constexpr int kDrPad = 4;                           // dR row: column c at index c + 4
+constexpr int kDrLen = 16 * ((kLearnedMaxWidth + 15) / 16) + 16;
 
+template <bool RING>
 struct BwdSmem {
+    uint32_t sp[(RING ? kRingSlots : 9) * kPP];
+    uint32_t dr[RING ? 2 : 1][3][kDrLen];           // the parts in the pair layout (columns x and x + 1)
     int off_tab[9];
-    uint32_t sp[9 * kPP];
-    float dr[kDrLen];
 };
 
-template <int STORE, bool CUBIC>
-__global__ __launch_bounds__(kThreads) void k_learned_bwd(LearnedArgs a) {
+template <int STORE, bool CUBIC, bool RING>
+__global__ __launch_bounds__(kThreads, 4) void k_learned_bwd(LearnedArgs a) {
     // the task state, and after the last task the waves' partial gradients
     __shared__ union {
-        BwdSmem s;
+        BwdSmem<RING> s;
         float red[4 * kLearnedParams];
     } smu;
-    BwdSmem& sm = smu.s;
+    BwdSmem<RING>& sm = smu.s;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int lr = lane & 15, lg = lane >> 4;
     const FwdOperands op = load_fwd_operands<kPP>(a.w);
     const float b1l = bf2f(a.w[kOffB1 + lr]);             // bias of the lane's channel
-    // B operands of dA: W2[ch = lr][a2][b = 4 t + g] (zero for b >= 5)
-    float w2b[5][2];
+    // dA: K slot s = 4 g + i is part s / 5 of dR at offset b = s % 5 (slot 15:
+    // weight zero); B operand W2[ch = lr][a2][b], A operand read at gco
+    s4v w2op[5];
+    int gco[4];
 #pragma unroll
-    for (int a2 = 0; a2 < 5; ++a2)
+    for (int i = 0; i < 4; ++i) {
+        const int sl = min(4 * lg + i, 14);
+        gco[i] = 2 * ((sl / 5) * kDrLen + kDrPad + lr - sl % 5 + 2);       // in 16-bit halves
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int b = 4 * t + lg;
-            w2b[a2][t] = b < 5 ? bf2f(a.w[kOffW2 + lr * 25 + a2 * 5 + b]) : 0.0f;
-        }
+        for (int a2 = 0; a2 < 5; ++a2)
+            w2op[a2][i] = 4 * lg + i < 15 ? (short)a.w[kOffW2 + lr * 25 + a2 * 5 + sl % 5] : (short)0;
+    }
+    const int gto = kDrPad + 4 * lg - min(lr, 4) + 2;       // dW2: columns 4 g .. of row b = lr (rows above 4 are discarded)
     // the lane's dW1 rows: taps lr and lr + 16 (taps >= 25 read a valid
     // tile entry and give discarded rows)
     int xoff[2];
@@ -566,6 +584,83 @@ __global__ __launch_bounds__(kThreads) void k_learned_bwd(LearnedArgs a) {
     for (int a2 = 0; a2 < 5; ++a2) gw2[a2] = (f4v){0.0f, 0.0f, 0.0f, 0.0f};
     float gb1 = 0.0f, gb2 = 0.0f;
 
+    typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+    typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+    // one tile of 16 columns: S rows at sp, dR parts at dr
+    auto tile_grad = [&](const uint32_t* sp, const uint32_t* dr, int col0, int width) {
+        u2v gt[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const uint32_t* g = dr + t * kDrLen + col0 + gto;
+            gt[t] = (u2v){g[0], g[2]};
+        }
+        const uint16_t* dh16 = reinterpret_cast<const uint16_t*>(dr) + 2 * col0;
+        s4v gc = {(short)dh16[gco[0]], (short)dh16[gco[1]], (short)dh16[gco[2]], (short)dh16[gco[3]]};
+        if (col0 + 16 > width) {                           // uniform: the last tile
+            const int left = width - (col0 + 4 * lg);      // columns of the lane's four inside [0, W)
+            const uint32_t m0 = left >= 2 ? 0xFFFFFFFFu : (left == 1 ? 0xFFFFu : 0u);
+            const uint32_t m1 = left >= 4 ? 0xFFFFFFFFu : (left == 3 ? 0xFFFFu : 0u);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) gt[t] &= (u2v){m0, m1};
+            if (col0 + lr >= width) gc = (s4v){0, 0, 0, 0};
+        }
+        const bf8v gt01 = __builtin_bit_cast(bf8v, (u4v){gt[0][0], gt[0][1], gt[1][0], gt[1][1]});
+        const bf8v gt2 = __builtin_bit_cast(bf8v, (u4v){gt[2][0], gt[2][1], 0u, 0u});
+        const uint32_t* ph = sp + col0 + op.hoff;
+        const uint32_t* pv = sp + col0 + op.voff;
+        u2v dhp = {0u, 0u}, xp[2];
+#pragma unroll
+        for (int a2 = 0; a2 < 5; ++a2) {
+            const u4v d = {ph[a2 * kPP], ph[a2 * kPP + 2], pv[a2 * kPP], pv[a2 * kPP + kPP]};
+            const f4v b1v = {b1l, b1l, b1l, b1l};
+            // H[col0 + 4 g + i][ch = lr], bias included
+            const f4v h =
+                __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, d), op.w1, b1v, 0, 0, 0);
+            // A = ReLU(H) rounded to BF16 (the value conv2 multiplies)
+            const s4v act = relu_bf16(h);
+            const s8v act2 = {act[0], act[1], act[2], act[3], act[0], act[1], act[2], act[3]};
+            gw2[a2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gt01, __builtin_bit_cast(bf8v, act2), gw2[a2], 0, 0, 0);
+            // (the same K = 32 instruction for the third part: measured, a K = 16
+            // product right behind the K = 32 one it accumulates onto read two of
+            // its four sums before they were written)
+            gw2[a2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gt2, __builtin_bit_cast(bf8v, act2), gw2[a2], 0, 0, 0);
+            const f4v zero = {0.0f, 0.0f, 0.0f, 0.0f};
+            const f4v da = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(gc, w2op[a2], zero, 0, 0, 0);
+            float dh[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                dh[i] = h[i] > 0.0f ? da[i] : 0.0f;
+                gb1 += dh[i];
+            }
+            // B operand of dW1: dH[col0 + 4 g + i][ch = lr] in BF16; A operand: S
+            // of tap lr + 16 mt at columns col0 + 4 g .. + 3 (pair entries x and
+            // x + 2 hold staged columns x .. x + 3)
+            typedef float f2v __attribute__((ext_vector_type(2)));
+            typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
+            const u2v dhop = {__builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){dh[0], dh[1]}, bf2v)),
+                              __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){dh[2], dh[3]}, bf2v))};
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+                const uint32_t* e = sp + a2 * kPP + col0 + xoff[mt];
+                const u2v x = {e[0], e[2]};
+                if (a2 == 4) {
+                    gw1[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+                        __builtin_bit_cast(s4v, x), __builtin_bit_cast(s4v, dhop), gw1[mt], 0, 0, 0);
+                } else if (a2 & 1) {
+                    gw1[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf8v, (u4v){xp[mt][0], xp[mt][1], x[0], x[1]}),
+                        __builtin_bit_cast(bf8v, (u4v){dhp[0], dhp[1], dhop[0], dhop[1]}), gw1[mt], 0, 0, 0);
+                } else {
+                    xp[mt] = x;
+                }
+            }
+            dhp = dhop;
+            // (the next angle's operand loads stay behind: moved ahead of these
+            // products they cost the fourth wave per SIMD its registers)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
     const unsigned ntot = fwd_grid(a);
     for (unsigned task = blockIdx.x; task < ntot; task += gridDim.x) {
         const int x8 = (int)(task % kXcds), i8 = (int)(task / kXcds);
@@ -577,91 +672,102 @@ __global__ __launch_bounds__(kThreads) void k_learned_bwd(LearnedArgs a) {
         __syncthreads();                                   // the previous task's reads are done
         const float* acq = a.ac_p + (size_t)q * a.p;   // crop offsets a_c(beta_p) + u0
         const float u0f = (float)u0;
-        if (threadIdx.x < 9) {
+        if (!RING && threadIdx.x < 9) {
             int off = ((int)threadIdx.x - 4) * a.d % a.p;
             sm.off_tab[threadIdx.x] = off < 0 ? off + a.p : off;
         }
-        for (int e = threadIdx.x; e < 9 * kPP; e += kThreads) sm.sp[e] = 0u;
-        for (int e = threadIdx.x; e < kDrLen; e += kThreads) sm.dr[e] = 0.0f;
+        for (int e = threadIdx.x; e < (RING ? kRingSlots : 9) * kPP; e += kThreads) sm.sp[e] = 0u;
+        for (int e = threadIdx.x; e < (RING ? 2 : 1) * 3 * kDrLen; e += kThreads) (&sm.dr[0][0][0])[e] = 0u;
         const int col = threadIdx.x;                        // staged column (local column col - 2)
         const int jj = col - 2;
         const bool stager = col < width + 4;
         const bool valid = jj >= 0 && jj < width;
         const size_t yrow = (size_t)a.squares[q].y_off_row * a.nv + (size_t)v * width;
         const size_t yplane = (size_t)a.nv * width;
-        CentreWalk cw(a.p, a.pd);
-        __syncthreads();
-        int offr[9];
+        // the row of dR at the thread's column, and its three parts into buffer b
+        auto load_dr = [&](int m) { return col < width ? a.dws[yrow + (size_t)m * yplane + col] : 0.0f; };
+        auto stage_dr = [&](int b, float g) {
+            gb2 += g;
+            if (col >= width) return;
+            const float g1 = g - bf2f(f2bf(g));
+            const float g2 = g1 - bf2f(f2bf(g1));
+            const float part[3] = {g, g1, g2};
 #pragma unroll
-        for (int t = 0; t < 9; ++t) offr[t] = __builtin_amdgcn_readfirstlane(sm.off_tab[t]);
-        for (int m = 0; m < a.pd; ++m) {
+            for (int t = 0; t < 3; ++t) {
+                uint16_t* h = reinterpret_cast<uint16_t*>(sm.dr[b][t]);
+                const uint16_t val = (uint16_t)f2bf(part[t]);
+                h[2 * (kDrPad + col)] = val;
+                h[2 * (kDrPad + col - 1) + 1] = val;
+            }
+        };
+        __syncthreads();
+        if constexpr (RING) {
+            int pn = (a.p - (4 * a.d) % a.p) % a.p;        // p(0) = -4 d mod P
+            auto fetch = [&](SRow<CUBIC>& r) {
+                srow_load<STORE, CUBIC>(a, v, pn, const_load(acq + pn) + u0f, jj, valid, r);
+                pn += a.d;
+                if (pn >= a.p) pn -= a.p;
+            };
             {
                 SRow<CUBIC> rows[9];
-                s_fetch_rows<STORE, CUBIC>(a, acq, u0f, v, cw.c, jj, valid, offr, rows);
-                if (stager) s_stage_pairs(sm.sp, col, rows);
-                cw.next();
-            }
-            if (col < width) {
-                const float g = a.dws[yrow + (size_t)m * yplane + col];
-                sm.dr[kDrPad + col] = g;
-                gb2 += g;
-            }
-            __syncthreads();
-            for (int tile = wave; tile < ntile; tile += kThreads / 64) {
-                const int col0 = tile * 16;
-                // dR operands of the tile (shared by the five angles):
-                // G^T[b = lr][col0 + 4 g + j] and G[col0 + lr][b = 4 t + g]
-                float gt[4], gc[2];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) gt[j] = sm.dr[kDrPad + col0 + 4 * lg + j - lr + 2];
+                for (int u = 0; u < 9; ++u) fetch(rows[u]);
+                const float g = load_dr(0);
+                if (stager) {
 #pragma unroll
-                for (int t = 0; t < 2; ++t) gc[t] = sm.dr[kDrPad + col0 + lr - (4 * t + lg) + 2];
-                bool cin[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) cin[i] = col0 + 4 * lg + i < width;
-                const uint32_t* ph = sm.sp + col0 + op.hoff;
-                const uint32_t* pv = sm.sp + col0 + op.voff;
-#pragma unroll
-                for (int a2 = 0; a2 < 5; ++a2) {
-                    typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-                    const u4v d = {ph[a2 * kPP], ph[a2 * kPP + 2], pv[a2 * kPP], pv[a2 * kPP + kPP]};
-                    const f4v b1v = {b1l, b1l, b1l, b1l};
-                    // H[col0 + 4 g + i][ch = lr], bias included
-                    const f4v h = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, d), op.w1, b1v,
-                                                                           0, 0, 0);
-                    // A = ReLU(H) rounded to BF16 (the value conv2 multiplies), zero outside [0, W)
-                    float av[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) av[i] = cin[i] ? bf2f(f2bf(fmaxf(h[i], 0.0f))) : 0.0f;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        gw2[a2] = __builtin_amdgcn_mfma_f32_16x16x4f32(gt[j], av[j], gw2[a2], 0, 0, 0);
-                    f4v da = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-                        da = __builtin_amdgcn_mfma_f32_16x16x4f32(gc[t], w2b[a2][t], da, 0, 0, 0);
-                    float dh[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        dh[i] = (cin[i] && h[i] > 0.0f) ? da[i] : 0.0f;
-                        gb1 += dh[i];
-                    }
-                    // B operand of dW1: dH[col0 + 4 g + i][ch = lr] in BF16
-                    const s4v dhop = {(short)f2bf(dh[0]), (short)f2bf(dh[1]), (short)f2bf(dh[2]),
-                                      (short)f2bf(dh[3])};
-#pragma unroll
-                    for (int mt = 0; mt < 2; ++mt) {
-                        // A operand: S of tap lr + 16 mt at columns col0 + 4 g .. + 3 (pair
-                        // entries x and x + 2 hold staged columns x .. x + 3)
-                        const int e = a2 * kPP + col0 + xoff[mt];
-                        const uint32_t lo = sm.sp[e], hi = sm.sp[e + 2];
-                        typedef uint32_t u2v __attribute__((ext_vector_type(2)));
-                        const s4v xop = __builtin_bit_cast(s4v, (u2v){lo, hi});
-                        gw1[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xop, dhop, gw1[mt], 0, 0, 0);
-                    }
+                    for (int u = 0; u < 9; ++u) ring_stage<kPP, CUBIC>(sm.sp, u, col, rows[u]);
                 }
+                stage_dr(0, g);
+                vmem_drain();
             }
             __syncthreads();
+            for (int m = 0; m < a.pd; ++m) {
+                const bool more = m + 1 < a.pd;
+                SRow<CUBIC> rows[4];
+                float g = 0.0f;
+                if (more) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) fetch(rows[k]);
+                    g = load_dr(m + 1);
+                }
+                const uint32_t* win = sm.sp + ((4 * m) & (kRing - 1)) * kPP;
+#pragma unroll 1
+                for (int tile = wave; tile < ntile; tile += kThreads / 64)
+                    tile_grad(win, &sm.dr[m & 1][0][0], tile * 16, width);
+                if (more) {
+                    if (stager) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            ring_stage<kPP, CUBIC>(sm.sp, (4 * m + 9 + k) & (kRing - 1), col, rows[k]);
+                    }
+                    stage_dr((m + 1) & 1, g);
+                }
+                vmem_drain();
+                __syncthreads();
+            }
+        } else {
+            CentreWalk cw(a.p, a.pd);
+            int offr[9];
+#pragma unroll
+            for (int t = 0; t < 9; ++t) offr[t] = __builtin_amdgcn_readfirstlane(sm.off_tab[t]);
+            SRow<CUBIC> rows[9];
+            s_fetch_rows<STORE, CUBIC>(a, acq, u0f, v, cw.c, jj, valid, offr, rows);
+            float g = load_dr(0);
+            for (int m = 0; m < a.pd; ++m) {
+                if (stager) s_stage_pairs(sm.sp, col, rows);
+                stage_dr(0, g);
+                vmem_drain();
+                __syncthreads();
+                if (m + 1 < a.pd) {
+                    cw.next();
+                    s_fetch_rows<STORE, CUBIC>(a, acq, u0f, v, cw.c, jj, valid, offr, rows);
+                    g = load_dr(m + 1);
+                }
+#pragma unroll 1
+                for (int tile = wave; tile < ntile; tile += kThreads / 64)
+                    tile_grad(sm.sp, &sm.dr[0][0][0], tile * 16, width);
+                __syncthreads();
+            }
         }
     }
     // the wave's partials: dW1^T[tap = 4 g + i + 16 mt][ch = lr],
@@ -699,14 +805,26 @@ __global__ __launch_bounds__(kThreads) void k_learned_bwd(LearnedArgs a) {
             ((red[e] + red[kLearnedParams + e]) + red[2 * kLearnedParams + e]) + red[3 * kLearnedParams + e];
 }
 
-// grad[e] = sum over the backward pass's workgroups of their partials, in
-// workgroup order.
-__global__ __launch_bounds__(256) void k_grad_sum(const float* partials, int nblocks, float* grad) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= kLearnedParams) return;
+// grad[e] = sum over the backward pass's workgroups of their partials, in a
+// fixed order: sixteen threads take every sixteenth workgroup each, their
+// sums are added in thread order.  (One thread per parameter walked all 1024
+// workgroups, one dependent load after the other: 240-320 us.)
+constexpr int kGradSeg = 16;
+__global__ __launch_bounds__(16 * kGradSeg) void k_grad_sum(const float* partials, int nblocks, float* grad) {
+    __shared__ float part[kGradSeg][16];
+    const int i = threadIdx.x & 15, seg = threadIdx.x >> 4;
+    const int e = blockIdx.x * 16 + i;
     float acc = 0.0f;
-    for (int b = 0; b < nblocks; ++b) acc += partials[(size_t)b * kLearnedParams + e];
-    grad[e] = acc;
+    if (e < kLearnedParams) {
+#pragma unroll 8
+        for (int b = seg; b < nblocks; b += kGradSeg) acc += partials[(size_t)b * kLearnedParams + e];
+    }
+    part[seg][i] = acc;
+    __syncthreads();
+    if (seg == 0 && e < kLearnedParams) {
+        for (int k = 1; k < kGradSeg; ++k) acc += part[k][i];
+        grad[e] = acc;
+    }
 }
 
 // Transpose of the backprojection of decimated data (training): for every
@@ -957,9 +1075,14 @@ void launch_fwd_store(const LearnedArgs& a, int max_width, bool ring, int store,
     }
 }
 
+// consecutive decimated angles share five of their nine S rows (see above)
+bool ring_rows(const LearnedArgs& a, int dfac) {
+    return dfac >= 4 && a.p % dfac == 0 && a.pd * dfac == a.p && a.d * 4 == dfac;
+}
+
 hipError_t launch_learned_fwd(const LearnedArgs& a, int max_width, int dfac, int store, hipStream_t st) {
     if (max_width > kLearnedMaxWidth) return hipErrorInvalidValue;
-    const bool ring = dfac >= 4 && a.p % dfac == 0 && a.pd * dfac == a.p && a.d * 4 == dfac && a.p <= kRingMaxP;
+    const bool ring = ring_rows(a, dfac) && a.p <= kRingMaxP;
     if (a.cubic) launch_fwd_store<true>(a, max_width, ring, store, st);
     else launch_fwd_store<false>(a, max_width, ring, store, st);
     return hipGetLastError();
@@ -970,25 +1093,28 @@ hipError_t launch_learned_fwd(const LearnedArgs& a, int max_width, int dfac, int
 // per compute unit.
 constexpr unsigned kBwdGrid = kLearnedBwdGrid;
 
-hipError_t launch_learned_bwd(const LearnedArgs& a, int store, hipStream_t st) {
+template <int STORE>
+void launch_bwd(const LearnedArgs& a, bool ring, dim3 grid, hipStream_t st) {
+    if (ring) {
+        if (a.cubic) hipLaunchKernelGGL((k_learned_bwd<STORE, true, true>), grid, dim3(kThreads), 0, st, a);
+        else hipLaunchKernelGGL((k_learned_bwd<STORE, false, true>), grid, dim3(kThreads), 0, st, a);
+    } else {
+        if (a.cubic) hipLaunchKernelGGL((k_learned_bwd<STORE, true, false>), grid, dim3(kThreads), 0, st, a);
+        else hipLaunchKernelGGL((k_learned_bwd<STORE, false, false>), grid, dim3(kThreads), 0, st, a);
+    }
+}
+
+hipError_t launch_learned_bwd(const LearnedArgs& a, int dfac, int store, hipStream_t st) {
     if (!a.partials) return hipErrorInvalidValue;
+    const bool ring = ring_rows(a, dfac);
     const unsigned ntot = fwd_grid(a);
     const dim3 grid(ntot < kBwdGrid ? ntot : kBwdGrid);
     switch (store) {
-        case 0:
-            if (a.cubic) hipLaunchKernelGGL((k_learned_bwd<0, true>), grid, dim3(kThreads), 0, st, a);
-            else hipLaunchKernelGGL((k_learned_bwd<0, false>), grid, dim3(kThreads), 0, st, a);
-            break;
-        case 1:
-            if (a.cubic) hipLaunchKernelGGL((k_learned_bwd<1, true>), grid, dim3(kThreads), 0, st, a);
-            else hipLaunchKernelGGL((k_learned_bwd<1, false>), grid, dim3(kThreads), 0, st, a);
-            break;
-        default:
-            if (a.cubic) hipLaunchKernelGGL((k_learned_bwd<2, true>), grid, dim3(kThreads), 0, st, a);
-            else hipLaunchKernelGGL((k_learned_bwd<2, false>), grid, dim3(kThreads), 0, st, a);
-            break;
+        case 0: launch_bwd<0>(a, ring, grid, st); break;
+        case 1: launch_bwd<1>(a, ring, grid, st); break;
+        default: launch_bwd<2>(a, ring, grid, st); break;
     }
-    hipLaunchKernelGGL(k_grad_sum, dim3((kLearnedParams + 255) / 256), dim3(256), 0, st, a.partials,
+    hipLaunchKernelGGL(k_grad_sum, dim3((kLearnedParams + 15) / 16), dim3(16 * kGradSeg), 0, st, a.partials,
                        (int)grid.x, a.grad);
     return hipGetLastError();
 }
