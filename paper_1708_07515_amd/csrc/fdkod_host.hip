@@ -237,7 +237,7 @@ namespace fdkod {
 // consecutive slices within |z| <= zmax covers at any angle, margins included,
 // from the slice's smallest depth Dmin = R - (N-1)/sqrt(2).  cone_side > 0:
 // cone-corrected rows of squares at most cone_side voxels wide.
-static void bp_need(int n, double r, int edge, int slices, double zmax, int cone_side, double slack, int margin, int* need_c, int* need_r) {
+void bp_need(int n, double r, int edge, int slices, double zmax, int cone_side, double slack, int margin, int* need_c, int* need_r) {
     const double c = (n - 1) / 2.0;
     const double dmin = r - c * std::sqrt(2.0);
     const double mag = r / dmin;

@@ -2,6 +2,7 @@
 // (forward correction, weight gradient, transpose of the backprojection,
 // squared-error residual, AdamW).  Every call is asynchronous on the given
 // stream and allocates nothing.
+#include <algorithm>
 #include <cmath>
 
 #include "plan.h"
@@ -44,7 +45,7 @@ LearnedArgs learned_args(const fdkod_plan_s* pl, const void* filt, void* ws, con
 
 AdjArgs adjoint_args(const fdkod_plan_s* pl, const float* resid, float* dws, int v0, int nv, int zbase,
                      int nzs) {
-    AdjArgs a;
+    AdjArgs a{};
     a.resid = resid;
     a.dws = dws;
     a.squares = pl->d_sq;
@@ -71,6 +72,29 @@ AdjArgs adjoint_args(const fdkod_plan_s* pl, const float* resid, float* dws, int
     // of |contributions| per unit of max |resid|.
     const double umax = pl->r / (pl->r - (pl->n - 1) / std::sqrt(2.0));
     a.bound = 2.0 * (M_PI / pl->pd) * umax * umax * (double)a.nvox;
+    // The gather form takes blocks whose footprint fits its tile, with the
+    // longest run of slices that does, when the voxels of one column span at
+    // most four of a line: 2 / (R / D sin 45 deg) of them, D up to R + (N - 1) /
+    // sqrt(2), the angle off by a block's half diagonal seen from the source.
+    // R above about 2.8 N; a closer source keeps the scatter form.
+    a.zr = 0;
+    const double half = (pl->n - 1) / std::sqrt(2.0), near = pl->r - half;
+    const double slope = pl->r / (pl->r + half) * std::sin(M_PI / 4 - 8.0 * std::sqrt(2.0) / near);
+    const double zmax = std::max(std::fabs(zbase - a.cz), std::fabs(zbase + nzs - 1 - a.cz));
+    for (int zr = kAdjGatherZ; zr >= 1 && slope > 2.0 / 3.9; --zr) {
+        int need_c = 0, need_r = 0;
+        bp_need(pl->n, pl->r, kTileXY, zr, zmax, 0, 0.05, 2, &need_c, &need_r);
+        if (need_c > kAdjGatherCols || need_r > kAdjGatherRows) continue;
+        a.nruns = bp_zslabs(nzs, zr);
+        a.zr = (nzs + a.nruns - 1) / a.nruns;
+        // few blocks (small volumes) share the angles out, at least four to each
+        const int64_t blocks = (int64_t)pl->ntiles * a.nruns;
+        a.parts = (int)std::max<int64_t>(1, std::min<int64_t>((2048 + blocks - 1) / blocks, pl->pd / 4));
+        if (blocks * a.parts > (int64_t)1 << 30) a.zr = 0;
+        a.nlogical = (int)(blocks * a.parts);
+        a.chunk = (a.nlogical + 7) / 8;
+        break;
+    }
     a.qs = (AdjScale*)pl->d_adj;
     a.dq = (unsigned long long*)((char*)pl->d_adj + 256);
     return a;

@@ -253,7 +253,12 @@ struct AdjArgs {
     AdjScale* qs;            // the call's scale (device)
     double bound;            // an upper bound of sum |weight| over the voxels, per unit of max |resid|
     int64_t nvox;            // voxels of resid
+    // the gather form: slices of a run (0: the scatter form), runs, parts of
+    // the angles, workgroups in all and for each XCD
+    int zr, nruns, parts, nlogical, chunk;
 };
+// most slices of a gather block's run; rows and columns its footprint may span
+constexpr int kAdjGatherZ = 24, kAdjGatherRows = 32, kAdjGatherCols = 32;
 
 struct AdamArgs {
     float* master;           // FP32 parameters

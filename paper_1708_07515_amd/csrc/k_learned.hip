@@ -33,6 +33,8 @@
 // products, so the global-memory latency of one angle overlaps the
 // arithmetic of the previous one; when the decimated angles fall on original
 // ones the forward pass fetches only the four rows that the next angle adds.
+#include <algorithm>
+
 #include "internal.h"
 #include "dtype.h"
 #include "geom.h"
@@ -849,15 +851,24 @@ __global__ __launch_bounds__(16 * kGradSeg) void k_grad_sum(const float* partial
 // slice instead of two.
 constexpr int kAdjZR = 32, kAdjTW = 40, kAdjTH = 48;
 
-// max |resid| over the voxels, as the bits of a non-negative float
+// max |resid| over the voxels, as the bits of a non-negative float: one
+// atomic per workgroup (one per wave of 1024 workgroups queued on the one
+// address: 40 us for 2e5 voxels)
 __global__ __launch_bounds__(256) void k_adj_absmax(const float* resid, int64_t count, AdjScale* qs) {
+    __shared__ unsigned part[4];
     unsigned m = 0;
+#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x)
         m = max(m, __float_as_uint(resid[i]) & 0x7FFFFFFFu);
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) m = max(m, (unsigned)__shfl_xor((int)m, off, 64));
-    if ((threadIdx.x & 63) == 0 && m) atomicMax(&qs->rmax, m);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        m = max(max(part[0], part[1]), max(part[2], part[3]));
+        if (m) atomicMax(&qs->rmax, m);
+    }
 }
 
 // clears the maximum and the sums' buffer (a fill kernel, no memset node)
@@ -885,10 +896,13 @@ __global__ void k_adj_scale(AdjScale* qs, double bound) {
 
 // dY = the int64 sums / qscale, rounded once to FP32
 __global__ void k_adj_convert(const unsigned long long* dq, const AdjScale* qs, float* dws, int64_t count) {
-    const double q = qs->qscale;
+    // qscale is a power of two: its reciprocal and the products are exact (a
+    // 64-bit division per entry took 1.0 ms where the traffic takes 0.7)
+    const double q = qs->qscale, rq = 1.0 / q;
+#pragma unroll 4
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * blockDim.x)
-        dws[i] = q > 0.0 ? (float)((double)(long long)dq[i] / q) : __builtin_nanf("");
+        dws[i] = q > 0.0 ? (float)((double)(long long)dq[i] * rq) : __builtin_nanf("");
 }
 
 __global__ __launch_bounds__(256) void k_bp_adjoint(AdjArgs a) {
@@ -1010,6 +1024,217 @@ __global__ __launch_bounds__(256) void k_bp_adjoint(AdjArgs a) {
     }
 }
 
+// The transpose in two separable steps, for blocks whose footprint fits 32 x
+// 32 samples (every source not close to the volume).  Workgroup = a 16 x 16
+// tile, a run of zr slices and a part of the angles.  Per angle:
+//
+//  1. rows: every voxel column (x, y) sums its residuals onto the detector rows
+//     they lie between, weighted by (pi / P') U^-2 -- a scan along z in
+//     registers, each row stored once -- into H[voxel][row] in LDS.
+//  2. columns: entry (row, column) gathers w(tau - column) H[voxel][row] over the
+//     voxels within one column.  Those lie between two rays, i.e. between two
+//     straight lines of the tile, so along the axis that the column changes
+//     faster with, each of the 16 voxel lines has them in a run of at most four,
+//     whose start is linear in the line's index.  A thread owns one column and
+//     four rows (one 128-bit LDS read per voxel).
+//
+// A line's at most four terms are added in FP32 (as the rows' are), the lines
+// in FP64, and the block's sum is rounded once to a multiple of 1 / qscale and
+// added to the int64 sums: the result depends on no order, and holds fewer
+// roundings than one integer per term.  No LDS atomics: the scatter form
+// above spends its time on their conflicts and on a 64-bit conversion for
+// each term (2600 VALU instructions per thread and angle); bound here: VALU
+// issue (about 900 per thread and angle), then the LDS.
+// 32-slice slab at 2000^2, s = 4: 22.3 ms scattered, 8.75 gathered; 96 x 96 x 24
+// voxels, 32 angles: 648 us, 29.
+constexpr int kGatZ = kAdjGatherZ, kGatRows = kAdjGatherRows;
+static_assert(kGatRows == 32 && kAdjGatherCols == 32, "thread = one column and four rows");
+constexpr int kGatPitch = kGatRows + 4;    // words of a voxel's rows
+constexpr int kGatLine = 16 * kGatPitch + 4;   // words of a line of 16 voxels
+constexpr int kGatChunk = 16;              // angles whose constants are computed together
+constexpr float kGatMargin = 0.01f;        // of a sample: far above the coordinates' rounding
+
+struct GatAngle {
+    float ax, ay, cs, sn;       // R (dL Dc - Lc dD) / Dc = ax dx + ay dy; cos, sin
+    float dc, kc, kr;           // Dc, c_u - u0 - c0, c_v - r0
+    int c0, r0, nrows, xdom;    // footprint's first column and row, rows; 1: the column changes faster along x
+};
+
+__global__ __launch_bounds__(256, 4) void k_bp_adjoint_gather(AdjArgs a) {
+    __shared__ float4 hbuf[16 * kGatLine / 4];
+    __shared__ float taus[256 + 16];
+    __shared__ GatAngle ang[kGatChunk];
+    float* H = (float*)hbuf;
+    const int tid = threadIdx.x;
+    // XCD-aware order: each XCD runs a contiguous range (neighbouring tiles add to the same rows)
+    const int lblk = (int)(blockIdx.x & 7) * a.chunk + (int)(blockIdx.x >> 3);
+    if (lblk >= a.nlogical) return;
+    const int tile = lblk % a.ntiles, rest = lblk / a.ntiles;
+    const int run = rest % a.nruns, part = rest / a.nruns;
+    const int per = (a.pd + a.parts - 1) / a.parts;
+    const int m0 = part * per, m1 = min(m0 + per, a.pd);
+    const BpTile tl = a.tiles[tile];
+    const SquareDesc sq = a.squares[tl.sq];
+    const int2 gd = a.grid[tl.sq];
+    const int u0 = gd.x, width = gd.y;
+    const int tx = tid & 15, ty = tid >> 4;
+    const int ix1 = min(tl.x0 + 15, sq.x1 - 1), iy1 = min(tl.y0 + 15, sq.y1 - 1);
+    const int i = tl.x0 + tx, j = tl.y0 + ty;
+    const bool own = i <= ix1 && j <= iy1;
+    const int l0 = run * a.zr, nz = min(a.zr, a.nz - l0);
+    const float bx0 = (float)tl.x0 - a.cu - sq.xc, by0 = (float)tl.y0 - a.cu - sq.yc;
+    const float bx1 = (float)ix1 - a.cu - sq.xc, by1 = (float)iy1 - a.cu - sq.yc;
+    const float dx = (float)min(i, ix1) - a.cu - sq.xc, dy = (float)min(j, iy1) - a.cu - sq.yc;
+    const float z0 = (float)(a.zbase + l0) - a.cz, z1 = (float)(a.zbase + l0 + nz - 1) - a.cz;
+    const float kq = a.cu - (float)u0;
+    // the voxel column's residuals (zero outside the square)
+    float rz[kGatZ];
+#pragma unroll
+    for (int k = 0; k < kGatZ; ++k)
+        rz[k] = own && k < nz ? a.resid[((size_t)(l0 + k) * a.n + j) * a.n + i] : 0.0f;
+    const double qscale = a.qs->qscale;
+    const float sr2 = a.scale * a.r * a.r;
+    const int c = tid & 31, rg = tid >> 5;         // step 2: the thread's column and rows 4 rg ..
+
+    for (int m = m0; m < m1; ++m) {
+        const int ci = (m - m0) & (kGatChunk - 1);
+        if (ci == 0) {
+            // the chunk's angles, one lane each: the footprint from the block's corners
+            __syncthreads();
+            if (tid < kGatChunk && m + tid < m1) {
+                const float2 t = a.trig[m + tid];
+                const float dc = a.r + sq.xc * t.x + sq.yc * t.y;
+                const float lc = sq.yc * t.x - sq.xc * t.y;
+                const float rdc = 1.0f / dc;
+                const float lr = a.r * lc * rdc;
+                GatAngle g;
+                g.ax = -(a.r * t.y + lr * t.x);
+                g.ay = a.r * t.x - lr * t.y;
+                g.cs = t.x;
+                g.sn = t.y;
+                g.dc = dc;
+                float tlo = INFINITY, vlo = INFINITY, vhi = -INFINITY;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float cx = (k & 1) ? bx1 : bx0, cy = (k & 2) ? by1 : by0;
+                    const float rd = 1.0f / (dc + (cx * t.x + cy * t.y));
+                    tlo = fminf(tlo, (cx * g.ax + cy * g.ay) * rd + kq);
+                    const float va = z0 * a.r * rd + a.cv, vb = z1 * a.r * rd + a.cv;
+                    vlo = fminf(vlo, fminf(va, vb));
+                    vhi = fmaxf(vhi, fmaxf(va, vb));
+                }
+                g.c0 = (int)floorf(tlo - kGatMargin);
+                g.r0 = (int)floorf(vlo - kGatMargin);
+                g.nrows = min((int)floorf(vhi + kGatMargin) + 2 - g.r0, kGatRows);
+                g.kc = kq - (float)g.c0;
+                g.kr = a.cv - (float)g.r0;
+                // d tau / dx and d tau / dy at the block's centre, up to a common factor
+                const float mx = 0.5f * (bx0 + bx1), my = 0.5f * (by0 + by1);
+                const float num = mx * g.ax + my * g.ay, d = dc + (mx * t.x + my * t.y);
+                g.xdom = fabsf(g.ax * d - num * t.x) >= fabsf(g.ay * d - num * t.y);
+                ang[tid] = g;
+            }
+            __syncthreads();
+        }
+        const GatAngle& g = ang[ci];
+        const bool xdom = __builtin_amdgcn_readfirstlane(g.xdom) != 0;
+        const int nrows = __builtin_amdgcn_readfirstlane(g.nrows);
+        {
+            // step 1: the voxel column's rows
+            const int line = xdom ? ty : tx, pos = xdom ? tx : ty;
+            float* h = H + line * kGatLine + pos * kGatPitch;
+            const float d = g.dc + fmaf(dx, g.cs, dy * g.sn);
+            const float rd = 1.0f / d;
+            taus[line * 16 + pos] = fmaf(fmaf(dx, g.ax, dy * g.ay), rd, g.kc);
+            const float w = sr2 * rd * rd, vstep = a.r * rd;
+            // the whole run lies in [0, nrows - 1): the clamp only keeps the rows of
+            // a block that the planner has not bounded inside H
+            const float v0 = fminf(fmaxf(fmaf(z0, vstep, g.kr), 0.0f),
+                                   fmaf(-(float)(nz - 1), vstep, (float)(kGatRows - 1) - kGatMargin));
+#pragma unroll
+            for (int e = 0; e < kGatRows / 4; ++e)
+                if (4 * e < nrows) *(float4*)(h + 4 * e) = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            int rc = (int)v0;
+            float s0 = 0.0f, s1 = 0.0f;            // rows rc and rc + 1
+#pragma unroll
+            for (int k = 0; k < kGatZ; ++k) {
+                if (k >= nz) break;                // uniform
+                const float vv = fmaf((float)k, vstep, v0);
+                const int iv = (int)vv;
+                const float fv = __builtin_amdgcn_fractf(vv);
+                const int adv = iv - rc;           // 0, 1 or 2: one slice moves by R / D < 2 rows
+                if (adv > 0) h[rc] = s0;
+                if (adv > 1) h[rc + 1] = s1;
+                s0 = adv == 0 ? s0 : (adv == 1 ? s1 : 0.0f);
+                s1 = adv == 0 ? s1 : 0.0f;
+                rc = iv;
+                const float wr = w * rz[k];
+                s0 = fmaf(wr, 1.0f - fv, s0);
+                s1 = fmaf(wr, fv, s1);
+            }
+            h[rc] = s0;
+            h[rc + 1] = s1;
+        }
+        __syncthreads();
+        if (4 * rg < nrows) {
+            // step 2: P(l) = the position where line l crosses the column T:
+            // tau = T where p (A1 - q C1) = q Dc + l (q C2 - A2), q = T - kc, in
+            // offsets p along and l across the lines
+            const float A1 = xdom ? g.ax : g.ay, A2 = xdom ? g.ay : g.ax;
+            const float C1 = xdom ? g.cs : g.sn, C2 = xdom ? g.sn : g.cs;
+            const float p0 = xdom ? bx0 : by0, q0 = xdom ? by0 : bx0;
+            const float col = (float)c;
+            float lo = 0.0f, dlo = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const float q = (e ? col + 1.0f : col - 1.0f) - g.kc;
+                const float rden = 1.0f / (A1 - q * C1);
+                const float slope = (q * C2 - A2) * rden;
+                const float at = fmaf(q0, slope, q * g.dc * rden) - p0;
+                if (e == 0 || at < lo) {
+                    lo = at;
+                    dlo = slope;
+                }
+            }
+            lo -= kGatMargin;
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            const float* hrow = H + 4 * rg;
+#pragma unroll 2
+            for (int line = 0; line < 16; ++line) {
+                const int pi = (int)fminf(fmaxf(ceilf(fmaf((float)line, dlo, lo)), 0.0f), 12.0f);
+                const float* tp = taus + line * 16 + pi;
+                const float* hp = hrow + line * kGatLine + pi * kGatPitch;
+                float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float wt = __builtin_amdgcn_fmed3f(1.0f - fabsf(tp[k] - col), 0.0f, 1.0f);
+                    const float4 hv = *(const float4*)(hp + k * kGatPitch);
+                    s[0] = fmaf(wt, hv.x, s[0]);
+                    s[1] = fmaf(wt, hv.y, s[1]);
+                    s[2] = fmaf(wt, hv.z, s[2]);
+                    s[3] = fmaf(wt, hv.w, s[3]);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[r] += (double)s[r];
+            }
+            // rows outside the band and columns outside [0, W) are dropped; the
+            // product is exact (qscale is a power of two), the conversion rounds
+            const int oc = g.c0 + c;
+            const size_t plane = (size_t)sq.y_off_row * a.nv + (size_t)m * a.nv * width;
+            if (oc >= 0 && oc < width) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = g.r0 + 4 * rg + r - a.v0;
+                    if (4 * rg + r < nrows && row >= 0 && row < a.nv && acc[r] != 0.0)
+                        atomicAdd(a.dq + plane + (size_t)row * width + oc,
+                                  (unsigned long long)__double2ll_rn(acc[r] * qscale));
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
 __global__ __launch_bounds__(256) void k_residual(const float* f, const float* ref, float* r, double* loss,
                                                    int64_t count, float weight) {
     __shared__ double part[4];
@@ -1123,9 +1348,13 @@ hipError_t launch_bp_adjoint(const AdjArgs& a, hipStream_t st) {
     const int64_t nblk = (int64_t)a.ntiles * ((a.nz + kAdjZR - 1) / kAdjZR);
     if (nblk <= 0 || nblk > (int64_t)1 << 31) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_adj_clear, dim3(1024), dim3(256), 0, st, a.qs, a.dq, a.ws_elems);
-    hipLaunchKernelGGL(k_adj_absmax, dim3(1024), dim3(256), 0, st, a.resid, a.nvox, a.qs);
+    const unsigned nmax = (unsigned)std::min<int64_t>(1024, (a.nvox + 4095) / 4096);
+    hipLaunchKernelGGL(k_adj_absmax, dim3(nmax), dim3(256), 0, st, a.resid, a.nvox, a.qs);
     hipLaunchKernelGGL(k_adj_scale, dim3(1), dim3(1), 0, st, a.qs, a.bound);
-    hipLaunchKernelGGL(k_bp_adjoint, dim3((unsigned)nblk), dim3(256), 0, st, a);
+    if (a.zr > 0)
+        hipLaunchKernelGGL(k_bp_adjoint_gather, dim3(8u * (unsigned)a.chunk), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL(k_bp_adjoint, dim3((unsigned)nblk), dim3(256), 0, st, a);
     hipLaunchKernelGGL(k_adj_convert, dim3(1024), dim3(256), 0, st, (const unsigned long long*)a.dq,
                        (const AdjScale*)a.qs, a.dws, a.ws_elems);
     return hipGetLastError();

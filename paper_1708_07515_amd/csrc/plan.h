@@ -78,6 +78,11 @@ inline int max_chunks(const fdkod_plan_s* pl) { return pl->nw > 2 ? kDecimMaxChu
 inline int cone_side(const fdkod_plan_s* pl) { return pl->cone ? (pl->n + (1 << pl->s) - 1) >> pl->s : 0; }
 // a backprojection variant exists and its LDS footprint holds the plan's
 bool variant_holds(const fdkod_plan_s* pl, const BpVariant& v);
+// detector columns and rows that an edge x edge (x, y) tile times `slices`
+// slices within |z| <= zmax covers at any angle, plus slack, rounded up, plus
+// margin samples
+void bp_need(int n, double r, int edge, int slices, double zmax, int cone_side, double slack, int margin, int* need_c,
+             int* need_r);
 // the first key of a z run that holds the plan's geometry
 bool first_variant(const fdkod_plan_s* pl, int zrun, BpVariant* out);
 // the kernel shape of one plan (or a batch's: groups = false) for a z run;
