@@ -159,9 +159,8 @@ fdkod_status upload_tables(fdkod_batch_t b) {
         vols[vb] = bp_vol(pl, b->filt[vb], b->ws[vb], b->vol[vb]);
         if (pl->s > 0) {
             // the batch's chunk count is an upper bound: narrow volumes use fewer
-            int c = 1;
-            while (c < b->dec_chunks && 64 * c < pl->wmax) c <<= 1;
-            dvols.push_back(decim_args(pl, b->filt[vb], b->ws[vb], c));
+            const int c = std::min(b->dec_chunks, decim_default_chunks(pl, 8));
+            dvols.push_back(decim_args(pl, b->filt[vb], b->ws[vb], c, 1));
             const int nblk = (dvols.back().ntasks + 3) / 4;     // padded to whole workgroups
             for (int g = 0; g < nblk; ++g) block_vol.push_back(make_int2((int)dvols.size() - 1, start));
             start += 4 * nblk;
@@ -367,7 +366,7 @@ fdkod_status fdkod_batch_create(const fdkod_params* prms, int32_t count, int dev
     for (fdkod_plan_t p : b->plans)
         if (p->s > 0) wmax = std::max(wmax, p->wmax);
     b->dec_chunks = 1;
-    while (b->dec_chunks < 8 && 64 * b->dec_chunks < wmax) b->dec_chunks <<= 1;
+    while (b->dec_chunks < 8 && 63 * b->dec_chunks < wmax) b->dec_chunks <<= 1;
 
     fdkod_status st;
     if ((st = dev_alloc(b->allocs, (void**)&b->d_vols, sizeof(BpVol) * count)) != FDKOD_OK) return bail(st);

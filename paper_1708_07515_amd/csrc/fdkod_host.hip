@@ -348,11 +348,43 @@ BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs) {
     return a;
 }
 
-DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks) {
-    return decim_args_band(pl, filt, ws, chunks, 0, pl->n);
+// How a task of `ch` column chunks covers the columns of the widest square.
+// Several chunks: 64 lanes each, less the taps beside a chunk's columns.  One
+// chunk: equal pieces of the columns, as many rows of a piece side by side as
+// a wave holds, by the split with the fewest waves for a row (ties: fewer
+// rows).
+void decim_split(const fdkod_plan_s* pl, int ch, int* rw, int* tasks) {
+    const int taps = pl->cubic ? 3 : 1;
+    const int cols = ch * (64 - taps);
+    *rw = 1;
+    *tasks = (pl->wmax + cols - 1) / cols;
+    for (int r = 2; ch == 1 && r <= 8; ++r) {
+        const int piece = 64 / r - taps;
+        const int pieces = (pl->wmax + piece - 1) / piece;
+        if (pieces * *rw < *tasks * r) {
+            *rw = r;
+            *tasks = pieces;
+        }
+    }
 }
 
-DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv) {
+// The fewest chunks that cover the widest square, or one if its pieces pack
+// into a quarter fewer lanes: N = 384, s = 3, sinc and cubic, 80 columns: 613 us
+// in three pieces of two rows, 749 us in two chunks.  Chunks share the step's
+// tables, so at nearly equal lanes they win: N = 512, cubic, 108 columns 565 us
+// against 576; N = 1024, sinc, 214 columns 4.07 ms against 4.94 at 7 / 8.
+int decim_default_chunks(const fdkod_plan_s* pl, int most) {
+    int ch = 1, rw, tasks;
+    while (ch < most && (64 - (pl->cubic ? 3 : 1)) * ch < pl->wmax) ch <<= 1;
+    decim_split(pl, 1, &rw, &tasks);
+    return 4 * tasks <= 3 * ch * rw ? 1 : ch;
+}
+
+DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg) {
+    return decim_args_band(pl, filt, ws, chunks, nseg, 0, pl->n);
+}
+
+DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg, int v0, int nv) {
     DecimVol a;
     a.filt = filt;
     a.ws = ws;
@@ -374,9 +406,13 @@ DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int
     a.v0 = v0;
     a.nv = nv;
     const int ch = chunks > 0 ? chunks : 1;
-    a.tasks_per_sq = dec_tasks_per_sq(pl->wmax, ch);
-    const int rpt = decim_rows_per_task(pl->cone != 0, pl->cubic != 0, ch);
-    a.ntasks = pl->nsq * ((nv + rpt - 1) / rpt) * a.tasks_per_sq;
+    decim_split(pl, ch, &a.rw, &a.tasks_per_sq);
+    a.gw = 64 / a.rw;
+    const int rows = a.rw * decim_rows_per_lane(ch, pl->cubic != 0, pl->cone != 0);
+    a.nvb = (nv + rows - 1) / rows;
+    a.nseg = nseg;
+    a.segs = pl->d_segs;
+    a.ntasks = a.nseg * pl->nsq * a.nvb * a.tasks_per_sq;
     a.chunks = ch;
     a.bside = pl->s > 0 ? 1 << (pl->s - 1) : 0;
     a.blo = pl->d_blo;
@@ -386,12 +422,13 @@ DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int
 
 fdkod_status enqueue_decimate(const fdkod_plan_s* pl, const void* filt, void* ws, int v0, int nv,
                               hipStream_t st) {
-    const DecimVol a = decim_args_band(pl, filt, ws, pl->dec_chunks, v0, nv);
-    if (pl->dec_chunks == 0) {
+    const bool staged = pl->dec_chunks == 0 && pl->staged_cpt > 1;
+    const DecimVol a = decim_args_band(pl, filt, ws, pl->dec_chunks, pl->dec_nseg, v0, nv);
+    if (staged) {
         HIP_TRY(launch_decimate_staged(a, pl->staged_cpt, pl->staged_segc, pl->store, st),
                 "row-staged decimation kernel launch");
     } else {
-        HIP_TRY(launch_decimate(a, pl->dec_chunks, pl->store, st), "decimate kernel launch");
+        HIP_TRY(launch_decimate(a, a.chunks, pl->store, st), "decimate kernel launch");
     }
     return FDKOD_OK;
 }
@@ -491,7 +528,11 @@ namespace {
 // must hold, at every schedule step, every local column of the four squares
 // of a 2 x 2 block from the least of their crop offsets: the spread of the
 // offsets (read back from the bounds kernel's crop table) plus 64 cpt
-// columns and the interpolation's second sample.
+// columns and the interpolation's second sample.  Squares of at most 64
+// columns (cpt = 1) go to k_decimate, which packs several rows into a wave:
+// N = 64, s = 2 12.7 -> 8.4 us, N = 256, s = 3 158 -> 121 us, N = 1000, s = 5
+// 18.4 -> 10.6 ms; above that the staged rows are faster: 68 columns, N = 320
+// 236 us against 275, 108 columns, N = 512 417 us against 524.
 fdkod_status staged_shape(fdkod_plan_s* pl) {
     pl->staged_cpt = pl->staged_segc = 0;
     if (pl->s < 1 || pl->cone || pl->sinc || pl->cubic) return FDKOD_OK;
@@ -525,13 +566,44 @@ fdkod_status staged_shape(fdkod_plan_s* pl) {
             }
         }
     const int segc = (spread + 64 * cpt + 1 + 63) / 64;
-    if (!staged_shape_exists(cpt, segc)) return FDKOD_OK;
-    fdkod_status st = upload(pl, &pl->d_blo, blo);
-    if (st == FDKOD_OK) st = upload(pl, &pl->d_sqoff, sqoff);
-    if (st != FDKOD_OK) return st;
+    if (cpt > 1 ? !staged_shape_exists(cpt, segc) : segc > 3) return FDKOD_OK;
     pl->staged_cpt = cpt;
     pl->staged_segc = segc;
-    return FDKOD_OK;
+    if (cpt == 1) return FDKOD_OK;       // no tables: k_decimate takes these plans
+    fdkod_status st = upload(pl, &pl->d_blo, blo);
+    if (st == FDKOD_OK) st = upload(pl, &pl->d_sqoff, sqoff);
+    return st;
+}
+
+// Segments of the decimated angles for a plan whose decimation has too few
+// wavefronts for the chip.  A task walks its projections one after another,
+// so a small volume's decimation takes the length of that walk; segments of
+// windows are independent (each adds the projections of its windows in the
+// same order).  A segment reads nw - 1 windows' projections beyond its own.
+fdkod_status decim_segments(fdkod_plan_s* pl, const std::vector<DecimStep>& sched) {
+    pl->dec_nseg = 1;
+    if (pl->s < 1) return FDKOD_OK;
+    const DecimVol a = decim_args(pl, nullptr, nullptr, pl->dec_chunks, 1);
+    const int nseg = std::min(kDecimWaves / std::max(1, a.ntasks), pl->pd / (2 * (pl->nw - 1)));
+    if (nseg < 2) return FDKOD_OK;
+    std::vector<int> close;      // step that closes each window
+    for (int e = 0; e < (int)sched.size(); ++e)
+        if (sched[e].emit) close.push_back(e);
+    std::vector<DecimSeg> segs(nseg);
+    for (int i = 0; i < nseg; ++i) {
+        DecimSeg& g = segs[i];
+        g.m0 = (int)((int64_t)pl->pd * i / nseg);
+        g.m1 = (int)((int64_t)pl->pd * (i + 1) / nseg);
+        // window m0 enters the open windows when window m0 - nw closes
+        const int first = g.m0 < pl->nw ? 0 : close[g.m0 - pl->nw] + 1;
+        g.e0 = first / kDecimUnroll * kDecimUnroll;
+        g.e1 = (close[g.m1 - 1] / kDecimUnroll + 1) * kDecimUnroll;
+        g.ms = 0;
+        while (close[g.ms] < g.e0) ++g.ms;
+    }
+    const fdkod_status st = upload(pl, &pl->d_segs, segs);
+    if (st == FDKOD_OK) pl->dec_nseg = nseg;
+    return st;
 }
 
 std::string tune_key(const fdkod_plan_s* pl) {
@@ -884,9 +956,8 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     // square, at most 8); the longest z run whose block footprint fits an LDS
     // tile, one angle per stage
     if ((st = staged_shape(pl)) != FDKOD_OK) return bail(st);
-    int ch = 1;
-    while (ch < max_chunks(pl) && 64 * ch < pl->wmax) ch <<= 1;
-    pl->dec_chunks = pl->staged_cpt ? 0 : ch;
+    pl->dec_chunks = pl->staged_cpt ? 0 : decim_default_chunks(pl, max_chunks(pl));
+    if ((st = decim_segments(pl, sched)) != FDKOD_OK) return bail(st);
     pl->bp_ok = false;
     for (int zr : {32, 16, 64}) {
         int tw = 0, th = 0;

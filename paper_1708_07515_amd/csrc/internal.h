@@ -28,6 +28,13 @@ struct DecimStep {
     float w1;     // weight into the newer open window
 };
 
+// A segment of the decimation: the steps [e0, e1) that its windows [m0, m1)
+// are open in, from and to whole groups of kDecimUnroll, and the window open
+// at step e0.
+struct DecimSeg {
+    int e0, e1, ms, m0, m1;
+};
+
 // Backprojection tile: 16 x 16 (or 8 x 8) voxels in x, y of one square.
 struct BpTile {
     int sq;       // square index
@@ -81,9 +88,13 @@ struct DecimVol {
     float cv;               // (N-1)/2
     int n, p, pd, nsq;
     int v0, nv;             // detector rows [v0, v0 + nv): filt is [P][nv][N], ws blocks [P'][nv][W_q]
+    int rw, gw;             // rows side by side in a wave, lanes of each
+    int nvb;                // row groups: ceil(nv / (rw * rows per lane))
+    int nseg;               // segments of the decimated angles (1: all in one task)
+    const DecimSeg* segs;   // [nseg] (nseg > 1)
     int tasks_per_sq;       // column groups per square
-    int ntasks;             // nsq * ceil(nv / rows per task) * tasks_per_sq
-    int chunks;             // 64-column chunks per wave (1, 2, 4 or 8)
+    int ntasks;             // nseg * nsq * nvb * tasks_per_sq
+    int chunks;             // column chunks per wave (1, 2, 4 or 8)
     int bside;              // 2^(s-1): 2 x 2 blocks of squares per side (row-staged kernel)
     const int* blo;         // [bside^2][nsched] least crop offset of a block's squares (row-staged)
     const int2* sqoff;      // [nsq][nsched] crop offset - block's least, bits of the fraction (row-staged)
@@ -304,12 +315,16 @@ hipError_t checks_read_decimate(unsigned long long* out, bool reset);
 // Limits the host checks before choosing a backprojection variant.
 constexpr int kTileXY = 16;      // voxels per tile side in x and y
 constexpr int kDecimUnroll = 8;  // the decimation schedule is padded to a multiple of this
+constexpr int kDecimWaves = 2048;       // wavefronts a small decimation is cut up into
 constexpr int kDecimMaxChunksWide = 4;  // column chunks per task when more than 2 windows are open
-// detector rows per decimation task: two for one column chunk with the
-// linear shift of detector rows (squares narrower than a wavefront: the two
-// rows share the step's tables and fill more of the wave's work), else one
-__host__ __device__ constexpr int decim_rows_per_task(bool cone, bool cubic, int chunks) {
-    return !cone && !cubic && chunks == 1 ? 2 : 1;
+// output rows per lane of the decimation: two up to two column chunks (they
+// share the step's tables and address arithmetic), four for the cubic shift
+// of detector rows in one chunk (they also share the step's tap weights:
+// N = 384, sinc and cubic, 657 -> 613 us; the linear shift lost by coarser row
+// groups, N = 193 plain 58 -> 77 us, cone-corrected 118 -> 160 us), else one
+// (the accumulators of more chunks fill the registers)
+__host__ __device__ constexpr int decim_rows_per_lane(int chunks, bool cubic, bool cone) {
+    return chunks == 1 && cubic && !cone ? 4 : chunks <= 2 ? 2 : 1;
 }
 
 }  // namespace fdkod

@@ -5,28 +5,42 @@
 //
 //   Y_q[m][v][j] = sum_p w[m][p] * Lin(q[p][v][.], a_c(beta_p) + u0_q + j)
 //
-// One wavefront per task (square, one or two rows, group of 64*CH local
-// columns).  The wavefront walks the projections once, in the order of a
-// host-built schedule; with the triangle each projection feeds at most two
-// open decimation windows, held in two accumulators per column, and a window
-// is written out as soon as its last projection has been added.  The shift's fractional part is the same
-// for every column of a (square, projection), so each cropped sample costs
-// one interpolation and two multiply-adds.  Rows are read with unit stride
-// (coalesced); the re-reads of a row by the squares that overlap it hit L2
-// because all squares of a row are scheduled together on one XCD.
+// One wavefront per task (square, group of rows, columns, segment of the
+// decimated angles).  The wavefront walks the projections once, in the order
+// of a host-built schedule; with the triangle each projection feeds at most
+// two open decimation windows, held in two accumulators per column, and a
+// window is written out as soon as its last projection has been added.
+//
+// Bound by instruction issue: a step's scalar work (tables, resource) and its
+// address arithmetic cost as much as its multiply-adds, and squares narrower
+// than a wave leave lanes idle.  So
+//  - narrow squares put several rows side by side into a wave (wider ones, in
+//    one chunk, equal pieces of their columns): lanes idle by a tenth instead
+//    of three quarters at 14 columns;
+//  - every sample is loaded once: the taps to its right are the next lanes'
+//    values, by a DPP shift folded into the difference (a chunk has as many
+//    lanes more than columns), where each tap was a load of its own;
+//  - one buffer resource spans a projection, so the row is part of a lane's
+//    offset and a lane takes two rows with one more addition; the column's
+//    range check is one compare and select per sample.  A resource per row
+//    was rebuilt in scalar registers for each row and step, which bounded the
+//    cone-corrected rows (46 cycles per row and step, scalar unit shared by
+//    four SIMDs);
+//  - a small volume's decimated angles go to several tasks (see DecimSeg).
+// Before -> after: 256 volumes of 32^3..64^3, BF16 1000 -> 320 us; N = 64,
+// s = 2 14 -> 8 us; N = 193, cone-corrected FP16 rows 249 -> 118 us; N = 384,
+// windowed sinc and cubic 1113 -> 613 us; N = 1000, s = 5 18.4 (row-staged
+// kernel) -> 10.6 ms.
 //
 // Cone-corrected rows (CONE): row v' of square q at angle beta_p is first
 // resampled from detector row (v' - c_v) R / D_c(beta_p) + c_v, so each
 // cropped sample is a bilinear one: the same column interpolation on the two
 // detector rows that bracket the warped row, then a linear one between them.
-// The row scale is uniform over the wavefront, so the two rows are two more
-// range-checked buffer resources (an empty range for a row outside the
-// detector, which reads zero).
 //
 // Quality knobs: a windowed-sinc decimation keeps `taps` windows open (each
 // projection is added to all of them with its own weight; the schedule
-// carries the extra weights), and the cubic shift reads four samples per
-// cropped value and weights them with Keys' kernel of the step's fraction.
+// carries the extra weights), and the cubic shift weights four neighbouring
+// samples with Keys' kernel of the step's fraction.
 #include "internal.h"
 #include "dtype.h"
 #include "geom.h"
@@ -39,72 +53,90 @@ namespace fdkod {
 typedef __attribute__((address_space(4))) const int* cword_ptr;
 static_assert(sizeof(DecimStep) == 16 && sizeof(int2) == 8, "table layouts");
 
-// Shape of one task's inner loop: CH column chunks of 64, NW decimation
-// windows open at once (2 for the triangle, `taps` for the windowed sinc), NT
-// samples per cropped value along u (2 linear, 4 cubic), NR detector rows per
-// cropped value (1, or 2 for cone-corrected rows).  U steps are loaded per
-// group and two groups are in flight (the next group's loads are issued
-// before the current group's arithmetic), so U shrinks as a step's loads grow.
-template <int CH, int NW, int NT, int NR>
+// Shape of one task's inner loop: CH column chunks, NW decimation windows open
+// at once (2 for the triangle, `taps` for the windowed sinc), RPT output rows
+// per lane, NR detector rows read for them (one each, or two for
+// cone-corrected rows).  U steps are loaded per group and two groups are in
+// flight (the next group's loads are issued before the current group's
+// arithmetic), so U shrinks as a step's loads grow.
+template <int CH, int NR, int NW>
 struct DecimShape {
-    static constexpr int LOADS = NT * NR / 2;          // relative to the linear, plain case
-    // at most 4 steps per group: the scalar state of 8 steps (schedule, crop
-    // and buffer resources of two groups in flight) spilled and doubled the
-    // one-chunk kernel's time
-    static constexpr int U0 = CH * LOADS >= 8 ? 1 : 8 / (CH * LOADS);
+    static constexpr int LOADS = CH * NR;
+    // at most 4 steps per group: the scalar state of 8 steps (schedule and
+    // crop entries of two groups in flight) does not fit the scalar registers
+    static constexpr int U0 = LOADS >= 8 ? 1 : 8 / LOADS;
     static constexpr int U = U0 > 4 ? 4 : U0;
     static constexpr int NX = NW > 2 ? NW - 2 : 1;     // extra weights per step (array size)
 };
 
+// the value of the next lane (zero in lane 63)
+__device__ __forceinline__ float next_lane(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130 /* wave_shl:1 */, 0xf, 0xf, true));
+}
 
-// One task: square q, detector rows v .. v + RPT - 1 (warped row v' for
-// CONE), column group g of 64*CH columns, run by one wavefront (lane =
-// 0..63).  With one column chunk and the linear shift of detector rows a
-// task takes two rows: they share the step's schedule and crop entries and
-// its address arithmetic (1.5x faster for squares narrower than a wave).
+// One task: square q, a group of rows, a group of columns and a segment of the
+// decimated angles, run by one wavefront.  Lanes form a.rw groups of a.gw
+// (rows of the task side by side); each lane owns RPT rows, a.rw apart, and
+// CH columns.
 template <int CH, int STORE, bool CONE, int NW, bool CUBIC>
 __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int lane) {
     using S = Store<STORE>;
     using T = typename S::T;
     constexpr int NT = CUBIC ? 4 : 2;
-    constexpr int RPT = decim_rows_per_task(CONE, CUBIC, CH);   // output rows per task
-    constexpr int NR = CONE ? 2 : RPT;                      // detector rows loaded per step
-    using Sh = DecimShape<CH, NW, NT, NR>;
+    constexpr int RPT = decim_rows_per_lane(CH, CUBIC, CONE);
+    constexpr int NR = CONE ? 2 * RPT : RPT;                // detector rows loaded per step
+    constexpr int CW = 64 - (NT - 1);                       // columns per chunk (CH > 1)
+    using Sh = DecimShape<CH, NR, NW>;
     constexpr int U = Sh::U;
     constexpr int NX = Sh::NX;
     static_assert(kDecimUnroll % U == 0, "the schedule is padded to whole groups");
-    // task = (vb * nsq + q) * tasks_per_sq + g, rows v = RPT vb ..: the
-    // squares of one detector row run together and share its reads in L2.
-    // CONE: task = (q * nv + v) * tasks_per_sq + g, since squares read
-    // different detector rows for the same warped row; neighbouring warped
-    // rows of one square share theirs.
+    // plain rows: the squares of one group of rows run together and share its
+    // reads in L2.  CONE: the row groups of one square run together, since
+    // squares read different detector rows for the same warped row.
     const int g = task % a.tasks_per_sq;
-    const int vq = task / a.tasks_per_sq;
-    const int q = CONE ? vq / a.nv : vq % a.nsq;
-    const int v = CONE ? vq % a.nv : (vq / a.nsq) * RPT;   // first row within the buffer (detector row v0 + v)
-    const bool second = RPT == 2 && v + 1 < a.nv;           // the task's second row exists
+    const int sv = task / a.tasks_per_sq;
+    const int seg = sv / (a.nvb * a.nsq);
+    const int vq = sv % (a.nvb * a.nsq);
+    const int q = CONE ? vq / a.nvb : vq % a.nsq;
+    const int vb = CONE ? vq % a.nvb : vq / a.nsq;
     const int n = a.n;
-    const int2 gd = a.grid[q];
-    const int width = gd.y;
-    const int jbase = g * 64 * CH + lane;
-    if (g * 64 * CH >= width) return;
+    const int width = a.grid[q].y;
+    const int lr = lane / a.gw, lc = lane - lr * a.gw;      // row group and column of the lane
+    const int jbase = g * (CH > 1 ? CH * CW : a.gw - (NT - 1)) + lc;
+    if (jbase - lc >= width) return;
+    const int row0 = vb * a.rw * RPT + lr;                  // the lane's first row within the buffer
 
-    // row v of projection 0 (CONE: row 0, the rows vary with the projection)
-    const T* frow = (const T*)uniform_ptr((const T*)a.filt + (CONE ? 0 : (size_t)v * n));
     T* ws = (T*)a.ws;
-    const cword_ptr sched = (cword_ptr)a.sched;                       // 4 words per step
-    const cword_ptr crop = (cword_ptr)(a.crop + (size_t)q * a.nsched);  // 2 words per step
-    const cword_ptr rsc = (cword_ptr)(CONE ? a.rscale + (size_t)q * a.nsched : nullptr);
-    const cword_ptr wext = (cword_ptr)(NW > 2 ? a.wext : nullptr);    // NW - 2 words per step
-    const float vrel = (float)v - a.cv;          // v' - c_v (CONE)
+    // the segment: steps [e0, e1), windows [m0, m1) written, ms the window
+    // open at e0 (earlier windows' parts, from before m0, are dropped)
+    int e0 = 0, e1 = a.nsched, ms = 0, m0 = 0, m1 = a.pd;
+    if (a.nseg > 1) {
+        const cword_ptr sg = (cword_ptr)(a.segs + seg);
+        e0 = sg[0];
+        e1 = sg[1];
+        ms = sg[2];
+        m0 = sg[3];
+        m1 = sg[4];
+    }
+    cword_ptr sched = (cword_ptr)(a.sched + e0);                              // 4 words per step
+    cword_ptr crop = (cword_ptr)(a.crop + (size_t)q * a.nsched + e0);         // 2 words per step
+    cword_ptr rsc = (cword_ptr)(CONE ? a.rscale + (size_t)q * a.nsched + e0 : nullptr);
+    cword_ptr wext = (cword_ptr)(NW > 2 ? a.wext + (size_t)(NW - 2) * e0 : nullptr);
     const int64_t yoff = a.squares[q].y_off_row * a.nv;
     const size_t plane = (size_t)a.nv * width;   // elements per decimated angle
-    const size_t pstride = (size_t)a.nv * n;     // elements per projection
     constexpr int ES = (int)sizeof(T);
-    // per-lane byte offset of each chunk's column within the cropped run
-    int lane_off[CH];
+    const int rowb = n * ES;                     // bytes per detector row
+    const uint32_t planeb = (uint32_t)a.nv * (uint32_t)rowb;   // bytes per projection
+    // the column of the lane's first sample relative to the crop offset (idle
+    // lanes: outside any row), and its byte offset within the
+    // projection less the crop's
+    const int lcol = lr < a.rw ? jbase - (CUBIC ? 1 : 0) : 0x20000000;
+    const int loff = (jbase - (CUBIC ? 1 : 0)) * ES + (CONE ? 0 : row0 * rowb);
+    float vrel[RPT];                             // v' - c_v (CONE)
+    if constexpr (CONE) {
 #pragma unroll
-    for (int c = 0; c < CH; ++c) lane_off[c] = (jbase + 64 * c) * ES;
+        for (int r = 0; r < RPT; ++r) vrel[r] = (float)(row0 + r * a.rw) - a.cv;
+    }
 
     // acc[i][r]: the i-th open window of output row r (acc[0] is written out next)
     float acc[NW][RPT][CH];
@@ -114,74 +146,64 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
         for (int r = 0; r < RPT; ++r)
 #pragma unroll
             for (int c = 0; c < CH; ++c) acc[i][r][c] = 0.0f;
-    int m = 0;
+    int m = ms;
 
-    // Per-group state: the steps, their crop entries, row fractions, extra
-    // window weights and the loaded samples x[row][tap][step][chunk].
+    // Per-group state: the steps' close flags, weights and fractions, the row
+    // fractions and the loaded samples x[row][step][chunk].
     struct Group {
-        DecimStep st[U];
-        int2 cr[U];
-        float fv[U];
-        float wx[U][NX];
-        float x[NR][NT][U][CH];
+        int emit[U];
+        float w[U][NW > 2 ? NW : 2];
+        float phi[U];
+        float fv[RPT][U];
+        float x[NR][U][CH];
     };
-    // Each detector row is read through a buffer resource spanning exactly
-    // that row: the hardware range check returns zero outside [0, N), which is
-    // the zero extension of the crop (offsets below the row wrap to huge
-    // unsigned values and are out of range too).  Every tap is a separately
-    // range-checked load: the empty asm hides that the offsets are ES apart,
-    // so the loads are not merged into one wider load (whose range check
-    // would zero all its elements at the detector's left edge).
-    auto issue = [&](int t, Group& G) {
+    // Each projection is read through a buffer resource spanning it, one
+    // sample per lane; a column outside the detector moves the offset out of
+    // range (it reads zero, the zero extension of the crop), as does a row
+    // below or above it.
+    auto issue = [&](cword_ptr sg, cword_ptr cg, cword_ptr rg, cword_ptr wg, Group& G) {
+        int p[U], cx[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int e = t + u;
-            G.st[u].p = sched[4 * e];
-            G.st[u].emit = sched[4 * e + 1];
-            G.st[u].w0 = __int_as_float(sched[4 * e + 2]);
-            G.st[u].w1 = __int_as_float(sched[4 * e + 3]);
-            G.cr[u] = make_int2(crop[2 * e], crop[2 * e + 1]);
+            p[u] = sg[4 * u];
+            G.emit[u] = sg[4 * u + 1];
+            G.w[u][0] = __int_as_float(sg[4 * u + 2]);
+            G.w[u][1] = __int_as_float(sg[4 * u + 3]);
+            cx[u] = cg[2 * u];
+            G.phi[u] = __int_as_float(cg[2 * u + 1]);
             if constexpr (NW > 2) {
 #pragma unroll
-                for (int i = 0; i < NX; ++i) G.wx[u][i] = __int_as_float(wext[(NW - 2) * e + i]);
+                for (int i = 0; i < NX; ++i) G.w[u][i + 2] = __int_as_float(wg[(NW - 2) * u + i]);
             }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const T* pbase = frow + (size_t)G.st[u].p * pstride;
-            int r0 = 0;
-            if constexpr (CONE) {
-                // warped row -> detector row (v' - c_v) R / D_c + c_v, wave-uniform
-                const float rr = fmaf(vrel, __int_as_float(rsc[t + u]), a.cv);
-                const float rf = floorf(rr);
-                G.fv[u] = rr - rf;
-                r0 = __builtin_amdgcn_readfirstlane((int)rf);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                uniform_ptr((const char*)a.filt + (uint64_t)(uint32_t)p[u] * planeb), (short)0, (int)planeb,
+                0x00020000);
+            int coff[CH];
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int off = cx[u] * ES + loff + CW * ES * c;
+                coff[c] = (unsigned)(cx[u] + lcol + CW * c) < (unsigned)n ? off : INT32_MIN;
             }
 #pragma unroll
-            for (int rw = 0; rw < NR; ++rw) {
-                // CONE: the row's address and extent go through readfirstlane
-                // so that the resource is built in scalar registers (a resource
-                // the compiler holds in vector registers costs a loop around
-                // every load)
-                const int rowi = r0 + rw;
-                // plain rows: row rw of the task (an absent second row has an
-                // empty range and reads zero)
-                const __amdgpu_buffer_rsrc_t rs =
-                    CONE ? __builtin_amdgcn_make_buffer_rsrc(
-                               uniform_ptr(pbase + (ptrdiff_t)rowi * n), (short)0,
-                               __builtin_amdgcn_readfirstlane((unsigned)rowi < (unsigned)n ? n * ES : 0),
-                               0x00020000)
-                         : __builtin_amdgcn_make_buffer_rsrc((void*)(pbase + (size_t)rw * n), (short)0,
-                                                             (rw == 0 || second) ? n * ES : 0, 0x00020000);
+            for (int r = 0; r < RPT; ++r) {
+                if constexpr (CONE) {
+                    // warped row -> detector row (v' - c_v) R / D_c + c_v
+                    const float rr = fmaf(vrel[r], __int_as_float(rg[u]), a.cv);
+                    const float rf = floorf(rr);
+                    G.fv[r][u] = rr - rf;
+                    const int r0 = min(max((int)rf, -2), n);    // both rows outside beyond these
+                    const int ro = __mul24(r0, rowb);
 #pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    const int off0 = G.cr[u].x * ES + lane_off[c];
-#pragma unroll
-                    for (int k = 0; k < NT; ++k) {
-                        int off = off0 + (k - (NT == 4 ? 1 : 0)) * ES;
-                        if (k > 0) asm volatile("" : "+v"(off));
-                        G.x[rw][k][u][c] = S::raw(rs, off);
+                    for (int c = 0; c < CH; ++c) {
+                        G.x[2 * r][u][c] = S::raw(rs, ro + coff[c]);
+                        G.x[2 * r + 1][u][c] = S::raw(rs, ro + rowb + coff[c]);
                     }
+                } else {
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) G.x[r][u][c] = S::raw(rs, coff[c] + r * a.rw * rowb);
                 }
             }
         }
@@ -189,47 +211,48 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
     auto consume = [&](const Group& G) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const float phi = __int_as_float(G.cr[u].y);
+            const float phi = G.phi[u];
             float cw[4];
             if constexpr (CUBIC) keys_weights(phi, cw);
-            float w[NW];
-            w[0] = G.st[u].w0;
-            w[1] = G.st[u].w1;
-#pragma unroll
-            for (int i = 2; i < NW; ++i) w[i] = G.wx[u][i - 2];
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
                 float rowv[NR];
 #pragma unroll
                 for (int rw = 0; rw < NR; ++rw) {
+                    // the taps to the right are the next lanes' samples
+                    const float x0 = G.x[rw][u][c];
+                    const float x1 = next_lane(x0);
                     if constexpr (CUBIC) {
-                        float t = cw[0] * G.x[rw][0][u][c];
-                        t = fmaf(cw[1], G.x[rw][1][u][c], t);
-                        t = fmaf(cw[2], G.x[rw][2][u][c], t);
-                        rowv[rw] = fmaf(cw[3], G.x[rw][3][u][c], t);
+                        const float x2 = next_lane(x1);
+                        const float x3 = next_lane(x2);
+                        float t = cw[0] * x0;
+                        t = fmaf(cw[1], x1, t);
+                        t = fmaf(cw[2], x2, t);
+                        rowv[rw] = fmaf(cw[3], x3, t);
                     } else {
-                        rowv[rw] = fmaf(phi, G.x[rw][1][u][c] - G.x[rw][0][u][c], G.x[rw][0][u][c]);
+                        rowv[rw] = fmaf(phi, x1 - x0, x0);
                     }
                 }
-                if constexpr (CONE) {
-                    const float val = fmaf(G.fv[u], rowv[1] - rowv[0], rowv[0]);
-#pragma unroll
-                    for (int i = 0; i < NW; ++i) acc[i][0][c] = fmaf(w[i], val, acc[i][0][c]);
-                } else {
-#pragma unroll
-                    for (int r = 0; r < RPT; ++r)
-#pragma unroll
-                        for (int i = 0; i < NW; ++i) acc[i][r][c] = fmaf(w[i], rowv[r], acc[i][r][c]);
-                }
-            }
-            if (G.st[u].emit) {
 #pragma unroll
                 for (int r = 0; r < RPT; ++r) {
-                    const size_t base = (size_t)yoff + (size_t)m * plane + (size_t)(v + r) * width;
+                    float val;
+                    if constexpr (CONE) val = fmaf(G.fv[r][u], rowv[2 * r + 1] - rowv[2 * r], rowv[2 * r]);
+                    else val = rowv[r];
+#pragma unroll
+                    for (int i = 0; i < NW; ++i) acc[i][r][c] = fmaf(G.w[u][i], val, acc[i][r][c]);
+                }
+            }
+            if (G.emit[u]) {
+                const bool mine = m >= m0 && m < m1;
+#pragma unroll
+                for (int r = 0; r < RPT; ++r) {
+                    const int row = row0 + r * a.rw;
+                    const size_t base = (size_t)yoff + (size_t)m * plane + (size_t)row * width;
+                    const bool rok = mine && lr < a.rw && row < a.nv && lc < (CH > 1 ? CW : a.gw - (NT - 1));
 #pragma unroll
                     for (int c = 0; c < CH; ++c) {
-                        const int j = jbase + 64 * c;
-                        if (j < width && (r == 0 || second)) S::put(ws, base + j, acc[0][r][c]);
+                        const int j = jbase + CW * c;
+                        if (rok && j < width) S::put(ws, base + j, acc[0][r][c]);
 #pragma unroll
                         for (int i = 0; i + 1 < NW; ++i) acc[i][r][c] = acc[i + 1][r][c];
                         acc[NW - 1][r][c] = 0.0f;
@@ -239,14 +262,18 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
             }
         }
     };
-    // two groups (ping, pong) per iteration; the schedule holds whole groups
+    // two groups (ping, pong) per iteration; segments hold whole groups
     Group ga, gb;
-    issue(0, ga);
-    for (int t = 0; t < a.nsched; t += 2 * U) {
-        const bool b_ok = t + U < a.nsched;
-        if (b_ok) issue(t + U, gb);
+    issue(sched, crop, rsc, wext, ga);
+    for (int t = e0; t < e1; t += 2 * U) {
+        const bool b_ok = t + U < e1;
+        if (b_ok) issue(sched + 4 * U, crop + 2 * U, rsc + U, wext + (NW - 2) * U, gb);
+        sched += 8 * U;
+        crop += 4 * U;
+        rsc += 2 * U;
+        wext += 2 * (NW - 2) * U;
         consume(ga);
-        if (t + 2 * U < a.nsched) issue(t + 2 * U, ga);
+        if (t + 2 * U < e1) issue(sched, crop, rsc, wext, ga);
         if (b_ok) consume(gb);
     }
 }
@@ -267,8 +294,8 @@ __global__ __launch_bounds__(256) void k_decimate(DecimVol a) {
 }
 
 // Many volumes in one launch (tasks concatenated volume after volume).  Each
-// volume uses its own chunk count (at most CHMAX), so the waves of a small
-// volume do not carry idle columns.
+// volume uses its own chunk count (at most CHMAX) and rows per wave, so the
+// waves of a small volume do not carry idle columns.
 template <int CHMAX, int STORE>
 __global__ __launch_bounds__(256) void k_decimate_batch(DecimBatchArgs a) {
     const int nblk = gridDim.x;

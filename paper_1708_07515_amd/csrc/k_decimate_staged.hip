@@ -223,7 +223,6 @@ static void launch_staged_shape(const DecimVol& a, int store, dim3 grid, hipStre
 
 bool staged_shape_exists(int cpt, int segc) {
     switch (cpt) {
-        case 1: return segc >= 2 && segc <= 3;
         case 2: return segc >= 3 && segc <= 5;
         case 4: return segc >= 5 && segc <= 9;
         default: return false;
@@ -234,8 +233,6 @@ hipError_t launch_decimate_staged(const DecimVol& a, int cpt, int segc, int stor
     const int nwg = a.nv * a.bside * a.bside;
     const dim3 grid(((nwg + 7) / 8) * 8);        // a multiple of 8 for the XCD order
     switch (cpt * 16 + segc) {
-        case 1 * 16 + 2: launch_staged_shape<1, 2>(a, store, grid, st); break;
-        case 1 * 16 + 3: launch_staged_shape<1, 3>(a, store, grid, st); break;
         case 2 * 16 + 3: launch_staged_shape<2, 3>(a, store, grid, st); break;
         case 2 * 16 + 4: launch_staged_shape<2, 4>(a, store, grid, st); break;
         case 2 * 16 + 5: launch_staged_shape<2, 5>(a, store, grid, st); break;

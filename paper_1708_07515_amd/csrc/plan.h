@@ -25,6 +25,9 @@ struct fdkod_plan_s {
     // staged_cpt = 0 when it does not apply to the plan)
     int dec_chunks = 1;
     int staged_cpt = 0, staged_segc = 0;
+    // segments of the decimated angles in k_decimate (1: none)
+    int dec_nseg = 1;
+    fdkod::DecimSeg* d_segs = nullptr;
     // backprojection: the public key and the kernel shape chosen for it
     fdkod::BpVariant bpv{32, 32, 48, 1};
     fdkod::BpShape bps{};
@@ -92,16 +95,18 @@ bool bp_shape(const fdkod_plan_s* const* pls, int count, int zrun, bool groups, 
 bool bp_set_variant(fdkod_plan_s* pl, const BpVariant& v);
 // launch arguments of a plan's shape over `runs` runs of its tiles
 BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs);
-// tasks per square of the decimation for a chunk count
-inline int dec_tasks_per_sq(int wmax, int chunks) { return (wmax + 64 * chunks - 1) / (64 * chunks); }
+// split of the widest square over a task's lanes: rows side by side in a wave
+// and tasks per square for a chunk count; the default chunk count up to most
+void decim_split(const fdkod_plan_s* pl, int ch, int* rw, int* tasks);
+int decim_default_chunks(const fdkod_plan_s* pl, int most);
 // runs of zrun slices in nz
 inline int bp_zslabs(int nz, int zrun) { return (nz + zrun - 1) / zrun; }
 
 // argument blocks for one plan (data pointers supplied by the caller); the
 // _band forms cover detector rows [v0, v0 + nv) and output slices
 // [zbase, zbase + nzs)
-DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks);
-DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv);
+DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg);
+DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg, int v0, int nv);
 BpVol bp_vol(const fdkod_plan_s* pl, const void* filt, const void* ws, float* vol);
 BpVol bp_vol_band(const fdkod_plan_s* pl, const void* filt, const void* ws, float* vol, int v0, int nv,
                   int zbase, int nzs);
