@@ -20,6 +20,16 @@
 // apart.  The inverse transform is conj(FFT(conj(.))); 1/M is folded into G.
 // For M = 4096 (N = 1025..2048) a four-step form with one row pair per
 // wavefront replaces the Stockham stages (k_filter4096 below).
+//
+// Bound by vector issue and, for short rows, by the chain of memory latencies
+// (samples, tables, twiddles).  N <= M / 2, so only the lower half of the
+// positions is read, weighted, staged and written: the registers of the upper
+// half cost M = 2048 its fourth wave per SIMD (N = 1024, BF16, 720 projections
+// 4.13 -> 3.58 ms).  Rows that share a wave are read and written through one
+// buffer range per workgroup, without masks, and up to M = 256 the tables of
+// the products are requested with the samples: N = 32 9.0 -> 6.6 us, N = 64
+// 10.2 -> 7.6 us, N = 256 90 -> 79 us, 170 volumes of 48^3 and 64^3 217 ->
+// 195 us.
 #include "internal.h"
 #include "dtype.h"
 
@@ -230,6 +240,9 @@ __device__ __forceinline__ void filter_block(const FilterArgs& a, int block) {
     float2* z = buf + grp * MP;
     const int n = a.n;
     const float rr = a.r * a.r;
+    // the workgroup's rows: from that of its first pair on, at most two each
+    const int rb = min((block * PAIRS) / hp * a.nv + 2 * ((block * PAIRS) % hp), a.rows);
+    const int wrows = min(2 * PAIRS, a.rows - rb);
 
     // the pre-weighted rows p~ go to LDS; the first stage of the forward
     // transform reads their first difference d[u] = p~[u] - p~[u-1]
@@ -245,9 +258,11 @@ __device__ __forceinline__ void filter_block(const FilterArgs& a, int block) {
         return a.r * __builtin_amdgcn_rsqf(rb + au * au);
     };
     // every sample of the thread is requested before any is used: both
-    // rows, all positions
-    constexpr int IT = (M + TP - 1) / TP;
-    float q0[IT], q1[IT];
+    // rows, the lower half of the positions (N <= M / 2: the upper half holds
+    // no sample, the first stage does not read it, and no output lies there;
+    // held in registers, it cost M = 2048 its fourth wave per SIMD)
+    constexpr int IT = M / TP, IH = IT / 2;
+    float q0[IH], q1[IH];
     if constexpr (TP >= 64) {
         // one row pair per wave or more waves per pair: the rows are wave-
         // uniform, so they are read through buffer resources (32-bit offsets,
@@ -262,45 +277,71 @@ __device__ __forceinline__ void filter_block(const FilterArgs& a, int block) {
             (void*)(a.proj + (size_t)u1r * n), (short)0, __builtin_amdgcn_readfirstlane(has1 ? n * 4 : 0),
             0x00020000);
 #pragma unroll
-        for (int i = 0; i < IT; ++i) {
+        for (int i = 0; i < IH; ++i) {
             const int off = (t + i * TP) * 4;
             q0[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs0, off, 0, 0));
             q1[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs1, off, 0, 0));
         }
     } else {
+        // several pairs per wave: one resource spans the workgroup's rows, a
+        // lane's row is part of its offset and its samples are constant
+        // offsets apart.  Nothing is masked: past its row a lane reads the
+        // next one's samples, which the pre-weight replaces by zero; an absent
+        // row's offset is out of range.
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            uniform_ptr(a.proj + (size_t)rb * n), (short)0, wrows * n * 4, 0x00020000);
+        const int o0 = has0 ? ((r0 - rb) * n + t) * 4 : INT32_MIN;
+        const int o1 = has1 ? ((r1 - rb) * n + t) * 4 : INT32_MIN;
+#pragma unroll
+        for (int i = 0; i < IH; ++i) {
+            q0[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o0 + i * TP * 4, 0, 0));
+            q1[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, o1 + i * TP * 4, 0, 0));
+        }
+    }
+    // the tables of the products and of the last term: short rows request
+    // them here, behind the samples, instead of one memory latency each where
+    // they are used (from M = 512 on the registers do not hold them: spills)
+    float2 gr[IT];
+    float gtl[IH];
+    auto load_resp = [&]() {
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
-            const int u = t + i * TP;
-            const bool in = u < n;
-            q0[i] = (in && has0) ? p0[u] : 0.0f;
-            q1[i] = (in && has1) ? p1[u] : 0.0f;
+            const int k = t + i * TP;
+            gr[i] = k < M ? a.resp[k] : make_float2(0.0f, 0.0f);
         }
+    };
+    auto load_tail = [&]() {
+#pragma unroll
+        for (int i = 0; i < IH; ++i) {
+            const int u = t + i * TP;
+            if constexpr (TP >= 64) {
+                gtl[i] = u < n ? a.gtail[u] : 0.0f;          // g[u - N]
+            } else {
+                const __amdgpu_buffer_rsrc_t rg =
+                    __builtin_amdgcn_make_buffer_rsrc((void*)a.gtail, (short)0, n * 4, 0x00020000);
+                gtl[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rg, u * 4, 0, 0));
+            }
+        }
+    };
+    constexpr bool kEarly = LOGM <= 8;
+    if constexpr (kEarly) {
+        load_resp();
+        load_tail();
     }
     // pre-weighted rows p~[u] (zero from N on); the difference at u = N is
     // applied after the FFT
 #pragma unroll
-    for (int i = 0; i < IT; ++i) {
+    for (int i = 0; i < IH; ++i) {
         const int u = t + i * TP;
-        if (u < M) {
-            float d0 = 0.0f, d1 = 0.0f;
-            if (u < n) {
-                d0 = q0[i] * weight(u, rb0);
-                d1 = q1[i] * weight(u, rb1);
-            }
-            z[pidx(u)] = make_float2(d0, d1);
-        }
+        const float d0 = q0[i] * weight(u, rb0), d1 = q1[i] * weight(u, rb1);
+        z[pidx(u)] = u < n ? make_float2(d0, d1) : make_float2(0.0f, 0.0f);
     }
     const float last0 = has0 ? p0[n - 1] * weight(n - 1, rb0) : 0.0f;
     const float last1 = has1 ? p1[n - 1] * weight(n - 1, rb1) : 0.0f;
     transform_sync<TP>();
     fft_lds<LOGM, TP, true, false>(z, t, a.twiddle, n);
     // tables (L2-resident) are requested in one batch before their first use
-    float2 gr[IT];
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-        const int k = t + i * TP;
-        gr[i] = k < M ? a.resp[k] : make_float2(0.0f, 0.0f);
-    }
+    if constexpr (!kEarly) load_resp();
 #pragma unroll
     for (int i = 0; i < IT; ++i) {
         const int k = t + i * TP;
@@ -311,12 +352,7 @@ __device__ __forceinline__ void filter_block(const FilterArgs& a, int block) {
     }
     transform_sync<TP>();
     fft_lds<LOGM, TP, false, true>(z, t, a.twiddle, n);
-    float gtl[IT];
-#pragma unroll
-    for (int i = 0; i < IT; ++i) {
-        const int u = t + i * TP;
-        gtl[i] = u < n ? a.gtail[u] : 0.0f;          // g[u - N]
-    }
+    if constexpr (!kEarly) load_tail();
     typename S::T* out = (typename S::T*)a.out;
     if constexpr (TP >= 64) {
         // output rows through buffer resources likewise (an absent row's
@@ -331,7 +367,7 @@ __device__ __forceinline__ void filter_block(const FilterArgs& a, int block) {
             (void*)(out + (size_t)u1r * n), (short)0, __builtin_amdgcn_readfirstlane(has1 ? n * ES : 0),
             0x00020000);
 #pragma unroll
-        for (int i = 0; i < IT; ++i) {
+        for (int i = 0; i < IH; ++i) {
             const int u = t + i * TP;
             if (u < n) {
                 const float2 v = z[pidx(u)];          // conj of the result
@@ -340,13 +376,18 @@ __device__ __forceinline__ void filter_block(const FilterArgs& a, int block) {
             }
         }
     } else {
+        constexpr int ES = (int)sizeof(typename S::T);
+        const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+            uniform_ptr(out + (size_t)rb * n), (short)0, wrows * n * ES, 0x00020000);
+        const int o0 = has0 ? ((r0 - rb) * n + t) * ES : INT32_MIN;
+        const int o1 = has1 ? ((r1 - rb) * n + t) * ES : INT32_MIN;
 #pragma unroll
-        for (int i = 0; i < IT; ++i) {
+        for (int i = 0; i < IH; ++i) {
             const int u = t + i * TP;
             if (u < n) {
                 const float2 v = z[pidx(u)];          // conj of the result
-                if (has0) S::put(out, (size_t)r0 * n + u, v.x - last0 * gtl[i]);
-                if (has1) S::put(out, (size_t)r1 * n + u, -v.y - last1 * gtl[i]);
+                S::put_raw(ro, o0 + i * TP * ES, v.x - last0 * gtl[i]);
+                S::put_raw(ro, o1 + i * TP * ES, -v.y - last1 * gtl[i]);
             }
         }
     }
