@@ -198,7 +198,7 @@ typedef struct {
     int32_t z_run;            /* slices per backprojection thread, at most: 16, 32 or 64 */
     int32_t tile_w, tile_h;   /* footprint of a 16 x 16 x z_run block: 32/64 x 48/64/96 */
     int32_t angles_per_stage; /* 1, 2 or 4 */
-    int32_t decim_chunks;     /* 64-column chunks per decimation wavefront: 1, 2, 4 or 8 */
+    int32_t decim_chunks;     /* column chunks of a wave per decimation task: 1, 2, 4 or 8; 0: the plain form's default */
     float bp_ms;              /* backprojection time measured by fdkod_tune (else 0) */
     float decim_ms;           /* decimation time measured by fdkod_tune (else 0) */
 } fdkod_tuning;

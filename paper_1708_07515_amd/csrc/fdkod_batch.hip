@@ -3,7 +3,7 @@
 // launch, the filters as one launch per FFT length (volumes that fill the GPU
 // alone keep their own), the decimation as one grouped launch and the
 // backprojection as one persistent launch that takes (volume, square, tile,
-// slab) items from a ticket queue, largest first.
+// run of slice pairs) items from a ticket queue, largest first.
 // The launch sequence is capture-safe and can be replayed as a hipGraph.
 #include <algorithm>
 #include <cstring>

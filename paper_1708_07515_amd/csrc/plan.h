@@ -20,9 +20,10 @@ struct fdkod_plan_s {
     std::vector<fdkod::SquareDesc> sq;
     std::vector<int2> grid;
     int wmax = 0;
-    // decomposition kernel shape: 64-column chunks per wavefront of k_decimate,
-    // or 0 for the row-staged kernel (whose shape is staged_cpt, staged_segc;
-    // staged_cpt = 0 when it does not apply to the plan)
+    // decomposition kernel shape: column chunks per wavefront of k_decimate, or
+    // 0 for the plain form's default: the row-staged kernel (whose shape is
+    // staged_cpt, staged_segc; staged_cpt = 0 when it does not apply to the
+    // plan), or k_decimate with one chunk where staged_cpt = 1
     int dec_chunks = 1;
     int staged_cpt = 0, staged_segc = 0;
     // segments of the decimated angles in k_decimate (1: none)
