@@ -315,16 +315,21 @@ hipError_t checks_read_decimate(unsigned long long* out, bool reset);
 // Limits the host checks before choosing a backprojection variant.
 constexpr int kTileXY = 16;      // voxels per tile side in x and y
 constexpr int kDecimUnroll = 8;  // the decimation schedule is padded to a multiple of this
-constexpr int kDecimWaves = 2048;       // wavefronts a small decimation is cut up into
+// wavefronts a small decimation is cut up into (two per SIMD): N = 64, s = 2
+// 14.8 us uncut, 8.4 cut; N = 96, s = 2, 768 waves 20.6 / 10.7; N = 128, s = 3,
+// 2048 waves and uncut either way, 27 us
+constexpr int kDecimWaves = 2048;
 constexpr int kDecimMaxChunksWide = 4;  // column chunks per task when more than 2 windows are open
 // output rows per lane of the decimation: two up to two column chunks (they
 // share the step's tables and address arithmetic), four for the cubic shift
 // of detector rows in one chunk (they also share the step's tap weights:
 // N = 384, sinc and cubic, 657 -> 613 us; the linear shift lost by coarser row
-// groups, N = 193 plain 58 -> 77 us, cone-corrected 118 -> 160 us), else one
-// (the accumulators of more chunks fill the registers)
+// groups, N = 193 plain 58 -> 77 us, cone-corrected 118 -> 160 us), two for
+// four chunks of cone-corrected rows (N = 2000, s = 4 108 -> 94 ms; one detector
+// row per step was 97), else one (the accumulators of more chunks fill the
+// registers)
 __host__ __device__ constexpr int decim_rows_per_lane(int chunks, bool cubic, bool cone) {
-    return chunks == 1 && cubic && !cone ? 4 : chunks <= 2 ? 2 : 1;
+    return chunks == 1 && cubic && !cone ? 4 : chunks <= 2 || (chunks == 4 && cone) ? 2 : 1;
 }
 
 }  // namespace fdkod
