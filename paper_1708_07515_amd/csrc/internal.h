@@ -315,10 +315,12 @@ hipError_t checks_read_decimate(unsigned long long* out, bool reset);
 // Limits the host checks before choosing a backprojection variant.
 constexpr int kTileXY = 16;      // voxels per tile side in x and y
 constexpr int kDecimUnroll = 8;  // the decimation schedule is padded to a multiple of this
-// wavefronts a small decimation is cut up into (two per SIMD): N = 64, s = 2
-// 14.8 us uncut, 8.4 cut; N = 96, s = 2, 768 waves 20.6 / 10.7; N = 128, s = 3,
-// 2048 waves and uncut either way, 27 us
-constexpr int kDecimWaves = 2048;
+// wavefronts a small decimation is cut up into (four per SIMD): N = 64, s = 2
+// 14.8 us uncut, 8.7 cut; N = 96, s = 2, 768 waves 20.6 / 11.9; N = 128, s = 3,
+// 2048 waves 27.0 / 21.6; N = 256, s = 2, FP16, 2048 waves 115 / 69; N = 512,
+// s = 1, 2048 waves of eight chunks 285 / 251; from 4800 waves (N = 193, s = 3)
+// on nothing is left to gain
+constexpr int kDecimWaves = 4096;
 constexpr int kDecimMaxChunksWide = 4;  // column chunks per task when more than 2 windows are open
 // output rows per lane of the decimation: two up to two column chunks (they
 // share the step's tables and address arithmetic), four for the cubic shift
