@@ -99,9 +99,13 @@ StreamLayout stream_layout(const fdkod_plan_s* pl, int nzs) {
 fdkod_status launch_slab(const fdkod_plan_s* pl, const void* filt, const void* ws, int v0, int nv, int z0,
                          int nzs, float* vol, hipStream_t st) {
     // lower slices of the slab, and the lower slices whose images lie in it,
-    // two runs to a workgroup.  A slab that starts at a multiple of the z run
-    // takes the whole volume's runs (its bits); any other starts its own, so
-    // that no slice outside it is computed for their sake.
+    // two runs to a workgroup (of either kind: a slab about the mid-plane has
+    // one of each: 32 slices, N = 500, s = 3 160 us in two workgroups, 122 in
+    // one), but one up to a wave per SIMD (N = 200, s = 3, 32 slices 62.4 us in
+    // 256 workgroups, 48.8 in 512; N = 100, s = 0, 38.9 us in 507, 53.9 in
+    // 845).  A slab that starts at a multiple of the z run takes the whole
+    // volume's runs (its bits); any other starts its own, so that no slice
+    // outside it is computed for their sake.
     const int zp = pl->bps.zp, mid = (pl->nz - 1) / 2;      // last lower slice
     const int unit = z0 % pl->bpv.zrun == 0 ? zp : 1;
     int low0 = 0, low1 = 0, up0 = 0, up1 = 0;
@@ -113,13 +117,15 @@ fdkod_status launch_slab(const fdkod_plan_s* pl, const void* filt, const void* w
         up0 = (pl->nz - z0 - nzs) / unit * unit;
         up1 = pl->nz - std::max(z0, mid + 1);
     }
-    const int nlow = bp_zslabs(low1 - low0, 2 * zp), nup = bp_zslabs(up1 - up0, 2 * zp);
-    BpArgs a = bp_args(pl, bp_vol_band(pl, filt, ws, vol, v0, nv, z0, nzs), nlow + nup);
+    const int nlow = bp_zslabs(low1 - low0, zp), nruns = nlow + bp_zslabs(up1 - up0, zp);
+    const int64_t waves = (int64_t)(pl->bps.bx == 8 ? pl->ntiles8 : 4 * pl->ntiles) * pl->bps.ag * ((nruns + 1) / 2);
+    const int per = waves <= 1024 ? 1 : 2;
+    BpArgs a = bp_args(pl, bp_vol_band(pl, filt, ws, vol, v0, nv, z0, nzs), bp_zslabs(nruns, per));
     a.low0 = low0;
-    a.low1 = low1;
-    a.nlow = nlow;
     a.up0 = up0;
-    a.up1 = up1;
+    a.nlow = nlow;
+    a.nruns = nruns;
+    a.per = per;
     HIP_TRY(launch_backproject_slab(a, pl->bps, pl->store, st), "backprojection kernel launch");
     return FDKOD_OK;
 }

@@ -152,11 +152,11 @@ struct BpArgs {
     BpVol v;
     const BpTile* tiles;
     int ntiles;             // xy tiles
-    int nzt;                // runs of slice pairs (slab: of slices)
+    int nzt;                // runs of slice pairs (slab: groups of runs)
     int nlogical;           // ntiles * nzt
     int chunk;              // logical WGs per XCD
-    int low0, low1, nlow;   // slab: its lower slices [low0, low1) and their workgroups,
-    int up0, up1;           // the lower slices [up0, up1) whose images lie in it
+    int low0, up0;          // slab: first slices of its lower runs and of the lower runs whose images
+    int nlow, nruns, per;   // meet it; lower runs, runs in all, runs of a workgroup
 };
 
 // One work item of the batched (persistent) backprojection.

@@ -85,12 +85,16 @@ __device__ __forceinline__ float from_next_lane(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130 /* wave_shl:1 */, 0xf, 0xf, false));
 }
 
+// A run of ZP lower slices from l0 (side 0), or of their mirror images (1).
+struct BpRun {
+    int l0, side;
+};
+
 // Backprojection of one BX x BX (x, y) tile tl (BX = 16 or 8).  PAIR: the ZP
-// lower slices from l0 and their mirror images (l' = N_z - 1 - l).  Otherwise
-// (slabs): the lower (side 0) or mirrored (1) slices of the 2 ZP from l0, in
-// two runs of ZP with row indices of their own (the second only if `two`);
-// the arithmetic of a slice is the same, so a slab whose runs start where the whole volume's do gives its
-// bits.
+// lower slices from run a's first and their mirror images (l' = N_z - 1 - l).
+// Otherwise (slabs): the runs a and b, with row indices of their own (b only
+// if `two`); the arithmetic of a slice is the same, so a slab whose runs start
+// where the whole volume's do gives its bits.
 //
 // AG groups of BX BX threads share the angles (each takes a contiguous part)
 // and their sums are added in group order at the end.  Every thread of the
@@ -100,7 +104,7 @@ __device__ __forceinline__ float from_next_lane(float x) {
 // are already being loaded into registers, so global-memory latency overlaps
 // the arithmetic; two barriers per angle separate the LDS phases.
 template <int BX, int ZP, bool PAIR, int TW, int TH, int AG, int STORE>
-__device__ __forceinline__ void bp_block(const BpVol& v, int l0, int side, bool two, const BpTile& tl,
+__device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool two, const BpTile& tl,
                                          BpSmem<TW, TH> (&sms)[AG]) {
     // fused only where written: every instantiation rounds alike, and
     // D = Dc + dD rounds once
@@ -148,7 +152,7 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int l0, int side, bool 
     // the run covers ZP slices even past the volume's middle (those voxels
     // are computed and discarded), so the staged rows always hold the whole run
     // first slice of each footprint's run
-    const float z0[2] = {(float)l0 - v.cz, (float)(PAIR ? l0 : l0 + ZP) - v.cz};
+    const float z0[2] = {(float)a.l0 - v.cz, (float)(PAIR ? a.l0 : b.l0) - v.cz};
 
     const bool direct = v.row_stride_direct != 0;
     const int row_stride = direct ? v.row_stride_direct : width;
@@ -171,7 +175,7 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int l0, int side, bool 
     // stages both), and whether it is a mirrored one
     constexpr bool kSideUniform = SIDE_THR >= 64;
     const int st_t = kSideUniform ? __builtin_amdgcn_readfirstlane(tid / SIDE_THR) : tid / SIDE_THR;
-    const int mirrored = PAIR ? st_t : side;
+    const int mirrored = PAIR ? st_t : st_t ? b.side : a.side;
 
     // footprints of the block at the kFpChunk angles from m0 (a multiple of
     // kFpChunk), one lane of the first wave per angle: eq. (1) at the block's
@@ -216,23 +220,23 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int l0, int side, bool 
             }
             if (PAIR) r0[1] = r0[0];
             const float lr = v.r * lc * rdc;
-            BpAngle a;
-            a.ax = -fmaf(v.r, t.y, lr * t.x);
-            a.ay = fmaf(v.r, t.x, -(lr * t.y));
-            a.cs = t.x;
-            a.sn = t.y;
-            a.dc = dc;
-            a.kc = kq - (float)c0;
-            a.top = v.cone ? dc : v.r;
-            a.c0 = c0;
+            BpAngle an;
+            an.ax = -fmaf(v.r, t.y, lr * t.x);
+            an.ay = fmaf(v.r, t.x, -(lr * t.y));
+            an.cs = t.x;
+            an.sn = t.y;
+            an.dc = dc;
+            an.kc = kq - (float)c0;
+            an.top = v.cone ? dc : v.r;
+            an.c0 = c0;
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
-                const bool mir = PAIR ? f == 1 : side != 0;
-                a.kr[f] = v.cv - (float)r0[f];
-                a.off[f] = (((mir ? n - 1 - r0[f] : r0[f]) - v.v0) * row_stride + c0) * ES;
+                const bool mir = PAIR ? f == 1 : (f ? b.side : a.side) != 0;
+                an.kr[f] = v.cv - (float)r0[f];
+                an.off[f] = (((mir ? n - 1 - r0[f] : r0[f]) - v.v0) * row_stride + c0) * ES;
             }
-            a.nq = min((quads + NGRP - 1) / NGRP, NQ);
-            sm.ang[slot][tid] = a;
+            an.nq = min((quads + NGRP - 1) / NGRP, NQ);
+            sm.ang[slot][tid] = an;
         }
     };
     // detector samples of angle m's footprint into registers, as raw bits of
@@ -428,8 +432,9 @@ __device__ __forceinline__ void bp_block(const BpVol& v, int l0, int side, bool 
         for (int k = 0; k < ZP; ++k) {
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const bool mir = PAIR ? t == 1 : side != 0;
-                const int l = l0 + k + (PAIR ? 0 : t * ZP), lm = v.nzf - 1 - l;
+                if (!PAIR && t == 1 && !two) continue;
+                const bool mir = PAIR ? t == 1 : (t ? b.side : a.side) != 0;
+                const int l = (PAIR || t == 0 ? a.l0 : b.l0) + k, lm = v.nzf - 1 - l;
                 const int o = (mir ? lm : l) - v.zbase;
                 if ((mir ? l < lm : l <= lm) && o >= 0 && o < v.nz) out[(size_t)o * slice] = acc[t][k];
             }
@@ -447,11 +452,12 @@ __global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject
     if (lblk >= a.nlogical) return;               // before any barrier
     const int zt = lblk / a.ntiles;
     const BpTile tl = a.tiles[lblk - zt * a.ntiles];
-    bp_block<BX, ZP, true, TW, TH, AG, STORE>(a.v, zt * ZP, 0, true, tl, sm);
+    bp_block<BX, ZP, true, TW, TH, AG, STORE>(a.v, BpRun{zt * ZP, 0}, BpRun{0, 0}, true, tl, sm);
 }
 
-// A slab of slices: workgroup = tile x two runs of one side, those of the
-// lower runs that meet the slab first, then the mirrored ones'.
+// A slab of slices: workgroup = tile x two (one where there are few)
+// consecutive runs of the list of the lower runs that meet the slab and then
+// of those whose images do.
 template <int BX, int ZP, int TW, int TH, int AG, int STORE>
 __global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject_slab(BpArgs a) {
     __shared__ BpSmem<TW, TH> sm[AG];
@@ -460,9 +466,10 @@ __global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject
     if (lblk >= a.nlogical) return;               // before any barrier
     const int zt = lblk / a.ntiles;
     const BpTile tl = a.tiles[lblk - zt * a.ntiles];
-    const int side = zt >= a.nlow;
-    const int l0 = side ? a.up0 + 2 * ZP * (zt - a.nlow) : a.low0 + 2 * ZP * zt;
-    bp_block<BX, ZP, false, TW, TH, AG, STORE>(a.v, l0, side, l0 + ZP < (side ? a.up1 : a.low1), tl, sm);
+    auto run = [&](int i) { return i < a.nlow ? BpRun{a.low0 + ZP * i, 0} : BpRun{a.up0 + ZP * (i - a.nlow), 1}; };
+    const int i = zt * a.per;
+    const bool two = a.per == 2 && i + 1 < a.nruns;
+    bp_block<BX, ZP, false, TW, TH, AG, STORE>(a.v, run(i), run(two ? i + 1 : i), two, tl, sm);
 }
 
 // Persistent backprojection over the work items of many volumes.  Workgroup
@@ -491,7 +498,8 @@ __global__ __launch_bounds__(BX * BX, 4) void k_backproject_batch(BpBatchArgs a)
             // scalar registers, as the single-volume kernel's arguments are
             const BatchItem bi = uniform_load(a.items + beg + it);
             const BpVol v = uniform_load(a.vols + bi.vol);
-            bp_block<BX, ZP, true, TW, TH, 1, STORE>(v, bi.zt * ZP, 0, true, BpTile{bi.sq, bi.x0, bi.y0, 0}, sm);
+            bp_block<BX, ZP, true, TW, TH, 1, STORE>(v, BpRun{bi.zt * ZP, 0}, BpRun{0, 0}, true,
+                                                     BpTile{bi.sq, bi.x0, bi.y0, 0}, sm);
         }
     }
 }
