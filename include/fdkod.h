@@ -195,7 +195,9 @@ fdkod_status fdkod_backproject(fdkod_plan_t plan, const void* filt, float* vol,
  * angles_per_stage are part of a variant's key and have to hold the plan's
  * block footprint, but select nothing beyond it.                           */
 typedef struct {
-    int32_t z_run;            /* slices per backprojection thread, at most: 16, 32 or 64 */
+    int32_t z_run;            /* slices per backprojection thread, at most (two runs of half as many about the
+                                 mid-plane): 16, 32 or 64; 16 allows 32 where the geometry holds no run of 32.
+                                 No kernel takes more than 32: 64 selects what 32 does */
     int32_t tile_w, tile_h;   /* footprint of a 16 x 16 x z_run block: 32/64 x 48/64/96 */
     int32_t angles_per_stage; /* 1, 2 or 4 */
     int32_t decim_chunks;     /* column chunks of a wave per decimation task: 1, 2, 4 or 8; 0: the plain form's default */
@@ -209,6 +211,18 @@ fdkod_status fdkod_get_tuning(fdkod_plan_t plan, fdkod_tuning* out);
 /* Apply kernel shapes; E_UNSUPPORTED if the variant does not exist or its LDS
  * footprint cannot hold the plan's block footprint (the plan is unchanged). */
 fdkod_status fdkod_set_tuning(fdkod_plan_t plan, const fdkod_tuning* t);
+
+/* The backprojection kernel that the library takes for a plan (count 1,
+ * batch 0) or for a batch of `count` volumes, and a z run (0: the default):
+ * tile side, slice pairs per thread, columns and rows of the detector
+ * footprint staged in LDS, angle groups, and the waves per SIMD that its LDS
+ * allows (5 at most).  Host arithmetic, no device.  FDKOD_E_UNSUPPORTED when
+ * none holds the geometry. */
+typedef struct {
+    int32_t z_run, tile, pairs, columns, rows, groups, waves;
+} fdkod_shape;
+fdkod_status fdkod_backproject_shape(const fdkod_params* prms, int32_t count, int32_t batch, int32_t z_run,
+                                     fdkod_shape* out);
 
 /* Autotuner: times the backprojection for every valid z_run (fdkod_reconstruct)
  * and decimation chunking (fdkod_decompose) on the caller's buffers and

@@ -51,6 +51,10 @@ class Tuning(ctypes.Structure):
         return {k: getattr(self, k) for k, _ in self._fields_}
 
 
+class Shape(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_int32) for k in ("z_run", "tile", "pairs", "columns", "rows", "groups", "waves")]
+
+
 _VP = ctypes.c_void_p
 EXPORTS = {
     "fdkod_validate": (ctypes.c_int, [ctypes.POINTER(Params)]),
@@ -77,6 +81,8 @@ EXPORTS = {
     "fdkod_get_tuning": (ctypes.c_int, [_VP, ctypes.POINTER(Tuning)]),
     "fdkod_set_tuning": (ctypes.c_int, [_VP, ctypes.POINTER(Tuning)]),
     "fdkod_tune": (ctypes.c_int, [_VP, _VP, _VP, _VP, _VP, ctypes.POINTER(Tuning)]),
+    "fdkod_backproject_shape": (ctypes.c_int, [ctypes.POINTER(Params), ctypes.c_int32, ctypes.c_int32,
+                                               ctypes.c_int32, ctypes.POINTER(Shape)]),
     "fdkod_batch_create": (ctypes.c_int, [ctypes.POINTER(Params), ctypes.c_int32, ctypes.c_int,
                                           ctypes.POINTER(_VP)]),
     "fdkod_batch_destroy": (ctypes.c_int, [_VP]),
@@ -193,6 +199,16 @@ def choose_s(n, p, r, skip=0, nz=0, s_max=6, costs=MI355X_COSTS, **kw):
     _check(lib.fdkod_choose_s(ctypes.byref(prm), int(s_max), float(costs[0]), float(costs[1]),
                               ctypes.byref(s_out), ctypes.byref(ms)))
     return s_out.value, ms.value
+
+
+def backproject_shape(volumes, batch=False, z_run=0, **kw):
+    """The backprojection kernel chosen for a plan (a dict of its arguments) or
+    a batch (a list of them): a dict of the fields of fdkod_shape (host only)."""
+    vols = volumes if batch else [volumes]
+    arr = (Params * len(vols))(*[_params(**v, **kw) for v in vols])
+    out = Shape()
+    _check(load_library().fdkod_backproject_shape(arr, len(vols), 1 if batch else 0, int(z_run), ctypes.byref(out)))
+    return {k: getattr(out, k) for k, _ in Shape._fields_}
 
 
 def check_counts(reset=True):

@@ -343,25 +343,8 @@ fdkod_status fdkod_batch_create(const fdkod_params* prms, int32_t count, int dev
     };
     // common kernel shapes: the longest z run every volume supports, the
     // largest footprint among the volumes, chunks for the widest square
-    bool ok = false;
-    for (int zr : {32, 16}) {
-        int tw = 0, th = 0;
-        bool all = true;
-        for (fdkod_plan_t p : b->plans) {
-            int w = 0, h = 0;
-            if (!bp_tiles_for(p->n, p->nz, p->r, zr, 0, &w, &h)) {
-                all = false;
-                break;
-            }
-            tw = std::max(tw, w);
-            th = std::max(th, h);
-        }
-        if (!all) continue;
-        b->bpv = BpVariant{zr, tw, th, 1};
-        ok = holds_all(b, b->bpv);
-        if (ok) break;
-    }
-    if (!ok) return bail(fail(FDKOD_E_UNSUPPORTED, "no backprojection variant holds every volume"));
+    if (!batch_variant(b->plans.data(), count, &b->bpv))
+        return bail(fail(FDKOD_E_UNSUPPORTED, "no backprojection variant holds every volume"));
     int wmax = 0;
     for (fdkod_plan_t p : b->plans)
         if (p->s > 0) wmax = std::max(wmax, p->wmax);

@@ -273,20 +273,30 @@ bool bp_tiles_for(int n, int nz, double r, int zrun, int cone_side, int* tw, int
 // (us; 16 x 16 tiles of 16 pairs against the shape chosen): N = 64, s = 2, 256
 // waves 34.7 / 9.0; N = 96, s = 2, 864 waves 48.3 / 23.1; N = 128, s = 3, 2048
 // waves 38.2 / 23.5; at 5760 (N = 160, s = 3) the groups cost more than they
-// give (77.8 / 90.7).
+// give (77.8 / 90.7).  Footprints of more than 20 (8 x 8) or 44 columns leave
+// no room for a second workgroup of groups, which then cost more than they
+// give (N = 100, s = 0, R = 1.75 N 242 us, 192 without).
 //
-// With enough waves the cost is VALU instructions: about 12 per slice pair
-// and 58 (8 x 8 tiles: 76, the footprint's margin weighs more) per thread and
-// angle, over every lane and slice of the tiles, those outside the squares
-// and the volume included.  An 8 x 8 tile pays where squares fill 16 x 16
-// tiles badly: N = 192, s = 3 (24-voxel squares) 133 -> 112 us, N = 384, s = 4
-// 815 -> 748; 32-voxel squares (N = 256, s = 3) 217 / 303.
+// With enough waves the cost is the shape's measured time per update (its LDS
+// sets the waves that hide the staging) over every lane and slice of the
+// tiles, those outside the squares and the volume included, and in proportion
+// more while there are fewer than two waves per SIMD.  An 8 x 8 tile pays where
+// squares fill 16 x 16 tiles badly: N = 192, s = 3 (24-voxel squares) 133 ->
+// 112 us, N = 384, s = 4 815 -> 748; 32-voxel squares (N = 256, s = 3) 217 /
+// 303.
+//
+// A z run of 16 takes 16 pairs where no key of 32 slices holds the geometry.
 bool bp_shape(const fdkod_plan_s* const* pls, int count, int zrun, bool groups, BpShape* out) {
     int64_t waves8 = 0;
-    for (int i = 0; i < count; ++i) waves8 += (int64_t)pls[i]->ntiles8 * bp_zslabs((pls[i]->nz + 1) / 2, 8);
+    bool long_runs = false;
+    for (int i = 0; i < count; ++i) {
+        waves8 += (int64_t)pls[i]->ntiles8 * bp_zslabs((pls[i]->nz + 1) / 2, 8);
+        BpVariant v;
+        long_runs |= !first_variant(pls[i], 32, &v);
+    }
     auto shape = [&](int bx, int zp, int ag, BpShape* sh) {
         int need_c = 0, need_r = 0;
-        if (2 * zp > zrun) return false;
+        if (2 * zp > (long_runs ? std::max(zrun, 32) : zrun)) return false;
         for (int i = 0; i < count; ++i) {
             const fdkod_plan_s* pl = pls[i];
             int c = 0, r = 0;
@@ -303,23 +313,22 @@ bool bp_shape(const fdkod_plan_s* const* pls, int count, int zrun, bool groups, 
         int64_t most;
         int bx, zp, ag;
     };
-    const Try small[] = {{640, 8, 4, 4},  {640, 8, 8, 4},  {640, 16, 4, 4},  {640, 16, 8, 4}, {1200, 8, 8, 4},
-                         {1200, 16, 8, 4}, {4000, 16, 8, 2}};
     if (groups)
-        for (const Try& t : small)
+        for (const Try& t : {Try{640, 8, 4, 4}, Try{1200, 8, 8, 4}, Try{4000, 16, 8, 2}})
             if (waves8 <= t.most && shape(t.bx, t.zp, t.ag, out)) return true;
-    if (zrun == 64 && shape(16, 32, 1, out)) return true;
     double best = 0.0;
     bool found = false;
     for (const Try& t : {Try{0, 16, 16, 1}, Try{0, 16, 8, 1}, Try{0, 8, 8, 1}}) {
         BpShape sh;
         if (!shape(t.bx, t.zp, 1, &sh)) continue;
-        double cost = 0.0;
+        double cost = 0.0, waves = 0.0;
         for (int i = 0; i < count; ++i) {
             const fdkod_plan_s* pl = pls[i];
-            const double waves = (t.bx == 8 ? pl->ntiles8 * 1.1 : pl->ntiles * 4.0);
-            cost += waves * bp_zslabs((pl->nz + 1) / 2, t.zp) * pl->pd * (12 * t.zp + (t.bx == 8 ? 76 : 58));
+            const double w = (t.bx == 8 ? pl->ntiles8 : pl->ntiles * 4.0) * bp_zslabs((pl->nz + 1) / 2, t.zp);
+            waves += w;
+            cost += w * t.zp * pl->pd * sh.cost;
         }
+        cost *= std::max(1.0, 2048.0 / waves);
         if (!found || cost < best) {
             best = cost;
             *out = sh;
@@ -335,6 +344,73 @@ bool bp_set_variant(fdkod_plan_s* pl, const BpVariant& v) {
     pl->bpv = v;
     pl->bps = sh;
     return true;
+}
+
+bool default_variant(fdkod_plan_s* pl) {
+    for (int zr : {32, 16, 64}) {
+        int tw = 0, th = 0;
+        if (bp_tiles_for(pl->n, pl->nz, pl->r, zr, cone_side(pl), &tw, &th) &&
+            backproject_variant_exists(BpVariant{zr, tw, th, 1}) && bp_set_variant(pl, BpVariant{zr, tw, th, 1}))
+            return true;
+    }
+    return false;
+}
+
+bool batch_variant(const fdkod_plan_s* const* pls, int count, BpVariant* out) {
+    for (int zr : {32, 16}) {
+        int tw = 0, th = 0;
+        bool all = true;
+        for (int i = 0; i < count && all; ++i) {
+            int w = 0, h = 0;
+            all = bp_tiles_for(pls[i]->n, pls[i]->nz, pls[i]->r, zr, 0, &w, &h);
+            tw = std::max(tw, w);
+            th = std::max(th, h);
+        }
+        *out = BpVariant{zr, tw, th, 1};
+        for (int i = 0; i < count && all; ++i) all = variant_holds(pls[i], *out);
+        if (all) return true;
+    }
+    return false;
+}
+
+void describe(const fdkod_params& prm, fdkod_plan_s* pl) {
+    pl->prm = prm;
+    pl->n = prm.n;
+    pl->nz = prm.nz ? prm.nz : prm.n;
+    pl->p = prm.p;
+    pl->r = prm.r;
+    pl->s = prm.s;
+    pl->k = prm.skip;
+    pl->d = 1 << (prm.s - prm.skip);
+    pl->pd = (int)ceildiv(pl->p, pl->d);
+    pl->nsq = 1 << (2 * pl->s);
+    pl->store = prm.store;
+    pl->cone = prm.rows == FDKOD_ROWS_CONE && prm.s > 0;
+    pl->sinc = prm.decim == FDKOD_DECIM_SINC;
+    pl->nw = window_taps(prm);
+    pl->cubic = prm.interp == FDKOD_INTERP_CUBIC;
+    // squares (Sec. 2.1): vertex-mean centres in voxel coordinates
+    const double c = (pl->n - 1) / 2.0;
+    const auto bl = blocks(pl->n, 1 << pl->s);
+    for (auto& by : bl)
+        for (auto& bx : bl) {
+            SquareDesc d{};
+            d.x0 = bx.first; d.x1 = bx.second; d.y0 = by.first; d.y1 = by.second;
+            d.xc = (float)(0.5 * ((bx.first - c) + (bx.second - 1 - c)));
+            d.yc = (float)(0.5 * ((by.first - c) + (by.second - 1 - c)));
+            d.y_off_row = 0;
+            pl->sq.push_back(d);
+        }
+}
+
+std::vector<BpTile> make_tiles(const fdkod_plan_s* pl, int edge) {
+    std::vector<BpTile> t;
+    for (int q = 0; q < pl->nsq; ++q) {
+        const SquareDesc& d = pl->sq[q];
+        for (int y = d.y0; y < d.y1; y += edge)
+            for (int x = d.x0; x < d.x1; x += edge) t.push_back(BpTile{q, x, y, 0});
+    }
+    return t;
 }
 
 BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs) {
@@ -803,6 +879,34 @@ fdkod_status fdkod_validate(const fdkod_params* prm) {
     return FDKOD_OK;
 }
 
+fdkod_status fdkod_backproject_shape(const fdkod_params* prms, int32_t count, int32_t batch, int32_t z_run,
+                                     fdkod_shape* out) {
+    if (!prms || !out || count < 1 || count > 4096 || (!batch && count != 1)) return fail(FDKOD_E_ARG, "bad argument");
+    std::vector<fdkod_plan_s> pls(count);
+    std::vector<const fdkod_plan_s*> ptr;
+    for (int i = 0; i < count; ++i) {
+        const fdkod_status st = fdkod_validate(&prms[i]);
+        if (st != FDKOD_OK) return st;
+        describe(prms[i], &pls[i]);
+        pls[i].ntiles = (int)make_tiles(&pls[i], kTileXY).size();
+        pls[i].ntiles8 = (int)make_tiles(&pls[i], 8).size();
+        ptr.push_back(&pls[i]);
+    }
+    BpVariant key{};
+    bool ok = batch ? batch_variant(ptr.data(), count, &key) : default_variant(&pls[0]);
+    if (!batch) key = pls[0].bpv;
+    if (ok && z_run) {
+        key.zrun = z_run;
+        BpVariant v{};
+        for (int i = 0; i < count; ++i) ok = ok && first_variant(ptr[i], z_run, &v);
+    }
+    BpShape sh{};
+    if (!ok || !bp_shape(ptr.data(), count, key.zrun, !batch, &sh))
+        return fail(FDKOD_E_UNSUPPORTED, "no backprojection shape holds the geometry");
+    *out = fdkod_shape{key.zrun, sh.bx, sh.zp, sh.tw, sh.th, sh.ag, sh.waves};
+    return FDKOD_OK;
+}
+
 fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t* out) {
     if (!out) return fail(FDKOD_E_ARG, "out is NULL");
     *out = nullptr;
@@ -821,22 +925,8 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     HIP_TRY(hipSetDevice(device), "hipSetDevice");
 
     fdkod_plan_t pl = new fdkod_plan_s();
-    pl->prm = *prm;
     pl->device = device;
-    pl->n = prm->n;
-    pl->nz = prm->nz ? prm->nz : prm->n;
-    pl->p = prm->p;
-    pl->r = prm->r;
-    pl->s = prm->s;
-    pl->k = prm->skip;
-    pl->d = 1 << (prm->s - prm->skip);
-    pl->pd = (int)ceildiv(pl->p, pl->d);
-    pl->nsq = 1 << (2 * pl->s);
-    pl->store = prm->store;
-    pl->cone = prm->rows == FDKOD_ROWS_CONE && prm->s > 0;
-    pl->sinc = prm->decim == FDKOD_DECIM_SINC;
-    pl->nw = window_taps(*prm);
-    pl->cubic = prm->interp == FDKOD_INTERP_CUBIC;
+    describe(*prm, pl);
     {
         // the FFT length: the least power of two (at least 8) holding the
         // linear convolution, so N <= M / 2, which the filter kernel's pruned
@@ -852,19 +942,6 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
         (void)hipSetDevice(prev);
         return code;
     };
-
-    // squares (Sec. 2.1): vertex-mean centres in voxel coordinates
-    const double c = (pl->n - 1) / 2.0;
-    const auto bl = blocks(pl->n, 1 << pl->s);
-    for (auto& by : bl)
-        for (auto& bx : bl) {
-            SquareDesc d{};
-            d.x0 = bx.first; d.x1 = bx.second; d.y0 = by.first; d.y1 = by.second;
-            d.xc = (float)(0.5 * ((bx.first - c) + (bx.second - 1 - c)));
-            d.yc = (float)(0.5 * ((by.first - c) + (by.second - 1 - c)));
-            d.y_off_row = 0;
-            pl->sq.push_back(d);
-        }
 
     // tables
     const std::vector<float2> trig_p = trig_table(pl->p);
@@ -935,16 +1012,7 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     }
 
     // tiles of 16 x 16 voxels (also the transpose's) and of 8 x 8
-    auto make_tiles = [&](int edge) {
-        std::vector<BpTile> t;
-        for (int q = 0; q < pl->nsq; ++q) {
-            const SquareDesc& d = pl->sq[q];
-            for (int y = d.y0; y < d.y1; y += edge)
-                for (int x = d.x0; x < d.x1; x += edge) t.push_back(BpTile{q, x, y, 0});
-        }
-        return t;
-    };
-    const std::vector<BpTile> tiles = make_tiles(kTileXY), tiles8 = make_tiles(8);
+    const std::vector<BpTile> tiles = make_tiles(pl, kTileXY), tiles8 = make_tiles(pl, 8);
     pl->ntiles = (int)tiles.size();
     pl->ntiles8 = (int)tiles8.size();
     if ((int64_t)pl->ntiles * bp_zslabs(pl->nz, 16) > (int64_t)1 << 30)
@@ -960,15 +1028,7 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     if ((st = staged_shape(pl)) != FDKOD_OK) return bail(st);
     pl->dec_chunks = pl->staged_cpt ? 0 : decim_default_chunks(pl, max_chunks(pl));
     if ((st = decim_segments(pl, sched)) != FDKOD_OK) return bail(st);
-    pl->bp_ok = false;
-    for (int zr : {32, 16, 64}) {
-        int tw = 0, th = 0;
-        if (bp_tiles_for(pl->n, pl->nz, pl->r, zr, cone_side(pl), &tw, &th) &&
-            backproject_variant_exists(BpVariant{zr, tw, th, 1})) {
-            pl->bp_ok = bp_set_variant(pl, BpVariant{zr, tw, th, 1});
-            if (pl->bp_ok) break;
-        }
-    }
+    pl->bp_ok = default_variant(pl);
     {
         BpVariant cv{};
         int cc = 0;

@@ -185,9 +185,10 @@ struct BpVariant {
 };
 
 // A backprojection kernel's shape: tile side, slice pairs per thread, columns
-// and rows of its staged footprints, angle groups.
+// and rows of its staged footprints, angle groups, its measured time per
+// update on a full chip (relative), and the waves per SIMD its LDS allows.
 struct BpShape {
-    int bx, zp, tw, th, ag;
+    int bx, zp, tw, th, ag, cost, waves;
 };
 
 hipError_t launch_bounds(const BoundsArgs& a, hipStream_t st);

@@ -29,6 +29,14 @@
 // rows an angle needs are staged).  With one slice per index (10.4 per update)
 // 1.70 ms, 2000^2 x 1000 slices, s = 4: 50 ms, direct FDK at N = 256: 1.86 ms;
 // now 1.36, 41.5 and 1.41 ms (4.4e12 updates/s).
+//
+// A close source widens the footprints, and the LDS then sets the waves that
+// hide the staging; so the staged width follows the geometry in steps of eight
+// columns, and the rows end where one more workgroup fits.  Update times
+// relative to R = 4 N: 1.34 (R = 2.5 N), 1.53 (2 N), 1.77 (1.75 N), 2.7 (1.5 N);
+// with footprints of 32 or 64 columns only (one workgroup per compute unit
+// below R = 2.3 N, its loads not ahead of the arithmetic) 1.9, 5.5, 5.6 and 5.6,
+// one slice per index 2.6, 3.2, 3.2 and 4.1.
 #include "internal.h"
 #include "dtype.h"
 
@@ -71,14 +79,29 @@ struct BpAngle {
     int pad[3];
 };
 
+// LDS row pitch in quads of a footprint of tw columns: 4 or 12 mod 16, so that
+// the 16 lanes of one 4 x 4 patch of voxels (at most six columns of one or two
+// rows) read distinct groups of four banks.
+constexpr int bp_pitch(int tw) { return (tw + 3) / 8 * 8 + 4; }
+
 // LDS of one group of BX BX threads: two staged footprints (the quads of TH
-// detector rows: TH - 1 rows of TW + 4 quads) and, for two chunks of angles,
-// the per-angle constants.
+// detector rows: TH - 1 rows) and, for two chunks of angles, the per-angle
+// constants.
 template <int TW, int TH>
 struct BpSmem {
-    float4 tile[2 * (TH - 1) * (TW + 4)];
+    float4 tile[2 * (TH - 1) * bp_pitch(TW)];
     BpAngle ang[2][kFpChunk];
 };
+
+// Waves per SIMD that a shape's LDS allows, five at most (the registers of the
+// arithmetic allow no more).
+constexpr int kBpLds = 160 * 1024;
+template <int BX, int TW, int TH, int AG>
+constexpr int bp_waves() {
+    constexpr int groups = kBpLds / (int)(sizeof(BpSmem<TW, TH>) * AG);
+    constexpr int waves = groups * (BX * BX * AG / 64) / 4;
+    return waves < 1 ? 1 : waves < 5 ? waves : 5;
+}
 
 // Lane l receives lane l + 1's value (a DPP wave shift; lane 63 receives 0).
 __device__ __forceinline__ float from_next_lane(float x) {
@@ -118,10 +141,7 @@ __device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool 
     const int mbeg = grp * per, mend = min(mbeg + per, v.pd);
     using S = Store<STORE>;
     using T = typename S::T;
-    // LDS row pitch in quads: 4 mod 16, so that the 16 lanes of one 4 x 4
-    // patch of voxels (at most six columns of one or two rows) read distinct
-    // groups of four banks
-    constexpr int TWP = TW + 4;
+    constexpr int TWP = bp_pitch(TW);
     constexpr int SIDE = (TH - 1) * TWP;   // quads from a lower sample to the mirrored one
     auto& tile = sm.tile;
     const SquareDesc sq = v.squares[tl.sq];
@@ -164,13 +184,14 @@ __device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool 
     // one footprint column and nq consecutive rows (their quads), for which
     // it loads nq + 1 rows
     constexpr int SIDE_THR = NTHR / 2;
-    constexpr int NGRP = SIDE_THR / TW;
+    constexpr int SW = TW <= 16 ? 16 : TW <= 32 ? 32 : 64;   // lanes of a row (columns from TW on idle)
+    constexpr int NGRP = SIDE_THR / SW;
     static_assert((TH - 1) % NGRP == 0, "uniform staging trip count");
     constexpr int NQ = (TH - 1) / NGRP;          // at most; an angle's own count is BpAngle::nq
     constexpr int NR = NQ + 1;
     constexpr int NQMIN = NQ < 4 ? NQ : NQ / 2 + 1;  // rows staged without a branch
-    const int scol = tid % TW;
-    const int sgrp = (tid % SIDE_THR) / TW;
+    const int scol = tid % SW;
+    const int sgrp = (tid % SIDE_THR) / SW;
     // the footprint this thread stages (uniform over a wave unless one wave
     // stages both), and whether it is a mirrored one
     constexpr bool kSideUniform = SIDE_THR >= 64;
@@ -247,9 +268,9 @@ __device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool 
     // an offset beyond every plane, so its samples read zero too.  A lane's
     // samples are consecutive rows (downwards for a mirrored footprint), so
     // each costs one add.  Footprints of more than 16 samples per thread are
-    // loaded after the arithmetic instead (their registers would cost
-    // occupancy).
-    constexpr bool kPrefetch = NR <= 16;
+    // loaded after the arithmetic instead where their registers would cost
+    // occupancy (at three waves per SIMD or fewer the LDS has cost it already).
+    constexpr bool kPrefetch = NR <= (bp_waves<BX, TW, TH, AG>() <= 3 ? 32 : 16);
     const int rstep_bytes = (mirrored ? -row_stride : row_stride) * ES;
     uint32_t pre[NR];
     auto fetch = [&](int m) {
@@ -258,7 +279,7 @@ __device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool 
             uniform_ptr(data + (size_t)(mbeg + m) * plane), (short)0, (int)plane_bytes, 0x00020000);
         const int nq = __builtin_amdgcn_readfirstlane(an.nq);
         const int col = an.c0 + scol, at = an.off[st_t] + scol * ES + __mul24(sgrp, nq * rstep_bytes);
-        const int off0 = (unsigned)col < (unsigned)width ? at : (int)0x80000000;
+        const int off0 = (unsigned)col < (unsigned)width && (SW == TW || scol < TW) ? at : (int)0x80000000;
         // (each offset in its own register, never folded into the
         // instruction's constant offset: the range check must see the
         // whole offset of every sample)
@@ -294,7 +315,8 @@ __device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool 
             if (r >= NQMIN && r >= nq) break;    // uniform
             const float y1 = S::from_bits(pre[r + 1]);
             const float du1 = from_next_lane(y1) - y1;
-            dst[r * TWP] = make_float4(y0, du0, y1 - y0, du1 - du0);
+            const float4 quad = make_float4(y0, du0, y1 - y0, du1 - du0);
+            if (SW == TW || scol < TW) dst[r * TWP] = quad;
             y0 = y1;
             du0 = du1;
         }
@@ -444,7 +466,7 @@ __device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool 
 
 // Whole volume: workgroup = tile x run of slice pairs.
 template <int BX, int ZP, int TW, int TH, int AG, int STORE>
-__global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject(BpArgs a) {
+__global__ __launch_bounds__(BX * BX * AG, (bp_waves<BX, TW, TH, AG>())) void k_backproject(BpArgs a) {
     __shared__ BpSmem<TW, TH> sm[AG];
     // XCD-aware order: each XCD runs a contiguous range of logical blocks
     const int b = blockIdx.x;
@@ -459,7 +481,7 @@ __global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject
 // consecutive runs of the list of the lower runs that meet the slab and then
 // of those whose images do.
 template <int BX, int ZP, int TW, int TH, int AG, int STORE>
-__global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject_slab(BpArgs a) {
+__global__ __launch_bounds__(BX * BX * AG, (bp_waves<BX, TW, TH, AG>())) void k_backproject_slab(BpArgs a) {
     __shared__ BpSmem<TW, TH> sm[AG];
     const int b = blockIdx.x;
     const int lblk = (b & 7) * a.chunk + (b >> 3);
@@ -480,7 +502,7 @@ __global__ __launch_bounds__(BX * BX * AG, (ZP > 16 ? 4 : 5)) void k_backproject
 // all eight ranges are exhausted.  The counters must be zero at launch
 // (launch_reset_counter).
 template <int BX, int ZP, int TW, int TH, int STORE>
-__global__ __launch_bounds__(BX * BX, 4) void k_backproject_batch(BpBatchArgs a) {
+__global__ __launch_bounds__(BX * BX, (bp_waves<BX, TW, TH, 1>() < 4 ? bp_waves<BX, TW, TH, 1>() : 4)) void k_backproject_batch(BpBatchArgs a) {
     __shared__ BpSmem<TW, TH> sm[1];
     __shared__ int ticket;
     const int home = blockIdx.x & (kXcds - 1);
@@ -514,16 +536,26 @@ hipError_t launch_reset_counter(unsigned* counter, hipStream_t st) {
 }
 
 // Kernel shapes: (tile side, slice pairs per thread, footprint columns,
-// footprint rows, angle groups).  The whole-volume and slab kernels exist for
-// each, the batch kernel for those of one group.
+// footprint rows, angle groups, cost).  The whole-volume and slab kernels
+// exist for each, the batch kernel for those of one group.  The cost is the
+// time per update on a full chip (N = 333..1000, 250..1000 slices, FP32), 100
+// for the first shape.  What the narrower ones save: 36 columns against 44 at
+// R = 2.5 N 3.62 / 4.57 ms (N = 1000, s = 4, 360 projections, 500 slices), 44
+// against 52 at 2 N 4.57 / 5.31, 52 against 60 at 1.75 N 5.31 / 8.05, 60 against
+// 64 at 1.5 N 8.06 / 10.1; 45 rows against 49 (three workgroups, not two)
+// N = 333, 1000 slices, R = 3 N 1.67 / 2.28 ms; 33 rows against 49 at 52 columns
+// N = 500, s = 0, 60 slices, R = 1.75 N 1.27 / 1.41 ms; 8 x 8 tiles of 17 rows
+// against 20, N = 160, s = 3, R = 2.25 N 95 / 109 us.
 #define FDKOD_BP_SHAPES_ONE(X) \
-    X(16, 16, 32, 25, 1) X(16, 16, 32, 33, 1) X(16, 16, 32, 49, 1) X(16, 16, 64, 33, 1) X(16, 16, 64, 49, 1) \
-    X(16, 8, 32, 17, 1) X(16, 8, 32, 25, 1) X(16, 8, 32, 41, 1) X(16, 8, 64, 41, 1) X(16, 8, 64, 57, 1) \
-    X(8, 8, 16, 17, 1)
+    X(16, 16, 32, 25, 1, 100) X(16, 16, 32, 33, 1, 107) X(16, 16, 36, 35, 1, 119) X(16, 16, 32, 45, 1, 120) \
+    X(16, 16, 32, 49, 1, 164) X(16, 16, 52, 33, 1, 163) X(16, 16, 52, 49, 1, 177) X(16, 16, 64, 63, 1, 337) \
+    X(16, 8, 32, 17, 1, 110) X(16, 8, 32, 25, 1, 126) X(16, 8, 36, 23, 1, 134) X(16, 8, 44, 29, 1, 153) \
+    X(16, 8, 32, 41, 1, 172) X(16, 8, 52, 33, 1, 249) X(16, 8, 60, 43, 1, 268) X(16, 8, 64, 57, 1, 525) \
+    X(8, 8, 16, 17, 1, 150) X(8, 8, 20, 17, 1, 180) X(8, 8, 20, 20, 1, 200) X(8, 8, 28, 28, 1, 335)
 #define FDKOD_BP_SHAPES(X) FDKOD_BP_SHAPES_ONE(X) \
-    X(16, 32, 32, 49, 1) X(16, 32, 32, 65, 1) \
-    X(16, 8, 32, 17, 2) X(16, 8, 32, 17, 4) X(16, 8, 32, 25, 2) X(16, 8, 32, 25, 4) X(16, 4, 32, 17, 4) \
-    X(8, 8, 16, 17, 4) X(8, 4, 16, 13, 4)
+    X(16, 8, 32, 17, 2, 110) X(16, 8, 32, 25, 2, 126) X(16, 8, 36, 23, 2, 134) X(16, 8, 44, 29, 2, 153) \
+    X(8, 8, 16, 17, 4, 150) X(8, 8, 20, 20, 4, 200) \
+    X(8, 4, 16, 13, 4, 190) X(8, 4, 20, 13, 4, 220) X(8, 4, 28, 20, 4, 400)
 
 // Public tuning keys (z run, tile columns, tile rows, angles per stage).
 #define FDKOD_BP_VARIANTS(X)  \
@@ -547,9 +579,9 @@ bool backproject_variant_exists(const BpVariant& var) {
 
 bool backproject_shape_for(int bx, int zp, int ag, int need_c, int need_r, BpShape* out) {
     BpShape best{};
-#define FDKOD_X(B, Z, W, H, A)                                                                       \
-    if (B == bx && Z == zp && A == ag && W >= need_c && H >= need_r && (!best.zp || W * H < best.tw * best.th)) \
-        best = BpShape{B, Z, W, H, A};
+#define FDKOD_X(B, Z, W, H, A, C)                                                                    \
+    if (B == bx && Z == zp && A == ag && W >= need_c && H >= need_r && (!best.zp || C < best.cost)) \
+        best = BpShape{B, Z, W, H, A, C, bp_waves<B, W, H, A>()};
     FDKOD_BP_SHAPES(FDKOD_X)
 #undef FDKOD_X
     *out = best;
@@ -571,7 +603,7 @@ static bool same_shape(const BpShape& sh, int bx, int zp, int tw, int th, int ag
 
 hipError_t launch_backproject(const BpArgs& a, const BpShape& sh, int store, hipStream_t st) {
     const dim3 grid(8 * a.chunk);
-#define FDKOD_X(B, Z, W, H, A) \
+#define FDKOD_X(B, Z, W, H, A, C) \
     if (same_shape(sh, B, Z, W, H, A)) { FDKOD_BP_LAUNCH(k_backproject, grid, B * B * A, B, Z, W, H, A) }
     FDKOD_BP_SHAPES(FDKOD_X)
 #undef FDKOD_X
@@ -580,7 +612,7 @@ hipError_t launch_backproject(const BpArgs& a, const BpShape& sh, int store, hip
 
 hipError_t launch_backproject_slab(const BpArgs& a, const BpShape& sh, int store, hipStream_t st) {
     const dim3 grid(8 * a.chunk);
-#define FDKOD_X(B, Z, W, H, A) \
+#define FDKOD_X(B, Z, W, H, A, C) \
     if (same_shape(sh, B, Z, W, H, A)) { FDKOD_BP_LAUNCH(k_backproject_slab, grid, B * B * A, B, Z, W, H, A) }
     FDKOD_BP_SHAPES(FDKOD_X)
 #undef FDKOD_X
@@ -588,7 +620,7 @@ hipError_t launch_backproject_slab(const BpArgs& a, const BpShape& sh, int store
 }
 
 hipError_t launch_backproject_batch(const BpBatchArgs& a, const BpShape& sh, int store, int blocks, hipStream_t st) {
-#define FDKOD_X(B, Z, W, H, A) \
+#define FDKOD_X(B, Z, W, H, A, C) \
     if (same_shape(sh, B, Z, W, H, A)) { FDKOD_BP_LAUNCH(k_backproject_batch, dim3(blocks), B * B, B, Z, W, H) }
     FDKOD_BP_SHAPES_ONE(FDKOD_X)
 #undef FDKOD_X
@@ -598,7 +630,7 @@ hipError_t launch_backproject_batch(const BpBatchArgs& a, const BpShape& sh, int
 int backproject_batch_occupancy(const BpShape& sh, int store) {
     int nb = 0;
     hipError_t e = hipErrorInvalidValue;
-#define FDKOD_X(B, Z, W, H, A)                                                                     \
+#define FDKOD_X(B, Z, W, H, A, C)                                                                  \
     if (same_shape(sh, B, Z, W, H, A)) {                                                           \
         switch (store) {                                                                           \
             case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_backproject_batch<B, Z, W, H, 0>, B * B, 0); break; \

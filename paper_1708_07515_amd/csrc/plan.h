@@ -94,6 +94,15 @@ bool first_variant(const fdkod_plan_s* pl, int zrun, BpVariant* out);
 bool bp_shape(const fdkod_plan_s* const* pls, int count, int zrun, bool groups, BpShape* out);
 // set a plan's key and the shape that follows from it (false: unchanged)
 bool bp_set_variant(fdkod_plan_s* pl, const BpVariant& v);
+// the default key of a plan: the longest z run that a shape holds (false: none)
+bool default_variant(fdkod_plan_s* pl);
+// the common key of a batch's volumes: the longest z run every volume supports
+// and the largest footprint among them
+bool batch_variant(const fdkod_plan_s* const* pls, int count, BpVariant* out);
+// a plan's parameters, derived counts and squares (host, from validated params)
+void describe(const fdkod_params& prm, fdkod_plan_s* pl);
+// the squares' tiles of edge x edge voxels
+std::vector<BpTile> make_tiles(const fdkod_plan_s* pl, int edge);
 // launch arguments of a plan's shape over `runs` runs of its tiles
 BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs);
 // split of the widest square over a task's lanes: rows side by side in a wave

@@ -16,10 +16,10 @@ def _gpu():
     require_gpu()
 
 
-# n, nz, p, r, s, skip: a single slice, one pair, an odd middle, runs of 4, 8
-# and 16 pairs with a remainder, squares of 8, 9, 12 and 24 voxels, fewer
-# angles than angle groups, a close source (64-column footprints), and enough
-# waves for tiles without angle groups
+# n, nz, p, r, s, skip: a single slice, one pair, an odd middle, runs of 4 and
+# 8 pairs with a remainder, squares of 8, 9, 12 and 24 voxels, fewer angles
+# than angle groups and a close source (all small volumes, which take angle
+# groups: every shape by name is in test_gpu_backproject_shapes.py)
 CASES = [(32, 1, 48, 256.0, 1, 0), (32, 2, 45, 128.0, 2, 0), (33, 7, 3, 132.0, 0, 0), (48, 48, 67, 192.0, 2, 0),
          (72, 33, 64, 288.0, 3, 1), (64, 17, 48, 100.0, 2, 0), (96, 95, 24, 384.0, 2, 1), (64, 64, 16, 256.0, 3, 0),
          (120, 40, 24, 480.0, 0, 0), (192, 61, 20, 768.0, 3, 1)]
