@@ -39,6 +39,7 @@
 // one slice per index 2.6, 3.2, 3.2 and 4.1.
 #include "internal.h"
 #include "dtype.h"
+#include "offsets.h"
 
 namespace fdkod {
 
@@ -279,24 +280,24 @@ __device__ __forceinline__ void bp_block(const BpVol& v, BpRun a, BpRun b, bool 
             uniform_ptr(data + (size_t)(mbeg + m) * plane), (short)0, (int)plane_bytes, 0x00020000);
         const int nq = __builtin_amdgcn_readfirstlane(an.nq);
         const int col = an.c0 + scol, at = an.off[st_t] + scol * ES + __mul24(sgrp, nq * rstep_bytes);
-        const int off0 = (unsigned)col < (unsigned)width && (SW == TW || scol < TW) ? at : (int)0x80000000;
+        const uint32_t off0 = column_offset((unsigned)col < (unsigned)width && (SW == TW || scol < TW), at);
         // (each offset in its own register, never folded into the
         // instruction's constant offset: the range check must see the
         // whole offset of every sample)
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
             if (q > NQMIN && q > nq) break;      // uniform
-            int off;
+            uint32_t off;
             if (q == 0) {
                 off = off0;
                 asm volatile("" : "+v"(off));
             } else if constexpr (!kSideUniform) {
-                off = off0 + q * rstep_bytes;
+                off = moved(off0, q * rstep_bytes);
                 asm volatile("" : "+v"(off));
             } else {
                 asm volatile("v_add_u32 %0, %1, %2" : "=v"(off) : "s"(q * rstep_bytes), "v"(off0));
             }
-            pre[q] = S::raw_bits(rs, off);
+            pre[q] = S::raw_bits(rs, (int)off);
         }
     };
     // quads (Y, dU, dV, dUV) into LDS: at (r, c), Y = Y[r][c], dU = Y[r][c+1]

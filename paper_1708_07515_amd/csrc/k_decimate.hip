@@ -44,6 +44,7 @@
 #include "internal.h"
 #include "dtype.h"
 #include "geom.h"
+#include "offsets.h"
 
 namespace fdkod {
 
@@ -181,12 +182,10 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 uniform_ptr((const char*)a.filt + (uint64_t)(uint32_t)p[u] * planeb), (short)0, (int)planeb,
                 0x00020000);
-            int coff[CH];
+            uint32_t coff[CH];
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int off = cx[u] * ES + loff + CW * ES * c;
-                coff[c] = (unsigned)(cx[u] + lcol + CW * c) < (unsigned)n ? off : INT32_MIN;
-            }
+            for (int c = 0; c < CH; ++c)
+                coff[c] = column_offset((unsigned)(cx[u] + lcol + CW * c) < (unsigned)n, cx[u] * ES + loff + CW * ES * c);
 #pragma unroll
             for (int r = 0; r < RPT; ++r) {
                 if constexpr (CONE) {
@@ -198,12 +197,12 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
                     const int ro = __mul24(r0, rowb);
 #pragma unroll
                     for (int c = 0; c < CH; ++c) {
-                        G.x[2 * r][u][c] = S::raw(rs, ro + coff[c]);
-                        G.x[2 * r + 1][u][c] = S::raw(rs, ro + rowb + coff[c]);
+                        G.x[2 * r][u][c] = S::raw(rs, (int)moved(coff[c], ro));
+                        G.x[2 * r + 1][u][c] = S::raw(rs, (int)moved(coff[c], ro + rowb));
                     }
                 } else {
 #pragma unroll
-                    for (int c = 0; c < CH; ++c) G.x[r][u][c] = S::raw(rs, coff[c] + r * a.rw * rowb);
+                    for (int c = 0; c < CH; ++c) G.x[r][u][c] = S::raw(rs, (int)moved(coff[c], r * a.rw * rowb));
                 }
             }
         }
