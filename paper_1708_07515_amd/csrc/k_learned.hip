@@ -523,8 +523,9 @@ __global__ __launch_bounds__(kThreads) void k_learned_fwd_ring(LearnedArgs a) {
 //   dW1^T[tap][ch] += X^T[tap][col] x dH[col][ch]
 // All are BF16 products with FP32 accumulation.  A, W2, S and the rounded dH
 // are BF16 already; dR is FP32 and enters as the sum of three BF16 parts
-// (8 significant bits each: 24, so the parts add up to dR exactly), which
-// the row's staging splits once.  dA's three parts times five offsets fill
+// (8 significant bits each: 24, so the parts add up to dR exactly from |dR| =
+// 2^-103 on, below which the third leaves BF16's normal range), which the
+// row's staging splits once.  dA's three parts times five offsets fill
 // one K = 16 product, dW2 takes two K = 32 ones (two parts, the third), and
 // dW1 two angles in each K = 32 one: 26 matrix instructions per tile of 16
 // columns, against 45 (30 of them FP32 ones of twice the time) before.
@@ -691,13 +692,16 @@ __global__ __launch_bounds__(kThreads, 4) void k_learned_bwd(LearnedArgs a) {
         auto stage_dr = [&](int b, float g) {
             gb2 += g;
             if (col >= width) return;
-            const float g1 = g - bf2f(f2bf(g));
-            const float g2 = g1 - bf2f(f2bf(g1));
-            const float part[3] = {g, g1, g2};
+            // each part is the leading eight bits of what the ones before leave
+            // (cut off, not rounded: a value near the largest stays finite)
+            float part[3];
+            part[0] = g;
+#pragma unroll
+            for (int t = 1; t < 3; ++t) part[t] = part[t - 1] - __uint_as_float(__float_as_uint(part[t - 1]) & 0xFFFF0000u);
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
                 uint16_t* h = reinterpret_cast<uint16_t*>(sm.dr[b][t]);
-                const uint16_t val = (uint16_t)f2bf(part[t]);
+                const uint16_t val = (uint16_t)(__float_as_uint(part[t]) >> 16);
                 h[2 * (kDrPad + col)] = val;
                 h[2 * (kDrPad + col - 1) + 1] = val;
             }
