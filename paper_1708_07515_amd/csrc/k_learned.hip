@@ -538,6 +538,16 @@ __global__ __launch_bounds__(kThreads) void k_learned_fwd_ring(LearnedArgs a) {
 // the next angle's nine rows are fetched during the current one and staged
 // after it.  Without the prefetch every angle waited for its rows: 32-slice
 // slab at 2000^2, s = 4: 28.0 ms.
+//
+// Waves per SIMD: the linear shift is held to four, although the registers
+// then spill 44 (ring) or 108 bytes per lane: the fourth wave is worth more
+// (N = 300, s = 3: ring, 360 projections 2.53 ms against 2.97 without scratch
+// at three; general, 362 projections 3.47 against 3.98; N = 2000, 36 rows 3.88
+// against 4.63).  The cubic shift's rows hold four samples each, so its spills
+// were three times those of the ring and cost more than the waves gave: two
+// waves are asked for (ring 3.63 -> 3.20 ms; general 7.45 -> 4.64, and 6.55
+// before the rows were fetched ahead).
+constexpr int bwd_waves(bool cubic) { return cubic ? 2 : 4; }
 constexpr int kDrPad = 4;                           // dR row: column c at index c + 4
 constexpr int kDrLen = 16 * ((kLearnedMaxWidth + 15) / 16) + 16;
 
@@ -549,7 +559,7 @@ struct BwdSmem {
 };
 
 template <int STORE, bool CUBIC, bool RING>
-__global__ __launch_bounds__(kThreads, 4) void k_learned_bwd(LearnedArgs a) {
+__global__ __launch_bounds__(kThreads, bwd_waves(CUBIC)) void k_learned_bwd(LearnedArgs a) {
     // the task state, and after the last task the waves' partial gradients
     __shared__ union {
         BwdSmem<RING> s;
