@@ -160,7 +160,7 @@ fdkod_status upload_tables(fdkod_batch_t b) {
         if (pl->s > 0) {
             // the batch's chunk count is an upper bound: narrow volumes use fewer
             const int c = std::min(b->dec_chunks, decim_default_chunks(pl, 8));
-            dvols.push_back(decim_args(pl, b->filt[vb], b->ws[vb], c, 1));
+            dvols.push_back(decim_args(pl, b->filt[vb], b->ws[vb], c, 0, pl->n, true));
             const int nblk = (dvols.back().ntasks + 3) / 4;     // padded to whole workgroups
             for (int g = 0; g < nblk; ++g) block_vol.push_back(make_int2((int)dvols.size() - 1, start));
             start += 4 * nblk;

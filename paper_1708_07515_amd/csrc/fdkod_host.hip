@@ -456,11 +456,7 @@ int decim_default_chunks(const fdkod_plan_s* pl, int most) {
     return 4 * tasks <= 3 * ch * rw ? 1 : ch;
 }
 
-DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg) {
-    return decim_args_band(pl, filt, ws, chunks, nseg, 0, pl->n);
-}
-
-DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg, int v0, int nv) {
+DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv, bool batch) {
     DecimVol a;
     a.filt = filt;
     a.ws = ws;
@@ -486,9 +482,10 @@ DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int
     a.gw = 64 / a.rw;
     const int rows = a.rw * decim_rows_per_lane(ch, pl->cubic != 0, pl->cone != 0);
     a.nvb = (nv + rows - 1) / rows;
-    a.nseg = nseg;
+    a.ntasks = pl->nsq * a.nvb * a.tasks_per_sq;
+    a.nseg = batch ? 1 : std::max(1, std::min(kDecimWaves / std::max(1, a.ntasks), pl->dec_nseg));
     a.segs = pl->d_segs;
-    a.ntasks = a.nseg * pl->nsq * a.nvb * a.tasks_per_sq;
+    a.ntasks *= a.nseg;
     a.chunks = ch;
     a.bside = pl->s > 0 ? 1 << (pl->s - 1) : 0;
     a.blo = pl->d_blo;
@@ -499,7 +496,7 @@ DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int
 fdkod_status enqueue_decimate(const fdkod_plan_s* pl, const void* filt, void* ws, int v0, int nv,
                               hipStream_t st) {
     const bool staged = pl->dec_chunks == 0 && pl->staged_cpt > 1;
-    const DecimVol a = decim_args_band(pl, filt, ws, pl->dec_chunks, pl->dec_nseg, v0, nv);
+    const DecimVol a = decim_args(pl, filt, ws, pl->dec_chunks, v0, nv);
     if (staged) {
         HIP_TRY(launch_decimate_staged(a, pl->staged_cpt, pl->staged_segc, pl->store, st),
                 "row-staged decimation kernel launch");
@@ -651,36 +648,34 @@ fdkod_status staged_shape(fdkod_plan_s* pl) {
     return st;
 }
 
-// Segments of the decimated angles for a plan whose decimation has too few
-// wavefronts for the chip.  A task walks its projections one after another,
-// so a small volume's decimation takes the length of that walk; segments of
-// windows are independent (each adds the projections of its windows in the
-// same order).  A segment reads nw - 1 windows' projections beyond its own,
-// and keeps at least three times as many (N = 64, s = 2 from 90 projections
-// in segments of two windows: the reconstruction 26.4 us, of three 24.2).
+// Segments of the decimated angles for a decimation with too few wavefronts
+// for the chip (a small volume's, or a band of a few rows).  A task walks its
+// projections one after another, so such a call takes the length of that walk;
+// segments of windows are independent (each adds the projections of its windows
+// in the same order).  A segment reads nw - 1 windows' projections beyond its
+// own, and keeps at least three times as many (N = 64, s = 2 from 90
+// projections in segments of two windows: the reconstruction 26.4 us, of three
+// 24.2).  decim_args says how many a call takes.
 fdkod_status decim_segments(fdkod_plan_s* pl, const std::vector<DecimStep>& sched) {
     pl->dec_nseg = 1;
-    if (pl->s < 1) return FDKOD_OK;
-    const DecimVol a = decim_args(pl, nullptr, nullptr, pl->dec_chunks, 1);
-    const int nseg = std::min(kDecimWaves / std::max(1, a.ntasks), pl->pd / (3 * (pl->nw - 1)));
-    if (nseg < 2) return FDKOD_OK;
+    const int most = std::min(kDecimWaves, pl->pd / (3 * (pl->nw - 1)));
+    if (pl->s < 1 || most < 2) return FDKOD_OK;
     std::vector<int> close;      // step that closes each window
     for (int e = 0; e < (int)sched.size(); ++e)
         if (sched[e].emit) close.push_back(e);
-    std::vector<DecimSeg> segs(nseg);
-    for (int i = 0; i < nseg; ++i) {
-        DecimSeg& g = segs[i];
-        g.m0 = (int)((int64_t)pl->pd * i / nseg);
-        g.m1 = (int)((int64_t)pl->pd * (i + 1) / nseg);
-        // window m0 enters the open windows when window m0 - nw closes
-        const int first = g.m0 < pl->nw ? 0 : close[g.m0 - pl->nw] + 1;
+    std::vector<DecimSeg> segs(pl->pd);
+    int ms = 0;
+    for (int m = 0; m < pl->pd; ++m) {
+        DecimSeg& g = segs[m];
+        // window m enters the open windows when window m - nw closes
+        const int first = m < pl->nw ? 0 : close[m - pl->nw] + 1;
         g.e0 = first / kDecimUnroll * kDecimUnroll;
-        g.e1 = (close[g.m1 - 1] / kDecimUnroll + 1) * kDecimUnroll;
-        g.ms = 0;
-        while (close[g.ms] < g.e0) ++g.ms;
+        while (close[ms] < g.e0) ++ms;
+        g.ms = ms;
+        g.e1 = (close[m] / kDecimUnroll + 1) * kDecimUnroll;
     }
     const fdkod_status st = upload(pl, &pl->d_segs, segs);
-    if (st == FDKOD_OK) pl->dec_nseg = nseg;
+    if (st == FDKOD_OK) pl->dec_nseg = most;
     return st;
 }
 

@@ -28,11 +28,11 @@ struct DecimStep {
     float w1;     // weight into the newer open window
 };
 
-// A segment of the decimation: the steps [e0, e1) that its windows [m0, m1)
-// are open in, from and to whole groups of kDecimUnroll, and the window open
-// at step e0.
+// A decimated angle as the first or last of a segment: the steps from which
+// its window is open and to which, from and to whole groups of kDecimUnroll,
+// and the window that is next to close at step e0.
 struct DecimSeg {
-    int e0, e1, ms, m0, m1;
+    int e0, ms, e1;
 };
 
 // Backprojection tile: 16 x 16 (or 8 x 8) voxels in x, y of one square.
@@ -91,7 +91,7 @@ struct DecimVol {
     int rw, gw;             // rows side by side in a wave, lanes of each
     int nvb;                // row groups: ceil(nv / (rw * rows per lane))
     int nseg;               // segments of the decimated angles (1: all in one task)
-    const DecimSeg* segs;   // [nseg] (nseg > 1)
+    const DecimSeg* segs;   // [P'] (nseg > 1)
     int tasks_per_sq;       // column groups per square
     int ntasks;             // nseg * nsq * nvb * tasks_per_sq
     int chunks;             // column chunks per wave (1, 2, 4 or 8)

@@ -108,16 +108,18 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
     const int row0 = vb * a.rw * RPT + lr;                  // the lane's first row within the buffer
 
     T* ws = (T*)a.ws;
-    // the segment: steps [e0, e1), windows [m0, m1) written, ms the window
-    // open at e0 (earlier windows' parts, from before m0, are dropped)
+    // the segment: windows [m0, m1) written, of the steps [e0, e1) they are
+    // open in, ms the window open at e0 (earlier windows' parts, from before
+    // m0, are dropped)
     int e0 = 0, e1 = a.nsched, ms = 0, m0 = 0, m1 = a.pd;
     if (a.nseg > 1) {
-        const cword_ptr sg = (cword_ptr)(a.segs + seg);
-        e0 = sg[0];
-        e1 = sg[1];
-        ms = sg[2];
-        m0 = sg[3];
-        m1 = sg[4];
+        // (P' <= 32768 angles, at most kDecimWaves segments: below 2^31)
+        m0 = (int)((unsigned)(a.pd * seg) / (unsigned)a.nseg);
+        m1 = (int)((unsigned)(a.pd * (seg + 1)) / (unsigned)a.nseg);
+        const cword_ptr first = (cword_ptr)(a.segs + m0), last = (cword_ptr)(a.segs + m1 - 1);
+        e0 = first[0];
+        ms = first[1];
+        e1 = last[2];
     }
     cword_ptr sched = (cword_ptr)(a.sched + e0);                              // 4 words per step
     cword_ptr crop = (cword_ptr)(a.crop + (size_t)q * a.nsched + e0);         // 2 words per step

@@ -26,7 +26,8 @@ struct fdkod_plan_s {
     // plan), or k_decimate with one chunk where staged_cpt = 1
     int dec_chunks = 1;
     int staged_cpt = 0, staged_segc = 0;
-    // segments of the decimated angles in k_decimate (1: none)
+    // most segments of the decimated angles in k_decimate (1: none), and where
+    // one may start and end
     int dec_nseg = 1;
     fdkod::DecimSeg* d_segs = nullptr;
     // backprojection: the public key and the kernel shape chosen for it
@@ -115,8 +116,8 @@ inline int bp_zslabs(int nz, int zrun) { return (nz + zrun - 1) / zrun; }
 // argument blocks for one plan (data pointers supplied by the caller); the
 // _band forms cover detector rows [v0, v0 + nv) and output slices
 // [zbase, zbase + nzs)
-DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg);
-DecimVol decim_args_band(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int nseg, int v0, int nv);
+DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv,
+                    bool batch = false);
 BpVol bp_vol(const fdkod_plan_s* pl, const void* filt, const void* ws, float* vol);
 BpVol bp_vol_band(const fdkod_plan_s* pl, const void* filt, const void* ws, float* vol, int v0, int nv,
                   int zbase, int nzs);
