@@ -424,24 +424,71 @@ BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs) {
     return a;
 }
 
-// How a task of `ch` column chunks covers the columns of the widest square.
-// Several chunks: 64 lanes each, less the taps beside a chunk's columns.  One
-// chunk: equal pieces of the columns, as many rows of a piece side by side as
-// a wave holds, by the split with the fewest waves for a row (ties: fewer
-// rows).
-void decim_split(const fdkod_plan_s* pl, int ch, int* rw, int* tasks) {
+// How a task of `ch` column chunks covers the columns of the widest square and
+// nv detector rows.  Several chunks: 64 lanes each, less the taps beside a
+// chunk's columns.
+//
+// One chunk: equal pieces of the columns, rw rows of a piece side by side in a
+// wave, by the least (waves for a row) * per(rw).  What the lanes gain by
+// packing the loads pay again: every row of a wave is another line of memory,
+// and 64 / 3 or 64 / 5 lanes straddle lines.  per() is measured, over squares of
+// 14..60 columns, 16..1024 of them, N = 48..1024; it is lower while the rows of
+// a group of tasks stay in an XCD's L2.  N = 333, s = 4, 35 columns: one row 0.58
+// ms, two 0.60, four in three pieces 0.64, seven in five pieces 0.93; N = 900,
+// s = 5, 48 columns 4.8, 5.2, 7.6, 17.4; N = 193, s = 3, 42 columns 72, 73, 62, 180
+// us.  (By the fewest lanes alone, N = 700, s = 5, R = 2 N, 48 columns took 20.2
+// ms and N = 300, s = 3, 64 columns 408 us; in the row-staged kernel 9.0 and 209;
+// now 4.9 and 232.)
+//
+// Rows per lane of one chunk: two, which share a step's tables and addresses.
+// Four for the cubic shift, which also share its tap weights (N = 384, s = 3,
+// sinc 740 -> 679 us), and, where the tasks fill the chip all the same, in waves
+// of at most two cone-corrected rows (N = 256, s = 4 632 -> 421 us, N = 560, s = 4
+// 3.17 -> 2.98 ms; three rows and more N = 384, s = 4 1.56 / 1.37, N = 400, s = 5
+// 4.89 / 5.55 ms with five) or of one plain row while four rows of all projections
+// stay in the L2 (N = 256, s = 3, k = 1 221 -> 192 us; 11.5 MB, N = 1000, 720
+// projections, s = 5 10.5 -> 11.6 ms).  One, with arithmetic to share out (cone,
+// cubic, more than two windows), where even then all segments fit the chip: the
+// time is the length of a task's walk (N = 64, s = 2, sinc of six taps, cubic 34 us
+// with four rows, 14 with one; plain rows N = 64, s = 3 8.0 with two, 8.7).
+DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch) {
     const int taps = pl->cubic ? 3 : 1;
     const int cols = ch * (64 - taps);
-    *rw = 1;
-    *tasks = (pl->wmax + cols - 1) / cols;
-    for (int r = 2; ch == 1 && r <= 8; ++r) {
-        const int piece = 64 / r - taps;
-        const int pieces = (pl->wmax + piece - 1) / piece;
-        if (pieces * *rw < *tasks * r) {
-            *rw = r;
-            *tasks = pieces;
+    DecimSplit d{1, decim_rows_per_lane(ch, pl->cone != 0), (pl->wmax + cols - 1) / cols, 1};
+    auto ntasks = [&]() {
+        const int64_t rows = (int64_t)d.rw * d.rpt;
+        return pl->nsq * ((nv + rows - 1) / rows) * d.tasks;
+    };
+    if (ch == 1) {
+        const double row = (double)pl->p * pl->n * (pl->store == 0 ? 4 : 2);   // bytes of a detector row, all projections
+        const bool large = 8 * row > 2.5e6;
+        double best = d.tasks;
+        for (int rw : {2, 3, 4, 5, 8}) {
+            const double three = pl->cubic ? 1.47 : pl->cone ? (large ? 1.45 : 1.6) : 2.0;
+            const double per = rw == 2 ? (large ? 1.1 : 1.05) : rw == 3 ? three : rw == 4 ? (large ? 1.4 : 1.3)
+                             : rw == 5 ? (10 * row <= 1e6 && !pl->cubic ? 1.25 : 2.0) : 1.9;
+            const int piece = 64 / rw - taps, pieces = (pl->wmax + piece - 1) / piece;
+            const double cost = per * pieces / rw;
+            if (cost < best) {
+                best = cost;
+                d.rw = rw;
+                d.tasks = pieces;
+            }
         }
+        auto rows = [&](int r) {
+            d.rpt = r;
+            return ntasks();
+        };
+        if (batch) d.rpt = 2;
+        else if ((pl->nw > 2 || pl->cubic || pl->cone) && rows(1) * pl->dec_nseg <= kDecimWaves) d.rpt = 1;
+        else if (pl->cubic && !pl->cone) d.rpt = 4;
+        else d.rpt = rows(4) >= kDecimWaves && (pl->cone ? d.rw <= 2 : d.rw == 1 && 4 * row <= 6.5e6) ? 4 : 2;
     }
+    if (!batch) {
+        const int64_t want = kDecimWaves / std::max<int64_t>(1, ntasks());
+        d.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(want, pl->dec_nseg));
+    }
+    return d;
 }
 
 // The fewest chunks that cover the widest square, or one if its pieces pack
@@ -450,10 +497,10 @@ void decim_split(const fdkod_plan_s* pl, int ch, int* rw, int* tasks) {
 // tables, so at nearly equal lanes they win: N = 512, cubic, 108 columns 565 us
 // against 576; N = 1024, sinc, 214 columns 4.07 ms against 4.94 at 7 / 8.
 int decim_default_chunks(const fdkod_plan_s* pl, int most) {
-    int ch = 1, rw, tasks;
+    int ch = 1;
     while (ch < most && (64 - (pl->cubic ? 3 : 1)) * ch < pl->wmax) ch <<= 1;
-    decim_split(pl, 1, &rw, &tasks);
-    return 4 * tasks <= 3 * ch * rw ? 1 : ch;
+    const DecimSplit one = decim_split(pl, 1, pl->n, false);
+    return 4 * one.tasks <= 3 * ch * one.rw ? 1 : ch;
 }
 
 DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv, bool batch) {
@@ -478,14 +525,16 @@ DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chun
     a.v0 = v0;
     a.nv = nv;
     const int ch = chunks > 0 ? chunks : 1;
-    decim_split(pl, ch, &a.rw, &a.tasks_per_sq);
-    a.gw = 64 / a.rw;
-    const int rows = a.rw * decim_rows_per_lane(ch, pl->cubic != 0, pl->cone != 0);
-    a.nvb = (nv + rows - 1) / rows;
-    a.ntasks = pl->nsq * a.nvb * a.tasks_per_sq;
-    a.nseg = batch ? 1 : std::max(1, std::min(kDecimWaves / std::max(1, a.ntasks), pl->dec_nseg));
+    const DecimSplit d = nv == pl->n && !batch ? pl->dec_split[ch == 1 ? 0 : ch == 2 ? 1 : ch == 4 ? 2 : 3]
+                                               : decim_split(pl, ch, nv, batch);
+    a.rw = d.rw;
+    a.gw = 64 / d.rw;
+    a.rpt = d.rpt;
+    a.tasks_per_sq = d.tasks;
+    a.nvb = (nv + d.rw * d.rpt - 1) / (d.rw * d.rpt);
+    a.nseg = d.nseg;
     a.segs = pl->d_segs;
-    a.ntasks *= a.nseg;
+    a.ntasks = a.nseg * pl->nsq * a.nvb * a.tasks_per_sq;
     a.chunks = ch;
     a.bside = pl->s > 0 ? 1 << (pl->s - 1) : 0;
     a.blo = pl->d_blo;
@@ -655,7 +704,7 @@ fdkod_status staged_shape(fdkod_plan_s* pl) {
 // in the same order).  A segment reads nw - 1 windows' projections beyond its
 // own, and keeps at least three times as many (N = 64, s = 2 from 90
 // projections in segments of two windows: the reconstruction 26.4 us, of three
-// 24.2).  decim_args says how many a call takes.
+// 24.2).  decim_split says how many a call takes.
 fdkod_status decim_segments(fdkod_plan_s* pl, const std::vector<DecimStep>& sched) {
     pl->dec_nseg = 1;
     const int most = std::min(kDecimWaves, pl->pd / (3 * (pl->nw - 1)));
@@ -1021,8 +1070,9 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     // square, at most 8); the longest z run whose block footprint fits an LDS
     // tile, one angle per stage
     if ((st = staged_shape(pl)) != FDKOD_OK) return bail(st);
-    pl->dec_chunks = pl->staged_cpt ? 0 : decim_default_chunks(pl, max_chunks(pl));
     if ((st = decim_segments(pl, sched)) != FDKOD_OK) return bail(st);
+    for (int i = 0; i < 4; ++i) pl->dec_split[i] = decim_split(pl, 1 << i, pl->n, false);
+    pl->dec_chunks = pl->staged_cpt ? 0 : decim_default_chunks(pl, max_chunks(pl));
     pl->bp_ok = default_variant(pl);
     {
         BpVariant cv{};

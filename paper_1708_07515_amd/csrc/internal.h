@@ -35,6 +35,13 @@ struct DecimSeg {
     int e0, ms, e1;
 };
 
+// How the decimation's tasks cover the widest square and the rows of a call:
+// rows side by side in a wave and per lane, tasks per square and group of
+// rows, segments.
+struct DecimSplit {
+    int rw, rpt, tasks, nseg;
+};
+
 // Backprojection tile: 16 x 16 (or 8 x 8) voxels in x, y of one square.
 struct BpTile {
     int sq;       // square index
@@ -89,7 +96,8 @@ struct DecimVol {
     int n, p, pd, nsq;
     int v0, nv;             // detector rows [v0, v0 + nv): filt is [P][nv][N], ws blocks [P'][nv][W_q]
     int rw, gw;             // rows side by side in a wave, lanes of each
-    int nvb;                // row groups: ceil(nv / (rw * rows per lane))
+    int rpt;                // output rows per lane
+    int nvb;                // row groups: ceil(nv / (rw * rpt))
     int nseg;               // segments of the decimated angles (1: all in one task)
     const DecimSeg* segs;   // [P'] (nseg > 1)
     int tasks_per_sq;       // column groups per square
@@ -323,16 +331,13 @@ constexpr int kDecimUnroll = 8;  // the decimation schedule is padded to a multi
 // on nothing is left to gain
 constexpr int kDecimWaves = 4096;
 constexpr int kDecimMaxChunksWide = 4;  // column chunks per task when more than 2 windows are open
-// output rows per lane of the decimation: two up to two column chunks (they
-// share the step's tables and address arithmetic), four for the cubic shift
-// of detector rows in one chunk (they also share the step's tap weights:
-// N = 384, sinc and cubic, 657 -> 613 us; the linear shift lost by coarser row
-// groups, N = 193 plain 58 -> 77 us, cone-corrected 118 -> 160 us), two for
-// four chunks of cone-corrected rows (N = 2000, s = 4 108 -> 94 ms; one detector
-// row per step was 97), else one (the accumulators of more chunks fill the
-// registers)
-__host__ __device__ constexpr int decim_rows_per_lane(int chunks, bool cubic, bool cone) {
-    return chunks == 1 && cubic && !cone ? 4 : chunks <= 2 || (chunks == 4 && cone) ? 2 : 1;
+// output rows per lane of the decimation with several column chunks: two for
+// two of them (they share the step's tables and address arithmetic) and for
+// four of cone-corrected rows (N = 2000, s = 4 108 -> 94 ms; one detector row per
+// step was 97), else one (the accumulators of more chunks fill the registers);
+// one chunk takes 1, 2 or 4 (decim_split)
+__host__ __device__ constexpr int decim_rows_per_lane(int chunks, bool cone) {
+    return chunks == 2 || (chunks == 4 && cone) ? 2 : 1;
 }
 
 }  // namespace fdkod

@@ -79,12 +79,11 @@ __device__ __forceinline__ float next_lane(float x) {
 // decimated angles, run by one wavefront.  Lanes form a.rw groups of a.gw
 // (rows of the task side by side); each lane owns RPT rows, a.rw apart, and
 // CH columns.
-template <int CH, int STORE, bool CONE, int NW, bool CUBIC>
+template <int CH, int STORE, bool CONE, int NW, bool CUBIC, int RPT>
 __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int lane) {
     using S = Store<STORE>;
     using T = typename S::T;
     constexpr int NT = CUBIC ? 4 : 2;
-    constexpr int RPT = decim_rows_per_lane(CH, CUBIC, CONE);
     constexpr int NR = CONE ? 2 * RPT : RPT;                // detector rows loaded per step
     constexpr int CW = 64 - (NT - 1);                       // columns per chunk (CH > 1)
     using Sh = DecimShape<CH, NR, NW>;
@@ -279,7 +278,7 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
     }
 }
 
-template <int CH, int STORE, bool CONE, int NW, bool CUBIC>
+template <int CH, int STORE, bool CONE, int NW, bool CUBIC, int RPT>
 __global__ __launch_bounds__(256) void k_decimate(DecimVol a) {
     // XCD-aware order: consecutive logical blocks share an XCD (and its L2)
     const int nblk = gridDim.x;
@@ -291,7 +290,7 @@ __global__ __launch_bounds__(256) void k_decimate(DecimVol a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int task = lblk * 4 + wave;
     if (task >= a.ntasks) return;         // no barriers in this kernel
-    decimate_task<CH, STORE, CONE, NW, CUBIC>(a, task, threadIdx.x & 63);
+    decimate_task<CH, STORE, CONE, NW, CUBIC, RPT>(a, task, threadIdx.x & 63);
 }
 
 // Many volumes in one launch (tasks concatenated volume after volume).  Each
@@ -311,18 +310,31 @@ __global__ __launch_bounds__(256) void k_decimate_batch(DecimBatchArgs a) {
     const int t = task - bv.y;
     if (t >= dv.ntasks) return;                         // padding of the volume's range
     const int lane = threadIdx.x & 63;
-    if (CHMAX >= 8 && dv.chunks >= 8) decimate_task<(CHMAX >= 8 ? 8 : 1), STORE, false, 2, false>(dv, t, lane);
-    else if (CHMAX >= 4 && dv.chunks >= 4) decimate_task<(CHMAX >= 4 ? 4 : 1), STORE, false, 2, false>(dv, t, lane);
-    else if (CHMAX >= 2 && dv.chunks >= 2) decimate_task<(CHMAX >= 2 ? 2 : 1), STORE, false, 2, false>(dv, t, lane);
-    else decimate_task<1, STORE, false, 2, false>(dv, t, lane);
+    if (CHMAX >= 8 && dv.chunks >= 8) decimate_task<(CHMAX >= 8 ? 8 : 1), STORE, false, 2, false, 1>(dv, t, lane);
+    else if (CHMAX >= 4 && dv.chunks >= 4) decimate_task<(CHMAX >= 4 ? 4 : 1), STORE, false, 2, false, 1>(dv, t, lane);
+    else if (CHMAX >= 2 && dv.chunks >= 2) decimate_task<(CHMAX >= 2 ? 2 : 1), STORE, false, 2, false, 2>(dv, t, lane);
+    else decimate_task<1, STORE, false, 2, false, 2>(dv, t, lane);
+}
+
+template <int CH, bool CONE, int NW, bool CUBIC, int RPT>
+static void launch_rows(const DecimVol& a, int store, dim3 grid, hipStream_t st) {
+    switch (store) {
+        case 0: hipLaunchKernelGGL((k_decimate<CH, 0, CONE, NW, CUBIC, RPT>), grid, dim3(256), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((k_decimate<CH, 1, CONE, NW, CUBIC, RPT>), grid, dim3(256), 0, st, a); break;
+        default: hipLaunchKernelGGL((k_decimate<CH, 2, CONE, NW, CUBIC, RPT>), grid, dim3(256), 0, st, a); break;
+    }
 }
 
 template <int CH, bool CONE, int NW, bool CUBIC>
 static void launch_shape(const DecimVol& a, int store, dim3 grid, hipStream_t st) {
-    switch (store) {
-        case 0: hipLaunchKernelGGL((k_decimate<CH, 0, CONE, NW, CUBIC>), grid, dim3(256), 0, st, a); break;
-        case 1: hipLaunchKernelGGL((k_decimate<CH, 1, CONE, NW, CUBIC>), grid, dim3(256), 0, st, a); break;
-        default: hipLaunchKernelGGL((k_decimate<CH, 2, CONE, NW, CUBIC>), grid, dim3(256), 0, st, a); break;
+    if constexpr (CH > 1) {
+        launch_rows<CH, CONE, NW, CUBIC, decim_rows_per_lane(CH, CONE)>(a, store, grid, st);
+    } else {
+        switch (a.rpt) {
+            case 1: launch_rows<CH, CONE, NW, CUBIC, 1>(a, store, grid, st); break;
+            case 2: launch_rows<CH, CONE, NW, CUBIC, 2>(a, store, grid, st); break;
+            default: launch_rows<CH, CONE, NW, CUBIC, 4>(a, store, grid, st); break;
+        }
     }
 }
 

@@ -30,6 +30,7 @@ struct fdkod_plan_s {
     // one may start and end
     int dec_nseg = 1;
     fdkod::DecimSeg* d_segs = nullptr;
+    fdkod::DecimSplit dec_split[4] = {};   // of a whole volume's call in 1, 2, 4 and 8 chunks
     // backprojection: the public key and the kernel shape chosen for it
     fdkod::BpVariant bpv{32, 32, 48, 1};
     fdkod::BpShape bps{};
@@ -106,9 +107,9 @@ void describe(const fdkod_params& prm, fdkod_plan_s* pl);
 std::vector<BpTile> make_tiles(const fdkod_plan_s* pl, int edge);
 // launch arguments of a plan's shape over `runs` runs of its tiles
 BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs);
-// split of the widest square over a task's lanes: rows side by side in a wave
-// and tasks per square for a chunk count; the default chunk count up to most
-void decim_split(const fdkod_plan_s* pl, int ch, int* rw, int* tasks);
+// the split of a call over nv rows in ch column chunks (a batch: no segments)
+DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch);
+// the default chunk count up to most
 int decim_default_chunks(const fdkod_plan_s* pl, int most);
 // runs of zrun slices in nz
 inline int bp_zslabs(int nz, int zrun) { return (nz + zrun - 1) / zrun; }
