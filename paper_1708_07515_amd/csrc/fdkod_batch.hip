@@ -454,19 +454,27 @@ fdkod_status fdkod_batch_tune(fdkod_batch_t b, fdkod_stream_t stream, fdkod_tuni
         if ((r = upload_tables(b)) != FDKOD_OK) return r;
         if ((r = run_decimate(b, st)) != FDKOD_OK) return r;
     }
+    // (the current z run first, and no kernel twice: see fdkod_tune)
     float best = 1e30f;
-    BpVariant bestv = b->bpv;
-    for (int zr : {32, 16}) {
+    const BpVariant now = b->bpv;
+    BpVariant bestv = now;
+    std::vector<BpShape> tried;
+    for (int zr : {0, 32, 16}) {
         // the kernel follows from the z run and the geometries: one key for each z run
-        BpVariant v{};
-        bool holds = false;
+        BpVariant v = now;
+        bool holds = zr == 0;
         for (int tw : {32, 64})
             for (int th : {48, 64})
                 if (!holds) {
                     v = BpVariant{zr, tw, th, 1};
                     holds = holds_all(b, v);
                 }
-        if (!holds) continue;
+        BpShape sh;
+        if (!holds || !bp_shape(b->plans.data(), b->count, v.zrun, false, &sh)) continue;
+        bool seen = false;
+        for (const BpShape& t : tried) seen = seen || same_kernel(t, sh);
+        if (seen) continue;
+        tried.push_back(sh);
         b->bpv = v;
         if ((r = build_items(b)) != FDKOD_OK) return r;
         float ms = 0.0f;

@@ -1228,16 +1228,27 @@ fdkod_status fdkod_tune(fdkod_plan_t pl, const void* filt, void* ws, float* vol,
     if (!pl->bp_ok) return fail(FDKOD_E_UNSUPPORTED, "no backprojection variant holds this geometry");
     hipStream_t st = (hipStream_t)stream;
     fdkod_status r = FDKOD_OK;
-    // decimation chunking (its output feeds the backprojection timings)
+    // The current choice is timed first, and choices that run a kernel already
+    // timed are not: noise would pick among them, and the key that a cache file
+    // keeps (z_run also sets the slabs) would change for nothing.
+    // Decimation chunking (its output feeds the backprojection timings):
     if (pl->s > 0) {
         float best = 1e30f;
-        int bestc = pl->dec_chunks;
-        for (int c : {0, 1, 2, 4, 8}) {
+        const int now = pl->dec_chunks;
+        int bestc = now;
+        std::vector<int> tried;
+        for (int c : {now, 0, 1, 2, 4, 8}) {
             if (c > max_chunks(pl) || (c == 0 && !pl->staged_cpt)) continue;
+            const int kernel = c == 0 && pl->staged_cpt == 1 ? 1 : c;      // squares too narrow for staged rows
+            if (std::find(tried.begin(), tried.end(), kernel) != tried.end()) continue;
+            tried.push_back(kernel);
             pl->dec_chunks = c;
             float ms = 0.0f;
             r = time_ms(st, 3, [&] { return fdkod_decompose(pl, filt, ws, stream); }, &ms);
-            if (r != FDKOD_OK) return r;
+            if (r != FDKOD_OK) {
+                pl->dec_chunks = now;
+                return r;
+            }
             if (ms < best) {
                 best = ms;
                 bestc = c;
@@ -1247,15 +1258,24 @@ fdkod_status fdkod_tune(fdkod_plan_t pl, const void* filt, void* ws, float* vol,
         pl->tuned_dec_ms = best;
         if ((r = fdkod_decompose(pl, filt, ws, stream)) != FDKOD_OK) return r;
     }
-    // the kernel follows from the z run and the geometry: one key for each z run
+    // the kernel follows from the z run and the geometry: one key for each shape
     float best = 1e30f;
-    BpVariant bestv = pl->bpv;
-    for (int zr : {64, 32, 16}) {
-        BpVariant v{};
-        if (!first_variant(pl, zr, &v) || !bp_set_variant(pl, v)) continue;
+    const BpVariant now = pl->bpv;
+    BpVariant bestv = now;
+    std::vector<BpShape> tried;
+    for (int zr : {0, 64, 32, 16}) {
+        BpVariant v = now;
+        if (zr && (!first_variant(pl, zr, &v) || !bp_set_variant(pl, v))) continue;
+        bool seen = false;
+        for (const BpShape& t : tried) seen = seen || same_kernel(t, pl->bps);
+        if (seen) continue;
+        tried.push_back(pl->bps);
         float ms = 0.0f;
         r = time_ms(st, 3, [&] { return fdkod_reconstruct(pl, filt, ws, vol, stream); }, &ms);
-        if (r != FDKOD_OK) return r;
+        if (r != FDKOD_OK) {
+            bp_set_variant(pl, now);
+            return r;
+        }
         if (ms < best) {
             best = ms;
             bestv = v;

@@ -198,6 +198,9 @@ struct BpVariant {
 struct BpShape {
     int bx, zp, tw, th, ag, cost, waves;
 };
+inline bool same_kernel(const BpShape& a, const BpShape& b) {
+    return a.bx == b.bx && a.zp == b.zp && a.tw == b.tw && a.th == b.th && a.ag == b.ag;
+}
 
 hipError_t launch_bounds(const BoundsArgs& a, hipStream_t st);
 hipError_t launch_bounds_batch(const BoundsBatchArgs& a, int workgroups, hipStream_t st);
