@@ -461,12 +461,12 @@ DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch) {
     };
     if (ch == 1) {
         const double row = (double)pl->p * pl->n * (pl->store == 0 ? 4 : 2);   // bytes of a detector row, all projections
-        const bool large = 8 * row > 2.5e6;
+        const bool large = 8 * row > 2.5e6, small = 10 * row <= 1e6;
         double best = d.tasks;
         for (int rw : {2, 3, 4, 5, 8}) {
-            const double three = pl->cubic ? 1.47 : pl->cone ? (large ? 1.45 : 1.6) : 2.0;
+            const double three = pl->cubic ? 1.47 : pl->cone ? (large ? 1.45 : 1.6) : small ? 1.35 : 2.0;
             const double per = rw == 2 ? (large ? 1.1 : 1.05) : rw == 3 ? three : rw == 4 ? (large ? 1.4 : 1.3)
-                             : rw == 5 ? (10 * row <= 1e6 && !pl->cubic ? 1.25 : 2.0) : 1.9;
+                             : rw == 5 ? (small && !pl->cubic ? 1.25 : 2.0) : 1.9;
             const int piece = 64 / rw - taps, pieces = (pl->wmax + piece - 1) / piece;
             const double cost = per * pieces / rw;
             if (cost < best) {
