@@ -343,6 +343,10 @@ bool bp_set_variant(fdkod_plan_s* pl, const BpVariant& v) {
     if (!bp_shape(&pl, 1, v.zrun, true, &sh)) return false;
     pl->bpv = v;
     pl->bps = sh;
+    // thin slabs that start their own runs may take the shape of 8 pairs
+    int c = 0, r = 0;
+    bp_need(pl->n, pl->r, 16, 8, std::max((pl->nz - 1) / 2.0, 16.0), cone_side(pl), 0.05, 2, &c, &r);
+    if (sh.bx != 16 || sh.zp != 16 || !backproject_shape_for(16, 8, 1, c, r, &pl->bps_thin)) pl->bps_thin = sh;
     return true;
 }
 
@@ -413,11 +417,11 @@ std::vector<BpTile> make_tiles(const fdkod_plan_s* pl, int edge) {
     return t;
 }
 
-BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs) {
+BpArgs bp_args(const fdkod_plan_s* pl, const BpShape& sh, const BpVol& v, int runs) {
     BpArgs a{};
     a.v = v;
-    a.tiles = pl->bps.bx == 8 ? pl->d_tiles8 : pl->d_tiles;
-    a.ntiles = pl->bps.bx == 8 ? pl->ntiles8 : pl->ntiles;
+    a.tiles = sh.bx == 8 ? pl->d_tiles8 : pl->d_tiles;
+    a.ntiles = sh.bx == 8 ? pl->ntiles8 : pl->ntiles;
     a.nzt = runs;
     a.nlogical = a.ntiles * a.nzt;
     a.chunk = (a.nlogical + 7) / 8;
@@ -1142,7 +1146,7 @@ fdkod_status fdkod_reconstruct(fdkod_plan_t pl, const void* filt, const void* ws
     if (!direct && !ws) return fail(FDKOD_E_ARG, "workspace is NULL");
     if (!pl->bp_ok)
         return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds 64 x 64");
-    const BpArgs a = bp_args(pl, bp_vol(pl, filt, ws, vol), bp_zslabs((pl->nz + 1) / 2, pl->bps.zp));
+    const BpArgs a = bp_args(pl, pl->bps, bp_vol(pl, filt, ws, vol), bp_zslabs((pl->nz + 1) / 2, pl->bps.zp));
     HIP_TRY(launch_backproject(a, pl->bps, pl->store, (hipStream_t)stream), "backprojection kernel launch");
     return FDKOD_OK;
 }

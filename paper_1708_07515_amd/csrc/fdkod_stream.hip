@@ -106,27 +106,42 @@ fdkod_status launch_slab(const fdkod_plan_s* pl, const void* filt, const void* w
     // 845).  A slab that starts at a multiple of the z run takes the whole
     // volume's runs (its bits); any other starts its own, so that no slice
     // outside it is computed for their sake.
-    const int zp = pl->bps.zp, mid = (pl->nz - 1) / 2;      // last lower slice
-    const int unit = z0 % pl->bpv.zrun == 0 ? zp : 1;
+    // Such a slab may also take runs of 8 where runs of 16 reach far past it:
+    // by the shapes' cost of the slices that the workgroups compute, a run by
+    // itself at that of two (11 slices about the mid-plane, N = 333, s = 3, R =
+    // 1.75 N 155 us in two runs of 16, 100 in two of 8, 115 with one slice per row
+    // index; 24 slices, N = 500, s = 0 612 us in two of 16, 669 in three of 8).
+    const int mid = (pl->nz - 1) / 2;      // last lower slice
+    const bool own = z0 % pl->bpv.zrun != 0;
     int low0 = 0, low1 = 0, up0 = 0, up1 = 0;
-    if (z0 <= mid) {
-        low0 = z0 / unit * unit;
-        low1 = std::min(z0 + nzs - 1, mid) + 1;
-    }
-    if (z0 + nzs - 1 > mid) {
-        up0 = (pl->nz - z0 - nzs) / unit * unit;
-        up1 = pl->nz - std::max(z0, mid + 1);
-    }
-    const int nlow = bp_zslabs(low1 - low0, zp), nruns = nlow + bp_zslabs(up1 - up0, zp);
-    const int64_t waves = (int64_t)(pl->bps.bx == 8 ? pl->ntiles8 : 4 * pl->ntiles) * pl->bps.ag * ((nruns + 1) / 2);
+    auto runs = [&](const BpShape& sh, int* nlow) {
+        const int unit = own ? 1 : sh.zp;
+        if (z0 <= mid) {
+            low0 = z0 / unit * unit;
+            low1 = std::min(z0 + nzs - 1, mid) + 1;
+        }
+        if (z0 + nzs - 1 > mid) {
+            up0 = (pl->nz - z0 - nzs) / unit * unit;
+            up1 = pl->nz - std::max(z0, mid + 1);
+        }
+        *nlow = bp_zslabs(low1 - low0, sh.zp);
+        return *nlow + bp_zslabs(up1 - up0, sh.zp);
+    };
+    const BpShape &s0 = pl->bps, &s1 = pl->bps_thin;
+    int nlow = 0;
+    auto cost = [&](const BpShape& t) { return (int64_t)((runs(t, &nlow) + 1) / 2) * t.zp * t.cost; };
+    const bool thin = own && cost(s1) < cost(s0);
+    const BpShape& sh = thin ? s1 : s0;
+    const int nruns = runs(sh, &nlow);
+    const int64_t waves = (int64_t)(sh.bx == 8 ? pl->ntiles8 : 4 * pl->ntiles) * sh.ag * ((nruns + 1) / 2);
     const int per = waves <= 1024 ? 1 : 2;
-    BpArgs a = bp_args(pl, bp_vol_band(pl, filt, ws, vol, v0, nv, z0, nzs), bp_zslabs(nruns, per));
+    BpArgs a = bp_args(pl, sh, bp_vol_band(pl, filt, ws, vol, v0, nv, z0, nzs), bp_zslabs(nruns, per));
     a.low0 = low0;
     a.up0 = up0;
     a.nlow = nlow;
     a.nruns = nruns;
     a.per = per;
-    HIP_TRY(launch_backproject_slab(a, pl->bps, pl->store, st), "backprojection kernel launch");
+    HIP_TRY(launch_backproject_slab(a, sh, pl->store, st), "backprojection kernel launch");
     return FDKOD_OK;
 }
 

@@ -33,7 +33,7 @@ struct fdkod_plan_s {
     fdkod::DecimSplit dec_split[4] = {};   // of a whole volume's call in 1, 2, 4 and 8 chunks
     // backprojection: the public key and the kernel shape chosen for it
     fdkod::BpVariant bpv{32, 32, 48, 1};
-    fdkod::BpShape bps{};
+    fdkod::BpShape bps{}, bps_thin{};   // bps_thin: of thin slabs (see launch_slab)
     bool bp_ok = false;     // some variant's LDS footprint holds a block's footprint
     int ntiles = 0, ntiles8 = 0;   // tiles of 16 x 16 and of 8 x 8 voxels
     int64_t ws_row_elems = 0;  // workspace elements per detector row: P' * sum_q W_q
@@ -105,8 +105,8 @@ bool batch_variant(const fdkod_plan_s* const* pls, int count, BpVariant* out);
 void describe(const fdkod_params& prm, fdkod_plan_s* pl);
 // the squares' tiles of edge x edge voxels
 std::vector<BpTile> make_tiles(const fdkod_plan_s* pl, int edge);
-// launch arguments of a plan's shape over `runs` runs of its tiles
-BpArgs bp_args(const fdkod_plan_s* pl, const BpVol& v, int runs);
+// launch arguments of a shape over `runs` runs of the plan's tiles
+BpArgs bp_args(const fdkod_plan_s* pl, const BpShape& sh, const BpVol& v, int runs);
 // the split of a call over nv rows in ch column chunks (a batch: no segments)
 DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch);
 // the default chunk count up to most

@@ -42,3 +42,28 @@ def test_runs_match_the_volume(n, nz, s):
             # row positions below 512 rounded to 2^-16: a sample moves by that
             # part of its neighbour's difference, at most twice the largest
             assert float((slab - want).abs().max()) <= 2e-5 * float(vol.abs().max()), (z0, nzs)
+
+
+def test_thin_slabs_take_short_runs():
+    """A volume in runs of 16 pairs: thin slabs that start their own runs may
+    take the kernel of 8, slabs at the z run take the volume's bits."""
+    n, nz, p, r, s = 144, 50, 24, 1.6 * 144, 3
+    assert pkg.backproject_shape(dict(n=n, nz=nz, p=p, r=r, s=s, skip=2))["pairs"] == 16
+    proj = scan(n, p, r, 6, 41).to(DEV)
+    with pkg.Plan(n, p, r, s=s, skip=2, nz=nz) as plan:
+        filt, ws, vol = plan.empty_filtered(), plan.empty_workspace(), plan.empty_volume()
+        plan.filter(proj, filt)
+        plan.backproject(filt, vol, ws)
+        zr = plan.get_tuning()["z_run"]
+        for z0, nzs in ((19, 11), (23, 2), (1, 7), (1, 49), (26, 9), (2, 16), (0, 7), (zr, 5)):
+            v0, nr = plan.band_rows(z0, nzs)
+            _, fb, wb = plan.empty_band(nr)
+            fb.copy_(filt[:, v0:v0 + nr])
+            plan.decompose_band(fb, v0, wb)
+            slab = torch.full((nzs, n, n), float("nan"), dtype=torch.float32, device=DEV)
+            plan.reconstruct_slab(fb, wb, v0, nr, z0, slab)
+            torch.cuda.synchronize()
+            want = vol[z0:z0 + nzs]
+            if z0 % zr == 0:
+                assert torch.equal(slab, want), (z0, nzs)
+            assert float((slab - want).abs().max()) <= 2e-5 * float(vol.abs().max()), (z0, nzs)
