@@ -351,11 +351,14 @@ fdkod_status fdkod_learned_backward(fdkod_plan_t plan, const void* filt, const f
 /* Transpose of fdkod_reconstruct for s > 0: dws (float32, workspace layout,
  * overwritten) receives, for every voxel with value resid and every decimated
  * angle, resid * (pi / P') U^-2 spread over the four samples of its bilinear
- * interpolation.  resid: float32 [N_z][N][N].  Deterministic: each FP32
- * contribution is rounded to a multiple of 2^-e and the multiples are summed
- * exactly in int64 (e chosen per call from max |resid| so that no sum can
- * overflow; the step 2^-e is below 2^-60 of the largest possible sum), then
- * every entry is rounded once to FP32; a resid that holds a value that is
+ * interpolation.  resid: float32 [N_z][N][N].  Deterministic: a block of
+ * voxels adds up its contributions to an entry in a fixed order (FP32 along
+ * a voxel column and over up to four neighbours, FP64 beyond; where a close
+ * source spreads a block over more than 32 x 32 samples, each FP32 partial sum
+ * along a voxel column by itself), rounds the sum to a multiple of 2^-e, and the
+ * multiples are summed exactly in int64 (e chosen per call from max |resid| so
+ * that no sum can overflow; the step 2^-e is below 2^-60 of the largest possible
+ * sum), then every entry is rounded once to FP32; a resid that holds a value that is
  * not finite gives NaN.  The plan holds the int64 sums: the first call
  * allocates them (8 bytes per workspace element), a later call that needs
  * more grows them (hipFree waits for the device), and calls that overlap on
@@ -485,7 +488,7 @@ fdkod_status fdkod_backproject_noalloc(fdkod_plan_t plan, const void* filt, floa
  * events that the plan's geometry is meant to rule out, per kind, summed over
  * every launch on the current device since the last reset:
  *   [0] backprojection z runs whose detector rows fall outside the block's
- *       staged footprint (they contribute zero)
+ *       staged footprint (clamped)
  *   [1] backprojection columns outside the staged footprint (clamped)
  *   [2] decimation reads beyond the staged row segment
  *   [3] reserved (zero)

@@ -655,10 +655,11 @@ namespace {
 // of a 2 x 2 block from the least of their crop offsets: the spread of the
 // offsets (read back from the bounds kernel's crop table) plus 64 cpt
 // columns and the interpolation's second sample.  Squares of at most 64
-// columns (cpt = 1) go to k_decimate, which packs several rows into a wave:
-// N = 64, s = 2 12.7 -> 8.4 us, N = 256, s = 3 158 -> 121 us, N = 1000, s = 5
-// 18.4 -> 10.6 ms; above that the staged rows are faster: 68 columns, N = 320
-// 236 us against 275, 108 columns, N = 512 417 us against 524.
+// columns (cpt = 1) go to k_decimate, whose waves fit their rows and pieces to
+// the width: staged against that, N = 64, s = 2 12.7 / 8.4 us, N = 256, s = 3
+// 158 / 121 us, N = 1000, s = 5 18.4 / 10.6 ms; the staged rows were faster only
+// at 64 columns themselves (N = 298, s = 3 209 / 232 us), and are above: 68
+// columns, N = 320 236 / 275 us, 108 columns, N = 512 417 / 524 us.
 fdkod_status staged_shape(fdkod_plan_s* pl) {
     pl->staged_cpt = pl->staged_segc = 0;
     if (pl->s < 1 || pl->cone || pl->sinc || pl->cubic) return FDKOD_OK;
@@ -1068,11 +1069,9 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     if ((st = upload(pl, &pl->d_tiles, tiles)) != FDKOD_OK) return bail(st);
     if ((st = upload(pl, &pl->d_tiles8, tiles8)) != FDKOD_OK) return bail(st);
 
-    // default kernel shapes: the row-staged decimation where it applies (the
-    // paper's plain decimation), else 64 * chunks local columns per
-    // decimation wavefront (the smallest power of two covering the widest
-    // square, at most 8); the longest z run whose block footprint fits an LDS
-    // tile, one angle per stage
+    // default kernels: the row-staged decimation where it applies (the paper's
+    // plain decimation of squares of 65 to 256 columns), else k_decimate in the
+    // chunks of decim_default_chunks; the backprojection shape of bp_shape
     if ((st = staged_shape(pl)) != FDKOD_OK) return bail(st);
     if ((st = decim_segments(pl, sched)) != FDKOD_OK) return bail(st);
     for (int i = 0; i < 4; ++i) pl->dec_split[i] = decim_split(pl, 1 << i, pl->n, false);
@@ -1145,7 +1144,7 @@ fdkod_status fdkod_reconstruct(fdkod_plan_t pl, const void* filt, const void* ws
     if (direct && !filt) return fail(FDKOD_E_ARG, "filtered projections are NULL");
     if (!direct && !ws) return fail(FDKOD_E_ARG, "workspace is NULL");
     if (!pl->bp_ok)
-        return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds 64 x 64");
+        return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds every staged shape");
     const BpArgs a = bp_args(pl, pl->bps, bp_vol(pl, filt, ws, vol), bp_zslabs((pl->nz + 1) / 2, pl->bps.zp));
     HIP_TRY(launch_backproject(a, pl->bps, pl->store, (hipStream_t)stream), "backprojection kernel launch");
     return FDKOD_OK;

@@ -188,7 +188,7 @@ fdkod_status fdkod_reconstruct_slab(fdkod_plan_t pl, const void* filt_band, cons
     if (pl->s == 0 && !filt_band) return fail(FDKOD_E_ARG, "filtered band is NULL");
     if (pl->s > 0 && !ws_band) return fail(FDKOD_E_ARG, "workspace band is NULL");
     if (!pl->bp_ok)
-        return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds the LDS tiles");
+        return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds every staged shape");
     fdkod_status st = check_band(pl, v0, nrows);
     if (st != FDKOD_OK) return st;
     if ((st = check_rows_are_detector_rows(pl)) != FDKOD_OK) return st;
@@ -210,7 +210,7 @@ fdkod_status fdkod_reconstruct_streamed(fdkod_plan_t pl, const float* host_proj,
     if (nzs < 1) return fail(FDKOD_E_ARG, "slab must hold at least one slice");
     if (check_rows_are_detector_rows(pl) != FDKOD_OK) return FDKOD_E_UNSUPPORTED;
     if (!pl->bp_ok)
-        return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds the LDS tiles");
+        return fail(FDKOD_E_UNSUPPORTED, "R too small: a block's detector footprint exceeds every staged shape");
     const StreamLayout L = stream_layout(pl, nzs);
     if (work_bytes < L.total) return fail(FDKOD_E_ARG, "work buffer smaller than fdkod_streamed_bytes");
     int prev = 0;

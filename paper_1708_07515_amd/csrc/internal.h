@@ -303,9 +303,8 @@ hipError_t launch_adamw(const AdamArgs& a, hipStream_t st);
 
 // Checked builds (-DFDKOD_CHECKS).  Some kernel paths exist only to stay in
 // bounds when the host's planning has gone wrong (a backprojection z run
-// outside the staged detector rows contributes zero, a column outside the
-// staged footprint is clamped, a decimation read beyond the staged segment);
-// a checked build counts each such event in a device counter per kind, so
+// outside the staged detector rows or a column outside the staged footprint is
+// clamped, a decimation read beyond the staged segment); a checked build counts each such event in a device counter per kind, so
 // tests can require that none occurs.  Unchecked builds compile the counting
 // away.
 enum CheckKind { kCheckBpRows = 0, kCheckBpCols = 1, kCheckDecimSegment = 2, kCheckKinds = 4 };
@@ -327,11 +326,11 @@ hipError_t checks_read_decimate(unsigned long long* out, bool reset);
 // Limits the host checks before choosing a backprojection variant.
 constexpr int kTileXY = 16;      // voxels per tile side in x and y
 constexpr int kDecimUnroll = 8;  // the decimation schedule is padded to a multiple of this
-// wavefronts a small decimation is cut up into (four per SIMD): N = 64, s = 2
-// 14.8 us uncut, 8.7 cut; N = 96, s = 2, 768 waves 20.6 / 11.9; N = 128, s = 3,
-// 2048 waves 27.0 / 21.6; N = 256, s = 2, FP16, 2048 waves 115 / 69; N = 512,
-// s = 1, 2048 waves of eight chunks 285 / 251; from 4800 waves (N = 193, s = 3)
-// on nothing is left to gain
+// wavefronts a small decimation is cut up into (four per SIMD), counted for
+// each call (a volume's, a band's): N = 64, s = 2 14.8 us uncut, 8.7 cut; N = 96,
+// s = 2, 768 waves 20.6 / 11.9; N = 128, s = 3, 2048 waves 27.0 / 21.6; N = 256,
+// s = 2, FP16, 2048 waves 115 / 69; N = 512, s = 1, 2048 waves of eight chunks
+// 285 / 251; from 4800 waves (N = 193, s = 3) on nothing is left to gain
 constexpr int kDecimWaves = 4096;
 constexpr int kDecimMaxChunksWide = 4;  // column chunks per task when more than 2 windows are open
 // output rows per lane of the decimation with several column chunks: two for

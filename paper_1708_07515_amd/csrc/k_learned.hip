@@ -1054,8 +1054,10 @@ __global__ __launch_bounds__(256) void k_bp_adjoint(AdjArgs a) {
 //
 // A line's at most four terms are added in FP32 (as the rows' are), the lines
 // in FP64, and the block's sum is rounded once to a multiple of 1 / qscale and
-// added to the int64 sums: the result depends on no order, and holds fewer
-// roundings than one integer per term.  No LDS atomics: the scatter form
+// added to the int64 sums: the result depends on no order.  Against 64-bit sums
+// the error measured 1.3 to 7 times below the scatter's over ten geometries of
+// N = 32..320 (relative RMS, random residuals: N = 320 1.09e-5 / 1.69e-6, N = 96
+// 2.92e-6 / 1.31e-6; smooth ones, N = 96 4.8e-7 / 2.0e-7).  No LDS atomics: the scatter form
 // above spends its time on their conflicts and on a 64-bit conversion for
 // each term (2600 VALU instructions per thread and angle); bound here: VALU
 // issue (about 900 per thread and angle), then the LDS.
