@@ -455,7 +455,11 @@ BpArgs bp_args(const fdkod_plan_s* pl, const BpShape& sh, const BpVol& v, int ru
 // cubic, more than two windows), where even then all segments fit the chip: the
 // time is the length of a task's walk (N = 64, s = 2, sinc of six taps, cubic 34 us
 // with four rows, 14 with one; plain rows N = 64, s = 3 8.0 with two, 8.7).
-DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch) {
+//
+// A batch (batch_rows rows per lane, one segment) shares its L2 among volumes:
+// three rows of a wave don't fit there (24 volumes, N = 96, s = 2, 40 columns 106
+// us, 80 with four).
+DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, int batch_rows) {
     const int taps = pl->cubic ? 3 : 1;
     const int cols = ch * (64 - taps);
     DecimSplit d{1, decim_rows_per_lane(ch, pl->cone != 0), (pl->wmax + cols - 1) / cols, 1};
@@ -468,7 +472,7 @@ DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch) {
         const bool large = 8 * row > 2.5e6, small = 10 * row <= 1e6;
         double best = d.tasks;
         for (int rw : {2, 3, 4, 5, 8}) {
-            const double three = pl->cubic ? 1.47 : pl->cone ? (large ? 1.45 : 1.6) : small ? 1.35 : 2.0;
+            const double three = pl->cubic ? 1.47 : pl->cone ? (large ? 1.45 : 1.6) : small && !batch_rows ? 1.35 : 2.0;
             const double per = rw == 2 ? (large ? 1.1 : 1.05) : rw == 3 ? three : rw == 4 ? (large ? 1.4 : 1.3)
                              : rw == 5 ? (small && !pl->cubic ? 1.25 : 2.0) : 1.9;
             const int piece = 64 / rw - taps, pieces = (pl->wmax + piece - 1) / piece;
@@ -483,12 +487,12 @@ DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch) {
             d.rpt = r;
             return ntasks();
         };
-        if (batch) d.rpt = 2;
+        if (batch_rows) d.rpt = batch_rows;
         else if ((pl->nw > 2 || pl->cubic || pl->cone) && rows(1) * pl->dec_nseg <= kDecimWaves) d.rpt = 1;
         else if (pl->cubic && !pl->cone) d.rpt = 4;
         else d.rpt = rows(4) >= kDecimWaves && (pl->cone ? d.rw <= 2 : d.rw == 1 && 4 * row <= 6.5e6) ? 4 : 2;
     }
-    if (!batch) {
+    if (!batch_rows) {
         const int64_t want = kDecimWaves / std::max<int64_t>(1, ntasks());
         d.nseg = (int)std::max<int64_t>(1, std::min<int64_t>(want, pl->dec_nseg));
     }
@@ -503,11 +507,12 @@ DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch) {
 int decim_default_chunks(const fdkod_plan_s* pl, int most) {
     int ch = 1;
     while (ch < most && (64 - (pl->cubic ? 3 : 1)) * ch < pl->wmax) ch <<= 1;
-    const DecimSplit one = decim_split(pl, 1, pl->n, false);
+    const DecimSplit one = decim_split(pl, 1, pl->n, 0);
     return 4 * one.tasks <= 3 * ch * one.rw ? 1 : ch;
 }
 
-DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv, bool batch) {
+DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv,
+                    int batch_rows) {
     DecimVol a;
     a.filt = filt;
     a.ws = ws;
@@ -529,8 +534,8 @@ DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chun
     a.v0 = v0;
     a.nv = nv;
     const int ch = chunks > 0 ? chunks : 1;
-    const DecimSplit d = nv == pl->n && !batch ? pl->dec_split[ch == 1 ? 0 : ch == 2 ? 1 : ch == 4 ? 2 : 3]
-                                               : decim_split(pl, ch, nv, batch);
+    const DecimSplit d = nv == pl->n && !batch_rows ? pl->dec_split[ch == 1 ? 0 : ch == 2 ? 1 : ch == 4 ? 2 : 3]
+                                               : decim_split(pl, ch, nv, batch_rows);
     a.rw = d.rw;
     a.gw = 64 / d.rw;
     a.rpt = d.rpt;
@@ -1074,7 +1079,7 @@ fdkod_status fdkod_plan_create(const fdkod_params* prm, int device, fdkod_plan_t
     // chunks of decim_default_chunks; the backprojection shape of bp_shape
     if ((st = staged_shape(pl)) != FDKOD_OK) return bail(st);
     if ((st = decim_segments(pl, sched)) != FDKOD_OK) return bail(st);
-    for (int i = 0; i < 4; ++i) pl->dec_split[i] = decim_split(pl, 1 << i, pl->n, false);
+    for (int i = 0; i < 4; ++i) pl->dec_split[i] = decim_split(pl, 1 << i, pl->n, 0);
     pl->dec_chunks = pl->staged_cpt ? 0 : decim_default_chunks(pl, max_chunks(pl));
     pl->bp_ok = default_variant(pl);
     {

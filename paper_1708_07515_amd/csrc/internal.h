@@ -136,6 +136,7 @@ struct DecimBatchArgs {
     const int2* block_vol;  // [ntasks / 4]
     int nvols;
     int ntasks;             // sum of the padded task ranges
+    int rpt;                // output rows per lane of one-chunk tasks (2 or 4)
 };
 
 // Per-volume parameters of the backprojection.

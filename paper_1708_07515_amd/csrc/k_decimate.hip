@@ -76,10 +76,10 @@ __device__ __forceinline__ float next_lane(float x) {
 }
 
 // One task: square q, a group of rows, a group of columns and a segment of the
-// decimated angles, run by one wavefront.  Lanes form a.rw groups of a.gw
-// (rows of the task side by side); each lane owns RPT rows, a.rw apart, and
-// CH columns.
-template <int CH, int STORE, bool CONE, int NW, bool CUBIC, int RPT>
+// decimated angles (SEG; else all of them), run by one wavefront.  Lanes form
+// a.rw groups of a.gw (rows of the task side by side); each lane owns RPT rows,
+// a.rw apart, and CH columns.
+template <int CH, int STORE, bool CONE, int NW, bool CUBIC, int RPT, bool SEG>
 __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int lane) {
     using S = Store<STORE>;
     using T = typename S::T;
@@ -95,8 +95,8 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
     // squares read different detector rows for the same warped row.
     const int g = task % a.tasks_per_sq;
     const int sv = task / a.tasks_per_sq;
-    const int seg = sv / (a.nvb * a.nsq);
-    const int vq = sv % (a.nvb * a.nsq);
+    const int seg = SEG ? sv / (a.nvb * a.nsq) : 0;
+    const int vq = SEG ? sv % (a.nvb * a.nsq) : sv;
     const int q = CONE ? vq / a.nvb : vq % a.nsq;
     const int vb = CONE ? vq % a.nvb : vq / a.nsq;
     const int n = a.n;
@@ -111,7 +111,7 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
     // open in, ms the window open at e0 (earlier windows' parts, from before
     // m0, are dropped)
     int e0 = 0, e1 = a.nsched, ms = 0, m0 = 0, m1 = a.pd;
-    if (a.nseg > 1) {
+    if (SEG && a.nseg > 1) {
         // (P' <= 32768 angles, at most kDecimWaves segments: below 2^31)
         m0 = (int)((unsigned)(a.pd * seg) / (unsigned)a.nseg);
         m1 = (int)((unsigned)(a.pd * (seg + 1)) / (unsigned)a.nseg);
@@ -243,7 +243,7 @@ __device__ __forceinline__ void decimate_task(const DecimVol& a, int task, int l
                 }
             }
             if (G.emit[u]) {
-                const bool mine = m >= m0 && m < m1;
+                const bool mine = !SEG || (m >= m0 && m < m1);
 #pragma unroll
                 for (int r = 0; r < RPT; ++r) {
                     const int row = row0 + r * a.rw;
@@ -290,13 +290,17 @@ __global__ __launch_bounds__(256) void k_decimate(DecimVol a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int task = lblk * 4 + wave;
     if (task >= a.ntasks) return;         // no barriers in this kernel
-    decimate_task<CH, STORE, CONE, NW, CUBIC, RPT>(a, task, threadIdx.x & 63);
+    decimate_task<CH, STORE, CONE, NW, CUBIC, RPT, true>(a, task, threadIdx.x & 63);
 }
 
 // Many volumes in one launch (tasks concatenated volume after volume).  Each
 // volume uses its own chunk count (at most CHMAX) and rows per wave, so the
-// waves of a small volume do not carry idle columns.
-template <int CHMAX, int STORE>
+// waves of a small volume do not carry idle columns.  Rows per lane of one chunk
+// are the launch's: a kernel with both forms takes 15..18 % longer for two (its
+// scalar registers hold fewer waves), and the code of segments, which a batch
+// has none of, costs two chunks 14 % (4 volumes of 512^3, s = 3, BF16 4.05 / 3.55
+// ms).  32 mixed volumes of 128^3..512^3, BF16: two rows 33.9 ms, four 21.8.
+template <int CHMAX, int STORE, int RPT>
 __global__ __launch_bounds__(256) void k_decimate_batch(DecimBatchArgs a) {
     const int nblk = gridDim.x;
     const int chunk = nblk / 8;
@@ -310,10 +314,10 @@ __global__ __launch_bounds__(256) void k_decimate_batch(DecimBatchArgs a) {
     const int t = task - bv.y;
     if (t >= dv.ntasks) return;                         // padding of the volume's range
     const int lane = threadIdx.x & 63;
-    if (CHMAX >= 8 && dv.chunks >= 8) decimate_task<(CHMAX >= 8 ? 8 : 1), STORE, false, 2, false, 1>(dv, t, lane);
-    else if (CHMAX >= 4 && dv.chunks >= 4) decimate_task<(CHMAX >= 4 ? 4 : 1), STORE, false, 2, false, 1>(dv, t, lane);
-    else if (CHMAX >= 2 && dv.chunks >= 2) decimate_task<(CHMAX >= 2 ? 2 : 1), STORE, false, 2, false, 2>(dv, t, lane);
-    else decimate_task<1, STORE, false, 2, false, 2>(dv, t, lane);
+    if (CHMAX >= 8 && dv.chunks >= 8) decimate_task<(CHMAX >= 8 ? 8 : 1), STORE, false, 2, false, 1, false>(dv, t, lane);
+    else if (CHMAX >= 4 && dv.chunks >= 4) decimate_task<(CHMAX >= 4 ? 4 : 1), STORE, false, 2, false, 1, false>(dv, t, lane);
+    else if (CHMAX >= 2 && dv.chunks >= 2) decimate_task<(CHMAX >= 2 ? 2 : 1), STORE, false, 2, false, 2, false>(dv, t, lane);
+    else decimate_task<1, STORE, false, 2, false, RPT, false>(dv, t, lane);
 }
 
 template <int CH, bool CONE, int NW, bool CUBIC, int RPT>
@@ -362,13 +366,19 @@ static bool launch_ch(const DecimVol& a, int store, dim3 grid, hipStream_t st) {
     }
 }
 
+template <int CH, int RPT>
+static void launch_rows_batch(const DecimBatchArgs& a, int store, dim3 grid, hipStream_t st) {
+    switch (store) {
+        case 0: hipLaunchKernelGGL((k_decimate_batch<CH, 0, RPT>), grid, dim3(256), 0, st, a); break;
+        case 1: hipLaunchKernelGGL((k_decimate_batch<CH, 1, RPT>), grid, dim3(256), 0, st, a); break;
+        default: hipLaunchKernelGGL((k_decimate_batch<CH, 2, RPT>), grid, dim3(256), 0, st, a); break;
+    }
+}
+
 template <int CH>
 static void launch_ch_batch(const DecimBatchArgs& a, int store, dim3 grid, hipStream_t st) {
-    switch (store) {
-        case 0: hipLaunchKernelGGL((k_decimate_batch<CH, 0>), grid, dim3(256), 0, st, a); break;
-        case 1: hipLaunchKernelGGL((k_decimate_batch<CH, 1>), grid, dim3(256), 0, st, a); break;
-        default: hipLaunchKernelGGL((k_decimate_batch<CH, 2>), grid, dim3(256), 0, st, a); break;
-    }
+    if (a.rpt == 4) launch_rows_batch<CH, 4>(a, store, grid, st);
+    else launch_rows_batch<CH, 2>(a, store, grid, st);
 }
 
 static dim3 decimate_grid(int ntasks) {

@@ -107,8 +107,9 @@ void describe(const fdkod_params& prm, fdkod_plan_s* pl);
 std::vector<BpTile> make_tiles(const fdkod_plan_s* pl, int edge);
 // launch arguments of a shape over `runs` runs of the plan's tiles
 BpArgs bp_args(const fdkod_plan_s* pl, const BpShape& sh, const BpVol& v, int runs);
-// the split of a call over nv rows in ch column chunks (a batch: no segments)
-DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, bool batch);
+// the split of a call over nv rows in ch column chunks (a batch: batch_rows rows
+// per lane of one chunk, no segments)
+DecimSplit decim_split(const fdkod_plan_s* pl, int ch, int nv, int batch_rows);
 // the default chunk count up to most
 int decim_default_chunks(const fdkod_plan_s* pl, int most);
 // runs of zrun slices in nz
@@ -118,7 +119,7 @@ inline int bp_zslabs(int nz, int zrun) { return (nz + zrun - 1) / zrun; }
 // _band forms cover detector rows [v0, v0 + nv) and output slices
 // [zbase, zbase + nzs)
 DecimVol decim_args(const fdkod_plan_s* pl, const void* filt, void* ws, int chunks, int v0, int nv,
-                    bool batch = false);
+                    int batch_rows = 0);
 BpVol bp_vol(const fdkod_plan_s* pl, const void* filt, const void* ws, float* vol);
 BpVol bp_vol_band(const fdkod_plan_s* pl, const void* filt, const void* ws, float* vol, int v0, int nv,
                   int zbase, int nzs);

@@ -109,3 +109,32 @@ def test_batch_equals_single():
                 torch.cuda.synchronize()
                 e = plan.workspace_bytes
                 assert _close_bits(w[:e], one[:e]), v
+
+
+@pytest.mark.parametrize("store,wide", [("f32", ()), ("bf16", ()), ("f16", (150, 52, 600.0, 1)),
+                                        ("f32", (298, 20, 1192.0, 1)), ("bf16", (340, 20, 1360.0, 1))])
+def test_large_batch_equals_single(store, wide):
+    """Batches of at least 4096 tasks, whose lanes take four rows of a narrow
+    volume each, alone and beside a volume of two, four or eight column chunks."""
+    vols = [dict(n=n, p=72, r=4.0 * n, s=4) for n in (65, 96, 99, 131)]
+    if wide:
+        n, p, r, s = wide
+        vols.insert(2, dict(n=n, p=p, r=r, s=s))
+    with pkg.Batch(vols, store=store) as b:
+        filt, ws = [], []
+        for i, pl in enumerate(b.plans):
+            g = torch.Generator().manual_seed(40 + i)
+            f = torch.randn(pl.empty_filtered().shape, generator=g).to(pl.store_torch_dtype())
+            filt.append(f.to(DEV))
+            ws.append(pl.empty_workspace())
+        proj = [torch.zeros((pl.p, pl.n, pl.n), device=DEV) for pl in b.plans]
+        b.bind(proj, filt, ws, [pl.empty_volume() for pl in b.plans])
+        b.run()
+        torch.cuda.synchronize()
+        for v, f, w in zip(vols, filt, ws):
+            with pkg.Plan(**v, store=store) as plan:
+                one = plan.empty_workspace()
+                plan.decompose(f, one)
+                torch.cuda.synchronize()
+                e = plan.workspace_bytes
+                assert torch.equal(w[:e], one[:e]), v
