@@ -27,7 +27,7 @@
 //    cone-corrected rows (46 cycles per row and step, scalar unit shared by
 //    four SIMDs);
 //  - a small volume's decimated angles go to several tasks (see DecimSeg).
-// Before -> after: 256 volumes of 32^3..64^3, BF16 1000 -> 320 us; N = 64,
+// Before -> after: 256 volumes of 32^3..64^3, BF16 1000 -> 260 us; N = 64,
 // s = 2 14 -> 8 us; N = 193, cone-corrected FP16 rows 249 -> 118 us; N = 384,
 // windowed sinc and cubic 1113 -> 613 us; N = 1000, s = 5 18.4 (row-staged
 // kernel) -> 10.6 ms.
