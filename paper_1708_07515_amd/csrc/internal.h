@@ -337,8 +337,9 @@ constexpr int kDecimMaxChunksWide = 4;  // column chunks per task when more than
 // output rows per lane of the decimation with several column chunks: two for
 // two of them (they share the step's tables and address arithmetic) and for
 // four of cone-corrected rows (N = 2000, s = 4 108 -> 94 ms, 83 since the next
-// step's loads stay in flight; one detector row per step was 97), else one (the accumulators of more chunks fill the registers);
-// one chunk takes 1, 2 or 4 (decim_split)
+// step's loads stay in flight; one detector row per step was 97), else one (the
+// accumulators of more chunks fill the registers); one chunk takes 1, 2 or 4
+// (decim_split)
 __host__ __device__ constexpr int decim_rows_per_lane(int chunks, bool cone) {
     return chunks == 2 || (chunks == 4 && cone) ? 2 : 1;
 }
